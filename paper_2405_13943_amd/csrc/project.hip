@@ -661,6 +661,30 @@ __global__ __launch_bounds__(128) void k_project_bwd_acc(const T* __restrict__ P
     }
 }
 
+// Column of the i-th Gaussian (from 0) that no job covers, for jobs over
+// disjoint ranges in any order: the smallest c with
+// c = i + (columns of the jobs that start at or before c), reached by
+// iterating that map from c = i (it never passes the answer, and between two
+// steps at least one more job is counted, so n_jobs + 1 steps end it).
+__device__ inline int64_t uncovered_column(const gs_frame& frame, int64_t i) {
+    int64_t c = i;
+    for (int it = 0; it <= frame.n_jobs; it++) {
+        int64_t next = i;
+        for (int j = 0; j < frame.n_jobs; j++)
+            if (frame.jobs[j].g0 <= c) next += frame.jobs[j].g1 - frame.jobs[j].g0;
+        if (next == c) break;
+        c = next;
+    }
+    return c;
+}
+
+// workgroups of 256 per plane of n_unc uncovered columns (they stride over
+// the rest: the whole grid stays far below 2^32 threads)
+__host__ __device__ inline unsigned uncovered_blocks(int64_t n_unc) {
+    const int64_t b = (n_unc + 255) / 256;
+    return unsigned(b < 32768 ? b : 32768);
+}
+
 // Fused projection backward + Adam/ADMM for jobs over disjoint Gaussian
 // ranges (one record per Gaussian).  A block of kFusedBlock records works in
 // two phases.  (1) Each thread runs the chain rule of its record and leaves in
@@ -672,7 +696,13 @@ __global__ __launch_bounds__(128) void k_project_bwd_acc(const T* __restrict__ P
 // with 16-byte accesses, else one Gaussian per thread.  The gradient never
 // reaches HBM and the parameters read by the chain are still in cache for the
 // update.  Same arithmetic as k_project_bwd_rec followed by k_adam_admm.
-constexpr int kFusedBlock = 256;
+//
+// Columns that no job covers (the padding between blocks, views of a part of
+// the store) take the update with a zero gradient in workgroups past those of
+// the records, one plane of 256 uncovered columns each.  As a kernel of its
+// own over all columns, a thread walking the planes of each, they took 27 us
+// for 32 padding columns beside 500k records.
+constexpr int kFusedBlock = 256;      // also the width of uncovered_blocks
 
 // gradient of plane a of the block's Gaussian i from the phase-1 LDS arrays
 // (geo [11][kFusedBlock], Y [NK][kFusedBlock], dc [3][kFusedBlock])
@@ -770,10 +800,32 @@ __global__ __launch_bounds__(kFusedBlock) void k_project_bwd_adam(
     const float* __restrict__ pg,
     float* __restrict__ M,
     int64_t sm, float* __restrict__ V, int64_t sv, const float* __restrict__ Wp, int64_t sw,
-    const float* __restrict__ mask, AdamConsts c, uint32_t* __restrict__ status) {
+    const float* __restrict__ mask, AdamConsts c, uint32_t* __restrict__ status, unsigned rec_blocks, int64_t n,
+    int64_t n_unc) {
     constexpr int NK = (D + 1) * (D + 1);
     constexpr int A = 11 + 3 * NK;
     if (adam_skipped(status)) return;   // uniform over the grid: no wavefront reaches the barrier
+    if (blockIdx.x >= rec_blocks) {     // uniform: a plane of 256 uncovered columns
+        const unsigned per_plane = uncovered_blocks(n_unc);
+        const unsigned b = blockIdx.x - rec_blocks;
+        const int a = int(b / per_plane);
+        const int grp = plane_group(a);
+        float fin = 0.f;
+        for (int64_t i = int64_t(b % per_plane) * kFusedBlock + threadIdx.x; i < n_unc;
+             i += int64_t(per_plane) * kFusedBlock) {
+            const int64_t gu = uncovered_column(frame, i);
+            if (gu >= n) continue;
+            float xv = X[a * sx + gu], mv = M[a * sm + gu], vv = V[a * sv + gu];
+            const float wv = PEN ? Wp[a * sw + gu] : 0.f;
+            adam_one(xv, 0.f, mv, vv, wv, PEN ? c.rho[grp] * (MASK ? mask[gu] : 1.f) : 0.f, c.lr[grp], c);
+            X[a * sx + gu] = xv;
+            M[a * sm + gu] = mv;
+            V[a * sv + gu] = vv;
+            adam_finite(fin, xv, vv);
+        }
+        adam_flag(status, fin);
+        return;
+    }
     __shared__ __align__(16) float s_geo[11][kFusedBlock];
     __shared__ __align__(16) float s_Y[NK][kFusedBlock];
     __shared__ __align__(16) float s_dc[3][kFusedBlock];
@@ -823,43 +875,17 @@ __global__ __launch_bounds__(kFusedBlock) void k_project_bwd_adam(
     adam_flag(status, fin);
 }
 
-// Adam/ADMM with a zero gradient for Gaussians outside every job (disjoint
-// jobs that do not cover [0, n)); the fused kernel updates all the others.
-template <bool PEN, bool MASK>
-__global__ __launch_bounds__(256) void k_adam_uncovered(int64_t n, gs_frame frame, int A, float* __restrict__ X,
-                                                        int64_t sx, float* __restrict__ M, int64_t sm,
-                                                        float* __restrict__ V, int64_t sv,
-                                                        const float* __restrict__ Wp, int64_t sw,
-                                                        const float* __restrict__ mask, AdamConsts c,
-                                                        uint32_t* __restrict__ status) {
-    const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (g >= n || adam_skipped(status)) return;
-    for (int j = 0; j < frame.n_jobs; j++)
-        if (g >= frame.jobs[j].g0 && g < frame.jobs[j].g1) return;
-    const float k = MASK ? mask[g] : 1.f;
-    float fin = 0.f;
-    for (int a = 0; a < A; a++) {
-        const int grp = plane_group(a);
-        float xv = X[a * sx + g], mv = M[a * sm + g], vv = V[a * sv + g];
-        const float wv = PEN ? Wp[a * sw + g] : 0.f;
-        adam_one(xv, 0.f, mv, vv, wv, PEN ? c.rho[grp] * k : 0.f, c.lr[grp], c);
-        X[a * sx + g] = xv;
-        M[a * sm + g] = mv;
-        V[a * sv + g] = vv;
-        adam_finite(fin, xv, vv);
-    }
-    adam_flag(status, fin);
-}
-
-// zeros for Gaussians outside every job (disjoint jobs that do not cover [0, n))
+// zeros for Gaussians outside every job (disjoint jobs that do not cover [0, n)):
+// one thread per (uncovered column, plane), grid.y the planes.  A thread per
+// column of the whole store, planes in turn, took 27 us at 500k columns of
+// which 32 were uncovered.
 template <typename T>
-__global__ __launch_bounds__(256) void k_zero_uncovered(int64_t n, gs_frame frame, int A, T* __restrict__ grad,
-                                                        int64_t gstride) {
-    const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (g >= n) return;
-    for (int j = 0; j < frame.n_jobs; j++)
-        if (g >= frame.jobs[j].g0 && g < frame.jobs[j].g1) return;
-    for (int a = 0; a < A; a++) grad[int64_t(a) * gstride + g] = T(0);
+__global__ __launch_bounds__(256) void k_zero_uncovered(int64_t n, int64_t n_unc, gs_frame frame,
+                                                        T* __restrict__ grad, int64_t gstride) {
+    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n_unc; i += int64_t(gridDim.x) * blockDim.x) {
+        const int64_t g = uncovered_column(frame, i);
+        if (g < n) grad[int64_t(blockIdx.y) * gstride + g] = T(0);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -896,10 +922,11 @@ static void project_bwd_dispatch(const gs_params& p, const gs_frame& f, const gs
     const T* P = static_cast<const T*>(p.data);
     T* Gd = static_cast<T*>(grad.data);
     if (f.jobs_disjoint) {
-        const bool covers = f.n_records == p.n && f.g_max == p.n;
-        if (!covers)
-            GS_LAUNCH("k_zero_uncovered", (k_zero_uncovered<T>), dim3(unsigned((p.n + 255) / 256)), dim3(256), 0, s, p.n, f,
-                               11 + 3 * (D + 1) * (D + 1), Gd, grad.stride);
+        const int64_t n_unc = p.n - f.n_records;   // disjoint jobs: every record is another column
+        if (n_unc > 0)
+            GS_LAUNCH("k_zero_uncovered", (k_zero_uncovered<T>),
+                      dim3(uncovered_blocks(n_unc), 11 + 3 * (D + 1) * (D + 1)), dim3(256), 0, s, p.n, n_unc, f, Gd,
+                      grad.stride);
         if (f.n_records > 0)
             GS_LAUNCH("k_project_bwd_rec", (k_project_bwd_rec<T, D>), dim3(unsigned((f.n_records + 127) / 128)), dim3(128), 0, s,
                                P, p.stride, f, cfg, rec, M, pair_off, capacity, L, pg, Gd, grad.stride);
@@ -939,21 +966,21 @@ static void project_bwd_adam_launch(gs_params& x, const gs_frame& f, const gs_ra
     float* Vo = static_cast<float*>(v.data);
     const float* Wd = w ? static_cast<const float*>(w->data) : nullptr;
     const int64_t sw = w ? w->stride : 0;
-    const bool covers = f.n_records == x.n && f.g_max == x.n;
-    if (!covers)
-        GS_LAUNCH("k_adam_uncovered", (k_adam_uncovered<PEN, MASK>), dim3(unsigned((x.n + 255) / 256)), dim3(256), 0, s, x.n, f,
-                           11 + 3 * (D + 1) * (D + 1), X, x.stride, Mo, m.stride, Vo, v.stride, Wd, sw, mask, c,
-                           status);
     const bool vec = aligned16(X) && aligned16(Mo) && aligned16(Vo) && (!Wd || aligned16(Wd)) &&
                      (!mask || aligned16(mask)) && x.stride % 4 == 0 && m.stride % 4 == 0 && v.stride % 4 == 0 &&
                      sw % 4 == 0;
-    const dim3 grid(unsigned((f.n_records + kFusedBlock - 1) / kFusedBlock)), block(kFusedBlock);
-    if (f.n_records > 0 && vec)
+    constexpr unsigned A = 11 + 3 * (D + 1) * (D + 1);
+    const unsigned rec_blocks = unsigned((f.n_records + kFusedBlock - 1) / kFusedBlock);
+    const int64_t n_unc = x.n > f.n_records ? x.n - f.n_records : 0;   // disjoint jobs: every record is another column
+    const dim3 grid(rec_blocks + A * uncovered_blocks(n_unc)), block(kFusedBlock);
+    if (vec)
         GS_LAUNCH("k_project_bwd_adam", (k_project_bwd_adam<D, PEN, MASK, true>), grid, block, 0, s, X, x.stride, f,
-                  cfg, rec, M, pair_off, capacity, L, pg, Mo, m.stride, Vo, v.stride, Wd, sw, mask, c, status);
-    else if (f.n_records > 0)
+                  cfg, rec, M, pair_off, capacity, L, pg, Mo, m.stride, Vo, v.stride, Wd, sw, mask, c, status,
+                  rec_blocks, x.n, n_unc);
+    else
         GS_LAUNCH("k_project_bwd_adam", (k_project_bwd_adam<D, PEN, MASK, false>), grid, block, 0, s, X, x.stride,
-                  f, cfg, rec, M, pair_off, capacity, L, pg, Mo, m.stride, Vo, v.stride, Wd, sw, mask, c, status);
+                  f, cfg, rec, M, pair_off, capacity, L, pg, Mo, m.stride, Vo, v.stride, Wd, sw, mask, c, status,
+                  rec_blocks, x.n, n_unc);
 }
 
 template <int D>

@@ -114,3 +114,30 @@ def test_shared_gaussians_rejected():
     with pytest.raises(gs.GsError, match="share"):
         gs.render_bwd_adam(x, frame, cfg, buf, m, v, None, None, gs.adam_cfg(LR, RHO, 1), gs.LOSS_L1, target)
     assert np.isfinite(x.cpu().numpy()).all()
+
+
+@pytest.mark.parametrize("ranges", [
+    [(0, 0), (300, 301)],                                   # an empty job, one Gaussian
+    [(1500, 1990), (10, 260), (260, 300), (301, 1499)],     # jobs out of column order, gaps of 10, 1, 1 and 10
+    [(700, 956)],                                           # gaps longer than a workgroup on both sides
+])
+def test_columns_no_job_covers(ranges):
+    """Columns outside every job: zero gradient planes from the two-call
+    backward (over a buffer of NaN) and the zero-gradient update from the
+    fused call, equal to the two calls on every column."""
+    s = scenes.config1()
+    x = torch.from_numpy(s.params).cuda()
+    cfg = gs.raster_cfg((16, 16))
+    frame = gs.Frame([s.cams[0]], [gs.JobSpec(0, a, b, 1.0) for a, b in ranges], cfg)
+    assert frame.jobs_disjoint
+    target = torch.rand(3 * frame.n_pixels, generator=torch.Generator().manual_seed(4)).cuda()
+    buf = gs.rasterize(x, frame, cfg)
+    grad = torch.full_like(x, float("nan"))
+    gs.render_bwd(x, frame, cfg, buf, grad, gs.LOSS_L1, target)
+    covered = torch.zeros(x.shape[1], dtype=torch.bool, device="cuda")
+    for a, b in ranges:
+        covered[a:b] = True
+    assert torch.isfinite(grad).all()
+    assert (grad[:, ~covered] == 0).all()
+    a, b = both_paths(x, frame, cfg, target, True, True, step=4, seed=9)
+    assert_same(a, b)
