@@ -141,8 +141,9 @@ typedef struct {
                                 the whole list: 1 (0 = 1), 2 (16x8, 16x16, 32x8) or 4 (16x16,
                                 32x8); GS_WAVES_ADAPTIVE picks 1, 2 or 4 per tile from its
                                 list length against the frame mean (4 above 4x, 2 above
-                                1.25x; needs gs_bins.tile_order).  Images do not depend on them; gradients only
-                                through the order of their sums. */
+                                1.25x; needs gs_bins.tile_order).  Frames of few tiles take more than
+                                1 or the plan's count where that fills the chip.  Images do not depend
+                                on them; gradients only through the order of their sums. */
 } gs_raster_cfg;
 
 #define GS_WAVES_ADAPTIVE (-1)

@@ -110,9 +110,6 @@ __host__ __device__ inline bool bwd_adaptive(const gs_raster_cfg& c) { return c.
 __host__ __device__ inline int bwd_waves(const gs_raster_cfg& c) {
     return bwd_adaptive(c) ? 0 : (c.bwd_waves <= 1 ? 1 : c.bwd_waves);
 }
-// backward partial slots per tile pair the projection backward reads: one
-// per wavefront; adaptive: one (split tiles fold theirs into the first)
-__host__ __device__ inline int bwd_slots(const gs_raster_cfg& c) { return bwd_adaptive(c) ? 1 : bwd_waves(c); }
 
 // Wavefronts of one tile in an adaptive compositing pass, from its list
 // length against the frame's mean list length: 4 above 4 x the mean, 2 above
@@ -152,11 +149,12 @@ __device__ inline bool plan_wave(const uint32_t* __restrict__ order, int n_tiles
     return t < nt;
 }
 
-// Partials of wavefront `sub` for pair e in the adaptive layout: slot 0 of
-// every pair dense at e, the slots of the further wavefronts of split tiles
-// after all of them (3 per pair), so a one-wavefront tile's pairs stay
-// contiguous.  Capacity counts pairs; 9 values per slot.
-__host__ __device__ inline int64_t adaptive_slot(uint64_t capacity, uint64_t e, int sub) {
+// Partials of wavefront `sub` for pair e: slot 0 of every pair dense at e,
+// the slots of the further wavefronts of split tiles after all of them (3
+// per pair), so a one-wavefront tile's pairs stay contiguous.  The split
+// tiles' wavefronts fold theirs into slot 0, the only one the projection
+// backward reads.  Capacity counts pairs; 9 values per slot.
+__host__ __device__ inline int64_t partial_slot(uint64_t capacity, uint64_t e, int sub) {
     return sub == 0 ? int64_t(e) * 9 : (int64_t(capacity) + int64_t(e) * 3 + (sub - 1)) * 9;
 }
 
@@ -239,8 +237,19 @@ __device__ inline float row_sum_last(float v) {
     return v;
 }
 
+// (the two halves of a double moved by the same DPP steps)
+template <int CTRL>
+__device__ inline double dpp_move_bc_f64(double v) {
+    const uint64_t u = uint64_t(__double_as_longlong(v));
+    const uint32_t lo = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(u)), CTRL, 0xf, 0xf, true));
+    const uint32_t hi = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(u >> 32)), CTRL, 0xf, 0xf, true));
+    return __longlong_as_double((long long)(uint64_t(lo) | uint64_t(hi) << 32));
+}
 __device__ inline double row_sum_last(double v) {
-    for (int off = 8; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
+    v += dpp_move_bc_f64<0xb1>(v);
+    v += dpp_move_bc_f64<0x4e>(v);
+    v += dpp_move_bc_f64<0x114>(v);
+    v += dpp_move_bc_f64<0x118>(v);
     return v;
 }
 

@@ -411,22 +411,14 @@ __device__ inline void record_pairs(uint32_t ntiles, uint32_t off, uint64_t capa
     np = ntiles == 0 || p0 >= capacity ? 0 : (p0 + ntiles > capacity ? capacity - p0 : ntiles);
 }
 
-// Where the compositing backward left a pair's partials: `slots` consecutive
-// slots per pair, one per wavefront of its tile (one when the wavefronts were
-// adaptive: split tiles fold theirs into the first).
-struct PartialLayout {
-    int slots;
-};
-
-// Per lane: the 9 partials of its record summed over its pairs' slots (pair,
-// then slot, ascending; large records cooperatively).  Every lane of the wave
-// must call this.
+// Per lane: the 9 partials of its record summed over its pairs (ascending;
+// large records cooperatively).  Every lane of the wave must call this.
 template <typename T>
-__device__ inline void record_partials(const T* __restrict__ pg, const PartialLayout& L, const uint4& m,
-                                       uint32_t off, uint64_t capacity, T* d) {
+__device__ inline void record_partials(const T* __restrict__ pg, const uint4& m, uint32_t off, uint64_t capacity,
+                                       T* d) {
     uint64_t p0, np;
     record_pairs(meta_tiles(m.y), off, capacity, p0, np);
-    record_pair_sum(pg, p0 * uint64_t(L.slots), np * uint64_t(L.slots), d);
+    record_pair_sum(pg, p0, np, d);
 }
 
 // Chain rule of one visible record of Gaussian g seen by `camera`; emit(a, v)
@@ -607,7 +599,7 @@ __global__ __launch_bounds__(128) void k_project_bwd_rec(const T* __restrict__ P
                                                           gs_raster_cfg cfg, const T* __restrict__ rec,
                                                           const uint4* __restrict__ meta,
                                                           const uint32_t* __restrict__ pair_off, uint64_t capacity,
-                                                          PartialLayout L, const T* __restrict__ pg, T* __restrict__ grad,
+                                                          const T* __restrict__ pg, T* __restrict__ grad,
                                                           int64_t gstride) {
     constexpr int A = 11 + 3 * (D + 1) * (D + 1);
     const int64_t r = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -619,7 +611,7 @@ __global__ __launch_bounds__(128) void k_project_bwd_rec(const T* __restrict__ P
     const uint32_t ntiles = meta_tiles(m.y);
     const T axis = ntiles ? rec[r * GS_REC_WORDS + 9] : T(0);   // moment frame, loaded early
     T d[9];
-    record_partials(pg, L, m, ntiles ? pair_off[r] : 0u, capacity, d);
+    record_partials(pg, m, ntiles ? pair_off[r] : 0u, capacity, d);
     if (!active) return;
     T* gout = grad + g;
     if (ntiles == 0) {
@@ -638,7 +630,7 @@ __global__ __launch_bounds__(128) void k_project_bwd_acc(const T* __restrict__ P
                                                           gs_frame frame, gs_raster_cfg cfg,
                                                           const T* __restrict__ rec, const uint4* __restrict__ meta,
                                                           const uint32_t* __restrict__ pair_off, uint64_t capacity,
-                                                          PartialLayout L, const T* __restrict__ pg, T* __restrict__ grad,
+                                                          const T* __restrict__ pg, T* __restrict__ grad,
                                                           int64_t gstride) {
     constexpr int A = 11 + 3 * (D + 1) * (D + 1);
     const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -654,7 +646,7 @@ __global__ __launch_bounds__(128) void k_project_bwd_acc(const T* __restrict__ P
         const uint32_t ntiles = meta_tiles(m.y);
         const T axis = ntiles ? rec[r * GS_REC_WORDS + 9] : T(0);
         T d[9];
-        record_partials(pg, L, m, ntiles ? pair_off[r] : 0u, capacity, d);
+        record_partials(pg, m, ntiles ? pair_off[r] : 0u, capacity, d);
         if (ntiles == 0) continue;
         record_chain<T, D>(P, stride, g, frame.cams[job.cam], cfg, m.y, d, axis,
                            [&](int a, T v) { gout[int64_t(a) * gstride] += v; });
@@ -796,7 +788,7 @@ __device__ inline void adam_block_one(float* __restrict__ X, int64_t sx, float* 
 template <int D, bool PEN, bool MASK, bool VEC>
 __global__ __launch_bounds__(kFusedBlock) void k_project_bwd_adam(
     float* X, int64_t sx, gs_frame frame, gs_raster_cfg cfg, const float* __restrict__ rec,
-    const uint4* __restrict__ meta, const uint32_t* __restrict__ pair_off, uint64_t capacity, PartialLayout L,
+    const uint4* __restrict__ meta, const uint32_t* __restrict__ pair_off, uint64_t capacity,
     const float* __restrict__ pg,
     float* __restrict__ M,
     int64_t sm, float* __restrict__ V, int64_t sv, const float* __restrict__ Wp, int64_t sw,
@@ -840,7 +832,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_project_bwd_adam(
     const uint32_t ntiles = meta_tiles(m.y);
     const float axis = ntiles ? rec[r * GS_REC_WORDS + 9] : 0.f;   // moment frame, loaded early
     float d[9];
-    record_partials(pg, L, m, ntiles ? pair_off[r] : 0u, capacity, d);
+    record_partials(pg, m, ntiles ? pair_off[r] : 0u, capacity, d);
 
     // phase 1: chain rule into LDS
     float Y[NK], dc[3];
@@ -907,17 +899,10 @@ hipError_t launch_project(const gs_params& p, const gs_frame& f, const gs_raster
     return hipGetLastError();
 }
 
-template <typename T>
-static PartialLayout partial_layout(const gs_raster_cfg& cfg, const gs_bins&, const T*) {
-    PartialLayout L;
-    L.slots = bwd_slots(cfg);
-    return L;
-}
-
 template <typename T, int D>
 static void project_bwd_dispatch(const gs_params& p, const gs_frame& f, const gs_raster_cfg& cfg, const T* rec,
                                  const uint4* M,
-                                 const uint32_t* pair_off, uint64_t capacity, const PartialLayout& L, const T* pg,
+                                 const uint32_t* pair_off, uint64_t capacity, const T* pg,
                                  gs_params& grad, hipStream_t s) {
     const T* P = static_cast<const T*>(p.data);
     T* Gd = static_cast<T*>(grad.data);
@@ -929,10 +914,10 @@ static void project_bwd_dispatch(const gs_params& p, const gs_frame& f, const gs
                       grad.stride);
         if (f.n_records > 0)
             GS_LAUNCH("k_project_bwd_rec", (k_project_bwd_rec<T, D>), dim3(unsigned((f.n_records + 127) / 128)), dim3(128), 0, s,
-                               P, p.stride, f, cfg, rec, M, pair_off, capacity, L, pg, Gd, grad.stride);
+                               P, p.stride, f, cfg, rec, M, pair_off, capacity, pg, Gd, grad.stride);
     } else {
         GS_LAUNCH("k_project_bwd_acc", (k_project_bwd_acc<T, D>), dim3(unsigned((p.n + 127) / 128)), dim3(128), 0, s, P,
-                           p.stride, p.n, f, cfg, rec, M, pair_off, capacity, L, pg, Gd, grad.stride);
+                           p.stride, p.n, f, cfg, rec, M, pair_off, capacity, pg, Gd, grad.stride);
     }
 }
 
@@ -941,14 +926,13 @@ hipError_t launch_project_bwd(const gs_params& p, const gs_frame& f, const gs_ra
                               const uint32_t* meta, const gs_bins& bins, const T* pg, gs_params& grad, hipStream_t s) {
     if (p.n == 0) return hipSuccess;
     const uint4* M = reinterpret_cast<const uint4*>(meta);
-    const PartialLayout L = partial_layout(cfg, bins, pg);
     const uint32_t* po = bins.pair_off;
     const uint64_t cap = bins.capacity;
     switch (p.sh_degree) {
-        case 0: project_bwd_dispatch<T, 0>(p, f, cfg, rec, M, po, cap, L, pg, grad, s); break;
-        case 1: project_bwd_dispatch<T, 1>(p, f, cfg, rec, M, po, cap, L, pg, grad, s); break;
-        case 2: project_bwd_dispatch<T, 2>(p, f, cfg, rec, M, po, cap, L, pg, grad, s); break;
-        default: project_bwd_dispatch<T, 3>(p, f, cfg, rec, M, po, cap, L, pg, grad, s); break;
+        case 0: project_bwd_dispatch<T, 0>(p, f, cfg, rec, M, po, cap, pg, grad, s); break;
+        case 1: project_bwd_dispatch<T, 1>(p, f, cfg, rec, M, po, cap, pg, grad, s); break;
+        case 2: project_bwd_dispatch<T, 2>(p, f, cfg, rec, M, po, cap, pg, grad, s); break;
+        default: project_bwd_dispatch<T, 3>(p, f, cfg, rec, M, po, cap, pg, grad, s); break;
     }
     return hipGetLastError();
 }
@@ -958,8 +942,7 @@ static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 template <int D, bool PEN, bool MASK>
 static void project_bwd_adam_launch(gs_params& x, const gs_frame& f, const gs_raster_cfg& cfg, const float* rec,
                                     const uint4* M,
-                                    const uint32_t* pair_off, uint64_t capacity, const PartialLayout& L,
-                                    const float* pg, gs_params& m, gs_params& v, const gs_params* w,
+                                    const uint32_t* pair_off, uint64_t capacity, const float* pg, gs_params& m, gs_params& v, const gs_params* w,
                                     const float* mask, const AdamConsts& c, uint32_t* status, hipStream_t s) {
     float* X = static_cast<float*>(x.data);
     float* Mo = static_cast<float*>(m.data);
@@ -975,23 +958,23 @@ static void project_bwd_adam_launch(gs_params& x, const gs_frame& f, const gs_ra
     const dim3 grid(rec_blocks + A * uncovered_blocks(n_unc)), block(kFusedBlock);
     if (vec)
         GS_LAUNCH("k_project_bwd_adam", (k_project_bwd_adam<D, PEN, MASK, true>), grid, block, 0, s, X, x.stride, f,
-                  cfg, rec, M, pair_off, capacity, L, pg, Mo, m.stride, Vo, v.stride, Wd, sw, mask, c, status,
+                  cfg, rec, M, pair_off, capacity, pg, Mo, m.stride, Vo, v.stride, Wd, sw, mask, c, status,
                   rec_blocks, x.n, n_unc);
     else
         GS_LAUNCH("k_project_bwd_adam", (k_project_bwd_adam<D, PEN, MASK, false>), grid, block, 0, s, X, x.stride,
-                  f, cfg, rec, M, pair_off, capacity, L, pg, Mo, m.stride, Vo, v.stride, Wd, sw, mask, c, status,
+                  f, cfg, rec, M, pair_off, capacity, pg, Mo, m.stride, Vo, v.stride, Wd, sw, mask, c, status,
                   rec_blocks, x.n, n_unc);
 }
 
 template <int D>
 static void project_bwd_adam_pen(gs_params& x, const gs_frame& f, const gs_raster_cfg& cfg, const float* rec,
                                  const uint4* M,
-                                 const uint32_t* po, uint64_t cap, const PartialLayout& L, const float* pg,
+                                 const uint32_t* po, uint64_t cap, const float* pg,
                                  gs_params& m, gs_params& v, const gs_params* w, const float* mask,
                                  const AdamConsts& c, uint32_t* st, hipStream_t s) {
-    if (w && mask) project_bwd_adam_launch<D, true, true>(x, f, cfg, rec, M, po, cap, L, pg, m, v, w, mask, c, st, s);
-    else if (w) project_bwd_adam_launch<D, true, false>(x, f, cfg, rec, M, po, cap, L, pg, m, v, w, mask, c, st, s);
-    else project_bwd_adam_launch<D, false, false>(x, f, cfg, rec, M, po, cap, L, pg, m, v, w, mask, c, st, s);
+    if (w && mask) project_bwd_adam_launch<D, true, true>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, s);
+    else if (w) project_bwd_adam_launch<D, true, false>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, s);
+    else project_bwd_adam_launch<D, false, false>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, s);
 }
 
 hipError_t launch_project_bwd_adam(gs_params& x, const gs_frame& f, const gs_raster_cfg& cfg, const float* rec,
@@ -1001,15 +984,14 @@ hipError_t launch_project_bwd_adam(gs_params& x, const gs_frame& f, const gs_ras
     if (x.n == 0) return hipSuccess;
     const uint4* M = reinterpret_cast<const uint4*>(meta);
     const AdamConsts c = adam_consts(acfg);
-    const PartialLayout L = partial_layout(cfg, bins, pg);
     const uint32_t* po = bins.pair_off;
     const uint64_t cap = bins.capacity;
     uint32_t* st = bins.counters + GS_CTR_STATUS;
     switch (x.sh_degree) {
-        case 0: project_bwd_adam_pen<0>(x, f, cfg, rec, M, po, cap, L, pg, m, v, w, mask, c, st, s); break;
-        case 1: project_bwd_adam_pen<1>(x, f, cfg, rec, M, po, cap, L, pg, m, v, w, mask, c, st, s); break;
-        case 2: project_bwd_adam_pen<2>(x, f, cfg, rec, M, po, cap, L, pg, m, v, w, mask, c, st, s); break;
-        default: project_bwd_adam_pen<3>(x, f, cfg, rec, M, po, cap, L, pg, m, v, w, mask, c, st, s); break;
+        case 0: project_bwd_adam_pen<0>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, s); break;
+        case 1: project_bwd_adam_pen<1>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, s); break;
+        case 2: project_bwd_adam_pen<2>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, s); break;
+        default: project_bwd_adam_pen<3>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, s); break;
     }
     return hipGetLastError();
 }

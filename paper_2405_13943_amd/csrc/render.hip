@@ -164,7 +164,7 @@ __device__ inline void wave_lds_sync() {
 }
 
 // Stores the nine partials of two records' pairs (a at da, b at db; db may
-// be null), each summed over the wave's 64 lanes.  FP32: the two records are
+// be null), each summed over the wave's 64 lanes.  The two records are
 // reduced together; a swap of wave halves (v_permlane32_swap) and an add
 // leave record a's sums in lanes 0-31 and b's in lanes 32-63; a swap of
 // odd and even rows (v_permlane16_swap) between neighbouring partials and an
@@ -180,40 +180,40 @@ __device__ inline float swap_add16(float a, float b) {
     return __uint_as_float(p[0]) + __uint_as_float(p[1]);
 }
 
-__device__ inline void store_pair_partials(const float (&va)[9], const float (&vb)[9], float* da, float* db) {
+// the same swaps of the two 32-bit halves of a double
+template <bool ROWS>
+__device__ inline double swap_add_f64(double a, double b) {
+    const uint64_t ua = uint64_t(__double_as_longlong(a)), ub = uint64_t(__double_as_longlong(b));
+    const auto swap = [](uint32_t x, uint32_t y) {
+        return ROWS ? __builtin_amdgcn_permlane16_swap(x, y, false, false)
+                    : __builtin_amdgcn_permlane32_swap(x, y, false, false);
+    };
+    const auto lo = swap(uint32_t(ua), uint32_t(ub)), hi = swap(uint32_t(ua >> 32), uint32_t(ub >> 32));
+    const uint64_t p = uint64_t(lo[0]) | uint64_t(hi[0]) << 32, q = uint64_t(lo[1]) | uint64_t(hi[1]) << 32;
+    return __longlong_as_double((long long)p) + __longlong_as_double((long long)q);
+}
+__device__ inline double swap_add32(double a, double b) { return swap_add_f64<false>(a, b); }
+__device__ inline double swap_add16(double a, double b) { return swap_add_f64<true>(a, b); }
+
+template <typename T>
+__device__ inline void store_pair_partials(const T (&va)[9], const T (&vb)[9], T* da, T* db) {
     const int lane = lane_id();
-    float x[9], y[5];
+    T x[9], y[5];
 #pragma unroll
     for (int q = 0; q < 9; q++) x[q] = swap_add32(va[q], vb[q]);
 #pragma unroll
     for (int j = 0; j < 4; j++) y[j] = swap_add16(x[2 * j], x[2 * j + 1]);
-    y[4] = swap_add16(x[8], 0.f);
+    y[4] = swap_add16(x[8], T(0));
 #pragma unroll
     for (int j = 0; j < 5; j++) y[j] = row_sum_last(y[j]);
     if ((lane & 15) == 15) {
         const int r = lane >> 4;
-        float* dst = r < 2 ? da : db;
+        T* dst = r < 2 ? da : db;
         const int par = r & 1;
         if (dst)
 #pragma unroll
             for (int j = 0; j < 5; j++)
                 if (2 * j + par < 9) dst[2 * j + par] = y[j];
-    }
-}
-
-__device__ inline void store_pair_partials(const double (&va)[9], const double (&vb)[9], double* da, double* db) {
-    double sa[9], sb[9];
-#pragma unroll
-    for (int q = 0; q < 9; q++) {
-        sa[q] = wave_sum(va[q]);
-        sb[q] = wave_sum(vb[q]);
-    }
-    if (lane_id() == 0) {
-#pragma unroll
-        for (int q = 0; q < 9; q++) {
-            da[q] = sa[q];
-            if (db) db[q] = sb[q];
-        }
     }
 }
 
@@ -379,10 +379,10 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
     T* __restrict__ pg, const uint8_t* __restrict__ qmask) {
     constexpr int PPL = QX * QY;
     // NS wavefronts per tile, wave `sub` owning the tile's sub-tile of QX x QY
-    // quadrants and storing its own nine partials per pair (slot e NS + sub);
-    // NS = 0: the plan's wavefronts, heavy tiles first, each owning a run of
-    // the tile's quadrants (QX x QY is then the tile), partials in the
-    // adaptive layout
+    // quadrants; NS = 0: the plan's wavefronts, heavy tiles first, each owning
+    // a run of the tile's quadrants (QX x QY is then the tile).  A tile's
+    // wavefronts share a workgroup; each stores its own nine partials per
+    // pair (slot `sub`), which they fold into slot 0 at the end
     constexpr bool ADAPT = NS == 0;
     constexpr int NSD = ADAPT ? 1 : NS;
     __shared__ T s_rec[kRenderWaves][kBwdBatch][GS_REC_WORDS];
@@ -391,15 +391,15 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
     const int wave = threadIdx.x / kWave, lane = lane_id();
     int tile = 0, sub = 0, nwaves = NSD;
     uint32_t owned = (1u << PPL) - 1u;
-    bool valid = true;   // adaptive: no early return, the workgroup may meet at a barrier below
-    // L1 loss, adaptive: the workgroup's wavefronts leave their sums in LDS
-    // and the last to arrive adds them per job, one global atomic per job
-    // and workgroup instead of one per wavefront (same-address atomics from
+    bool valid = true;   // no early return: the workgroup may meet at a barrier below
+    // L1 loss: the workgroup's wavefronts leave their sums in LDS and the
+    // last to arrive adds them per job, one global atomic per job and
+    // workgroup instead of one per wavefront (same-address atomics from
     // every wavefront of the launch cost it about a sixth of its time)
     __shared__ T s_loss[kRenderWaves];
     __shared__ int s_ljob[kRenderWaves];
     __shared__ uint32_t s_larrived;
-    const bool wg_loss = ADAPT && mode == GS_LOSS_L1 && loss_out != nullptr;
+    const bool wg_loss = mode == GS_LOSS_L1 && loss_out != nullptr;
     auto arrive = [&](T l, int jl) {
         if (lane != 0) return;
         s_loss[wave] = l;
@@ -424,16 +424,14 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
     if (ADAPT) {
         valid = plan_wave(order, frame.n_tiles, blockIdx.x * kRenderWaves + wave, tile, sub, nwaves);
         owned = valid ? owned_quadrants(PPL, nwaves, sub) : 0u;
-        if (wg_loss && !valid) arrive(T(0), -1);
     } else {
         const int gw = xcd_block(blockIdx.x, gridDim.x) * kRenderWaves + wave;
         tile = gw / NSD;
         sub = gw % NSD;
-        if (tile >= frame.n_tiles) return;
+        valid = tile < frame.n_tiles;
     }
-    auto pslot = [&](uint32_t e) {
-        return ADAPT ? adaptive_slot(capacity, e, sub) : (int64_t(e) * NSD + sub) * 9;
-    };
+    if (wg_loss && !valid) arrive(T(0), -1);
+    auto pslot = [&](uint32_t e) { return partial_slot(capacity, e, NS == 1 ? 0 : sub); };
     do {
     if (!valid) break;
     const int j = job_of_tile(frame.jobs, frame.n_jobs, tile);
@@ -487,8 +485,7 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
     }
     if (mode == GS_LOSS_L1 && loss_out) {
         const T l = wave_sum(loss);
-        if (wg_loss) arrive(l, j);
-        else if (lane == 0) atomicAdd(loss_out + j, l);
+        arrive(l, j);
     }
 
     const uint2 range = ranges[tile];
@@ -634,15 +631,14 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
     }
     } while (0);
 
-    // Adaptive: a split tile's wavefronts share this workgroup.  Once all of
-    // them have stored their partials, fold each pair's further slots into
-    // slot 0 (slot 0 + 1 + 2 + 3, in that order), so the projection backward
-    // reads one dense slot per pair.  Whether a workgroup holds a split tile
-    // is the same for all its wavefronts (the plan puts split tiles first),
-    // and none of them has left the kernel.
-    if (ADAPT) {
-        const uint64_t split_waves = 4ull * order[0] + 2ull * order[1];
-        if (4ull * blockIdx.x < split_waves) {
+    // A split tile's wavefronts share this workgroup.  Once all of them have
+    // stored their partials, fold each pair's further slots into slot 0
+    // (slot 0 + 1 + 2 + 3, in that order), so the projection backward reads
+    // one dense slot per pair.  Whether a workgroup holds a split tile is the
+    // same for all its wavefronts (every one with NS > 1; the plan puts split
+    // tiles first), and none of them has left the kernel.
+    if (NS != 1) {
+        if (!ADAPT || 4ull * blockIdx.x < 4ull * order[0] + 2ull * order[1]) {
             __syncthreads();
             if (valid && nwaves > 1) {
                 const int jf = job_of_tile(frame.jobs, frame.n_jobs, tile);
@@ -655,12 +651,12 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
                     const uint4 mt = meta[r];
                     const uint32_t x0 = mt.z & 0xffffu, y0 = mt.z >> 16, x1 = mt.w & 0xffffu;
                     const uint32_t e = pair_off[r] + (fty - y0) * (x1 - x0 + 1) + (ftx - x0);
-                    T* d0 = pg + adaptive_slot(capacity, e, 0);
+                    T* d0 = pg + partial_slot(capacity, e, 0);
                     T acc[9];
 #pragma unroll
                     for (int q = 0; q < 9; q++) acc[q] = d0[q];
                     for (int sl = 1; sl < nwaves; sl++) {
-                        const T* src = pg + adaptive_slot(capacity, e, sl);
+                        const T* src = pg + partial_slot(capacity, e, sl);
 #pragma unroll
                         for (int q = 0; q < 9; q++) acc[q] += src[q];
                     }
@@ -673,6 +669,31 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
 }
 
 // ---------------------------------------------------------------------------
+
+// Wavefronts per tile of a launch (0: the plan's): what the configuration
+// asks for, except that a frame of few tiles, which one wavefront per tile
+// would leave most of the chip's 1,024 SIMDs idle with, takes 4 (at most the
+// tile's quadrants) up to fill4 tiles, and 2 up to fill2 tiles where it asks
+// for 1.  The lines lie where the split stops paying on both a scene of long
+// uneven lists (500k Gaussians of the scale scene) and one of even lists (60k
+// of the parity scene's), 16x16 tiles, us with 1 / 2 / 4 / plan:
+//   forward,  1,617 tiles: 227 / 141 / 122 / 146 and 92 / 65 / 63 / 101;
+//             2,072 tiles: 192 / 127 / 128 / 123 and 88 / 73 / 76 / 92;
+//             4,187 tiles: 132 / 126 / 134 / 85 and 97 / 94 / 106 / 101;
+//             8,214 tiles: 139 / 137 / 163 / 74 and 143 / 136 / 166 / 137;
+//   backward, 1,080 tiles: 601 / 383 / 300 / 398 and 154 / 153 / 151 / 169;
+//             1,350 tiles: 543 / 368 / 313 / 329 and 161 / 151 / 167 / 171;
+//             1,617 tiles: 453 / 314 / 299 / 295 and 154 / 166 / 180 / 162.
+// (The backward pays for each split with another reduction per record.)
+constexpr int kFwdFill4 = 1800, kFwdFill2 = 4200;
+constexpr int kBwdFill4 = 1200, kBwdFill2 = 1400;
+static int launch_waves(const gs_raster_cfg& cfg, int waves, int n_tiles, int fill4, int fill2) {
+    if (waves > 1) return waves;
+    const int quads = (cfg.tile_w / 8) * (cfg.tile_h / 8);
+    if (n_tiles <= fill4) return quads < 4 ? quads : 4;
+    if (n_tiles <= fill2 && waves == 1) return quads < 2 ? quads : 2;
+    return waves;
+}
 
 // grid of a compositing launch: NS (or 4, adaptive) wavefronts per tile, in
 // workgroups of kRenderWaves wavefronts (1, adaptive)
@@ -738,7 +759,7 @@ template <typename T>
 hipError_t launch_render_fwd(const gs_frame& f, const gs_raster_cfg& cfg, const T* rec, const gs_bins& bins,
                              T* rgb, T* Tfin, uint32_t* ncontrib, unsigned long long* kept, hipStream_t s) {
     if (f.n_tiles == 0) return hipSuccess;
-    GS_TILE_DISPATCH(fwd_waves(cfg), fwd_launch, f, cfg, rec, bins, rgb, Tfin, ncontrib, kept, s);
+    GS_TILE_DISPATCH(launch_waves(cfg, fwd_waves(cfg), f.n_tiles, kFwdFill4, kFwdFill2), fwd_launch, f, cfg, rec, bins, rgb, Tfin, ncontrib, kept, s);
     return hipGetLastError();
 }
 
@@ -747,7 +768,7 @@ hipError_t launch_render_bwd(const gs_frame& f, const gs_raster_cfg& cfg, const 
                              const gs_bins& bins, const T* rgb, const uint32_t* nc, gs_loss_mode mode, const T* gin,
                              T* loss, T* pg, hipStream_t s) {
     if (f.n_tiles == 0) return hipSuccess;
-    GS_TILE_DISPATCH(bwd_waves(cfg), bwd_launch, f, cfg, rec, meta, bins, rgb, nc, int(mode), gin, loss, pg, s);
+    GS_TILE_DISPATCH(launch_waves(cfg, bwd_waves(cfg), f.n_tiles, kBwdFill4, kBwdFill2), bwd_launch, f, cfg, rec, meta, bins, rgb, nc, int(mode), gin, loss, pg, s);
     return hipGetLastError();
 }
 
