@@ -140,8 +140,9 @@ typedef struct {
     int16_t bwd_waves;       /* compositing, each owning an equal part of the tile and walking
                                 the whole list: 1 (0 = 1), 2 (16x8, 16x16, 32x8) or 4 (16x16,
                                 32x8); GS_WAVES_ADAPTIVE picks 1, 2 or 4 per tile from its
-                                list length against the frame mean (4 above 4x, 2 above
-                                1.25x; needs gs_bins.tile_order).  Frames of few tiles take more than
+                                list length against the frame mean and the tiles of the frame
+                                (at most 4 above 4x the mean, 2 above 1.25x; needs
+                                gs_bins.tile_order).  Frames of few tiles take more than
                                 1 or the plan's count where that fills the chip.  Images do not depend
                                 on them; gradients only through the order of their sums. */
 } gs_raster_cfg;
@@ -157,7 +158,8 @@ typedef struct {
     uint64_t capacity;       /* pairs vals can hold */
     uint32_t *tile_order;    /* device [n_tiles + 4] or NULL: the compositing plan written by
                                 gs_bin_sort, needed when fwd_waves or bwd_waves is
-                                GS_WAVES_ADAPTIVE: [0..2] = tiles taking 4, 2 and 1 wavefronts,
+                                GS_WAVES_ADAPTIVE: [0..2] = tiles that may take 4, 2 and 1
+                                wavefronts, [3] = the shares of the list that the passes split,
                                 then the tile ids, those groups in that order */
     uint8_t *qmask;          /* device [capacity] or NULL: per list entry (vals order), bit q set
                                 unless no pixel centre of 8x8 quadrant q of its tile (row-major

@@ -580,7 +580,8 @@ __device__ void block_merge_sort(uint64_t* sk, uint32_t n) {
 // tiles first (one workgroup each), then 2-wave, then 1-wave tiles; inside
 // a group the longer lists first, by buckets of half the frame's mean list
 // length (the last bucket open-ended), so that the heaviest tiles of each
-// group do not start last.  One workgroup (of any multiple of the
+// group do not start last; and the leading share of that list which each
+// pass splits (pass_plan).  One workgroup (of any multiple of the
 // wavefront); the order inside a bucket is whatever the LDS atomics give,
 // which changes no result (each tile is composited on its own).  The first
 // pass counts the buckets and keeps each tile's bucket in `cache` (LDS, when
@@ -613,12 +614,24 @@ __device__ void tile_plan(const uint2* __restrict__ ranges, const uint32_t* __re
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t run = 0u, tot[3] = {0u, 0u, 0u};
+        const int bf = min(fwd_split_bucket(n_tiles), kPlanBuckets - 1);
+        const int bb = min(bwd_split_bucket(n_tiles), kPlanBuckets - 1);
+        uint32_t nf = 0u, nb = 0u;
         for (int k = 0; k < NB; k++) {
             const uint32_t c = cnt[k];
             cnt[k] = run;                  // first place of the bin
             run += c;
             tot[k / kPlanBuckets] += c;
+            const int bucket = kPlanBuckets - 1 - k % kPlanBuckets;
+            nf += bucket >= bf ? c : 0u;
+            nb += bucket >= bb ? c : 0u;
         }
+        // shares in 1/65536, rounded up so that a single tile counts
+        auto share = [&](uint32_t n) {
+            return n_tiles > 0 ? uint32_t(min((uint64_t(n) * 65536u + uint64_t(n_tiles) - 1u) / uint64_t(n_tiles),
+                                              uint64_t(0xffff))) : 0u;
+        };
+        order[3] = share(nf) | share(nb) << 16;
         order[0] = tot[0];
         order[1] = tot[1];
         order[2] = tot[2];

@@ -111,42 +111,89 @@ __host__ __device__ inline int bwd_waves(const gs_raster_cfg& c) {
     return bwd_adaptive(c) ? 0 : (c.bwd_waves <= 1 ? 1 : c.bwd_waves);
 }
 
-// Wavefronts of one tile in an adaptive compositing pass, from its list
-// length against the frame's mean list length: 4 above 4 x the mean, 2 above
-// 1.25 x, else 1; never more than the tile's quadrants.  Exact integer
-// arithmetic, so every kernel that needs it agrees.
+// Most wavefronts of one tile in an adaptive compositing pass (its group in
+// the plan), from its list length against the frame's mean list length: 4
+// above 4 x the mean, 2 above 1.25 x, else 1; never more than the tile's
+// quadrants.  Exact integer arithmetic, so every kernel that needs it agrees.
 __device__ inline int adaptive_waves(uint32_t count, uint32_t pairs, int n_tiles, int quads) {
     const uint64_t a = 4ull * count * uint64_t(n_tiles);
     const int s = a > 16ull * pairs ? 4 : (a > 5ull * pairs ? 2 : 1);
     return s < quads ? s : quads;
 }
 
+// How much of a frame's plan a compositing pass splits.  The plan lists the
+// tiles longest first (its wavefront groups, then buckets of half the mean
+// list length); a pass splits a leading run of it, over 4 wavefronts in the
+// plan's first group and 2 beyond.  A tile is worth splitting when its list
+// alone would outlast the launch: when it is longer than the entries per
+// resident wavefront by some factor, so the line moves with n_tiles / resident
+// wavefronts, in units of the mean list length; below some 3,000 tiles lines
+// of 1.5 (forward) and 2 (backward) times the mean take over.  Splitting
+// below the line repeats staging and, in the backward, each record's
+// reduction and store for nothing.  Measured, us with every tile above 1.25x
+// the mean split / with the line here / with no split (1600x1066 unless
+// noted; Gaussians of the scale scene):
+//   backward: 500k 201-217 / 164 / 184; 3M 775 / 467 / 443; three 1280x720
+//             views of 800k 692 / 542 / 542; four views of 1.5M 2073 / 1551 /
+//             1551; 500k at 979x651 227 / 218 / 334;
+//   forward:  500k 68-74 / 68 / 99; 3M 201 / 200 / 204; three views of 800k
+//             213 / 183 / 202; four of 1.5M 602 / 530 / 530.
+// Line in half means, rounded: the bucket from which tiles are split.
+__host__ __device__ inline int fwd_split_bucket(int n_tiles) {
+    const int b = (n_tiles + 1080) / 2160;     // 1.66 x entries per wavefront at 7 per SIMD
+    return b < 3 ? 3 : b;
+}
+__host__ __device__ inline int bwd_split_bucket(int n_tiles) {
+    const int b = (n_tiles + 560) / 1120;      // 1.83 x entries per wavefront at 4 per SIMD
+    return b < 4 ? 4 : b;
+}
+
+// The plan a pass runs (word 3 of the plan array holds the share of the list
+// it splits, in 1/65536: the forward's in the low half, the backward's in the
+// high half): tiles taking 4, 2 and 1 wavefronts, in list order; false for an
+// array that does not describe n_tiles tiles.
+struct PassPlan {
+    uint32_t m4, m2, m1;
+};
+template <bool BWD>
+__device__ inline bool pass_plan(const uint32_t* __restrict__ order, int n_tiles, PassPlan& p) {
+    const uint32_t nt = uint32_t(n_tiles), n4 = order[0], n2 = order[1], n1 = order[2];
+    p = {0u, 0u, 0u};
+    if (n4 > nt || n2 > nt || n1 > nt || n4 + n2 + n1 != nt) return false;
+    const uint32_t share = BWD ? order[3] >> 16 : order[3] & 0xffffu;
+    const uint32_t split = min(uint32_t((uint64_t(share) * nt) >> 16), n4 + n2);
+    p.m4 = min(n4, split);
+    p.m2 = split - p.m4;
+    p.m1 = nt - split;
+    return true;
+}
+
 // Wavefront gw of an adaptive compositing launch -> (tile, sub, waves) from
-// the plan of k_tile_plan; false when the wavefront has no work (past the
-// plan, or a plan that does not describe n_tiles tiles).
+// the plan; false when the wavefront has no work.
+template <bool BWD>
 __device__ inline bool plan_wave(const uint32_t* __restrict__ order, int n_tiles, uint32_t gw, int& tile, int& sub,
                                  int& waves) {
-    const uint32_t nt = uint32_t(n_tiles), n4 = order[0], n2 = order[1], n1 = order[2];
-    if (n4 > nt || n2 > nt || n1 > nt || n4 + n2 + n1 != nt) return false;
+    PassPlan p;
+    if (!pass_plan<BWD>(order, n_tiles, p)) return false;
     const uint32_t* list = order + 4;
     uint32_t g = gw, t;
-    if (g < 4u * n4) {
+    if (g < 4u * p.m4) {
         t = list[g / 4u];
         sub = int(g % 4u);
         waves = 4;
-    } else if ((g -= 4u * n4) < 2u * n2) {
-        t = list[n4 + g / 2u];
+    } else if ((g -= 4u * p.m4) < 2u * p.m2) {
+        t = list[p.m4 + g / 2u];
         sub = int(g % 2u);
         waves = 2;
-    } else if ((g -= 2u * n2) < n1) {
-        t = list[n4 + n2 + g];
+    } else if ((g -= 2u * p.m2) < p.m1) {
+        t = list[p.m4 + p.m2 + g];
         sub = 0;
         waves = 1;
     } else {
         return false;
     }
     tile = int(t);
-    return t < nt;
+    return t < uint32_t(n_tiles);
 }
 
 // Partials of wavefront `sub` for pair e: slot 0 of every pair dense at e,

@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kWave * kRenderWaves, kFwdWavesPerSimd) void k_rend
     uint32_t owned = (1u << PPL) - 1u;
     if (ADAPT) {
         int waves;
-        if (!plan_wave(order, frame.n_tiles, blockIdx.x * kRenderWaves + wave, tile, sub, waves)) return;
+        if (!plan_wave<false>(order, frame.n_tiles, blockIdx.x * kRenderWaves + wave, tile, sub, waves)) return;
         owned = owned_quadrants(PPL, waves, sub);
     } else {
         const int gw = xcd_block(blockIdx.x, gridDim.x) * kRenderWaves + wave;
@@ -422,7 +422,7 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
         __syncthreads();
     }
     if (ADAPT) {
-        valid = plan_wave(order, frame.n_tiles, blockIdx.x * kRenderWaves + wave, tile, sub, nwaves);
+        valid = plan_wave<true>(order, frame.n_tiles, blockIdx.x * kRenderWaves + wave, tile, sub, nwaves);
         owned = valid ? owned_quadrants(PPL, nwaves, sub) : 0u;
     } else {
         const int gw = xcd_block(blockIdx.x, gridDim.x) * kRenderWaves + wave;
@@ -638,7 +638,9 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
     // same for all its wavefronts (every one with NS > 1; the plan puts split
     // tiles first), and none of them has left the kernel.
     if (NS != 1) {
-        if (!ADAPT || 4ull * blockIdx.x < 4ull * order[0] + 2ull * order[1]) {
+        PassPlan plan = {0u, 0u, 0u};
+        if (ADAPT) pass_plan<true>(order, frame.n_tiles, plan);
+        if (!ADAPT || 4ull * blockIdx.x < 4ull * plan.m4 + 2ull * plan.m2) {
             __syncthreads();
             if (valid && nwaves > 1) {
                 const int jf = job_of_tile(frame.jobs, frame.n_jobs, tile);
