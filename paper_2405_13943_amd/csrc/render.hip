@@ -399,6 +399,7 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
     __shared__ T s_loss[kRenderWaves];
     __shared__ int s_ljob[kRenderWaves];
     __shared__ uint32_t s_larrived;
+    __shared__ uint32_t s_wend[kRenderWaves];   // per wavefront: list entries its pixels need (the fold reads as many)
     const bool wg_loss = mode == GS_LOSS_L1 && loss_out != nullptr;
     auto arrive = [&](T l, int jl) {
         if (lane != 0) return;
@@ -499,9 +500,11 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
         qend[k] = uniform(wave_max_u32(nc[k]));
         wend = qend[k] > wend ? qend[k] : wend;
     }
+    if (NS != 1 && lane == 0) s_wend[wave] = wend;
     for (uint32_t base = range.x; base < range.y; base += kBwdBatch) {
         const uint32_t cnt = min(uint32_t(kBwdBatch), range.y - base);
         const uint32_t pos0 = base - range.x;   // list position of the batch's first entry
+        if (NS != 1 && sub > 0 && pos0 >= wend) break;   // the fold does not read this slot past wend
         uint32_t e_own = 0;   // pair this lane stores at the end of the batch
         T w[GS_REC_WORDS];
         uint32_t m = 0, r = 0;
@@ -535,7 +538,7 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
         }
         if (pos0 >= wend) {
             // past every pixel's last contributor: the rest of the tile's
-            // pairs carry zero gradient
+            // pairs carry zero gradient (slot 0 of all of them is stored)
             if (uint32_t(lane) < cnt)
 #pragma unroll
                 for (int q = 0; q < 9; q++) pg[pslot(e_own) + q] = T(0);
@@ -648,8 +651,13 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
                 const int ltf = tile - jb.tile0;
                 const uint32_t ftx = uint32_t(ltf % jb.tiles_x), fty = uint32_t(ltf / jb.tiles_x);
                 const uint2 rg = ranges[tile];
-                for (uint32_t i = rg.x + uint32_t(sub * kWave + lane); i < rg.y; i += uint32_t(nwaves * kWave)) {
-                    const uint32_t r = vals[i];
+                // entries past what the further wavefronts' pixels need have nothing to fold
+                const int w0 = wave - sub;
+                uint32_t end = 0u;
+                for (int sl = 1; sl < nwaves; sl++) end = max(end, s_wend[w0 + sl]);
+                end = min(end, rg.y - rg.x);
+                for (uint32_t pos = uint32_t(sub * kWave + lane); pos < end; pos += uint32_t(nwaves * kWave)) {
+                    const uint32_t r = vals[rg.x + pos];
                     const uint4 mt = meta[r];
                     const uint32_t x0 = mt.z & 0xffffu, y0 = mt.z >> 16, x1 = mt.w & 0xffffu;
                     const uint32_t e = pair_off[r] + (fty - y0) * (x1 - x0 + 1) + (ftx - x0);
@@ -658,6 +666,7 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
 #pragma unroll
                     for (int q = 0; q < 9; q++) acc[q] = d0[q];
                     for (int sl = 1; sl < nwaves; sl++) {
+                        if (pos >= s_wend[w0 + sl]) continue;
                         const T* src = pg + partial_slot(capacity, e, sl);
 #pragma unroll
                         for (int q = 0; q < 9; q++) acc[q] += src[q];
@@ -675,25 +684,28 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
 // Wavefronts per tile of a launch (0: the plan's): what the configuration
 // asks for, except that a frame of few tiles, which one wavefront per tile
 // would leave most of the chip's 1,024 SIMDs idle with, takes 4 (at most the
-// tile's quadrants) up to fill4 tiles, and 2 up to fill2 tiles where it asks
-// for 1.  The lines lie where the split stops paying on both a scene of long
-// uneven lists (500k Gaussians of the scale scene) and one of even lists (60k
-// of the parity scene's), 16x16 tiles, us with 1 / 2 / 4 / plan:
-//   forward,  1,617 tiles: 227 / 141 / 122 / 146 and 92 / 65 / 63 / 101;
-//             2,072 tiles: 192 / 127 / 128 / 123 and 88 / 73 / 76 / 92;
-//             4,187 tiles: 132 / 126 / 134 / 85 and 97 / 94 / 106 / 101;
-//             8,214 tiles: 139 / 137 / 163 / 74 and 143 / 136 / 166 / 137;
-//   backward, 1,080 tiles: 601 / 383 / 300 / 398 and 154 / 153 / 151 / 169;
-//             1,350 tiles: 543 / 368 / 313 / 329 and 161 / 151 / 167 / 171;
-//             1,617 tiles: 453 / 314 / 299 / 295 and 154 / 166 / 180 / 162.
+// tile's quadrants) up to fill4 tiles, and 2 up to fill2 tiles; a pass that
+// splits by the plan takes 4 up to fill_plan tiles.  The lines lie where the
+// split stops paying on scenes of long uneven lists (the scale scene's 500k
+// Gaussians), of even ones (30k of the parity scene's) and of lists that end
+// early (200k of them), 16x16 tiles, us with 1 / 2 / 4 / the plan:
+//   forward,  1,617 tiles: 227 / 141 / 122 / 142, 91 / 62 / 61 / 83, 97 / 69 / 67 / 99;
+//             2,072 tiles: 192 / 127 / 128 / 120, 81 / 64 / 67 / 79, 95 / 75 / 77 / 102;
+//             4,056 tiles: 132 / 126 / 134 / 85, 85 / 85 / 93 / 75, 103 / 96 / 108 / 109;
+//   backward,   988 tiles: 601 / 383 / 300 / 398, 157 / 129 / 128 / 168, 168 / 150 / 150 / 181;
+//             1,350 tiles: 543 / 368 / 313 / 333, 162 / 130 / 140 / 152, 182 / 164 / 179 / 185;
+//             1,617 tiles: 453 / 314 / 299 / 289, 153 / 138 / 152 / 146, 170 / 193 / 198 / 183.
 // (The backward pays for each split with another reduction per record.)
-constexpr int kFwdFill4 = 1800, kFwdFill2 = 4200;
-constexpr int kBwdFill4 = 1200, kBwdFill2 = 1400;
-static int launch_waves(const gs_raster_cfg& cfg, int waves, int n_tiles, int fill4, int fill2) {
+struct FillRule {
+    int fill4, fill2, fill_plan;
+};
+constexpr FillRule kFwdFill = {1800, 3600, 1800};
+constexpr FillRule kBwdFill = {1000, 1400, 1400};
+static int launch_waves(const gs_raster_cfg& cfg, int waves, int n_tiles, const FillRule& f) {
     if (waves > 1) return waves;
     const int quads = (cfg.tile_w / 8) * (cfg.tile_h / 8);
-    if (n_tiles <= fill4) return quads < 4 ? quads : 4;
-    if (n_tiles <= fill2 && waves == 1) return quads < 2 ? quads : 2;
+    if (n_tiles <= (waves == 0 ? f.fill_plan : f.fill4)) return quads < 4 ? quads : 4;
+    if (waves == 1 && n_tiles <= f.fill2) return quads < 2 ? quads : 2;
     return waves;
 }
 
@@ -761,7 +773,7 @@ template <typename T>
 hipError_t launch_render_fwd(const gs_frame& f, const gs_raster_cfg& cfg, const T* rec, const gs_bins& bins,
                              T* rgb, T* Tfin, uint32_t* ncontrib, unsigned long long* kept, hipStream_t s) {
     if (f.n_tiles == 0) return hipSuccess;
-    GS_TILE_DISPATCH(launch_waves(cfg, fwd_waves(cfg), f.n_tiles, kFwdFill4, kFwdFill2), fwd_launch, f, cfg, rec, bins, rgb, Tfin, ncontrib, kept, s);
+    GS_TILE_DISPATCH(launch_waves(cfg, fwd_waves(cfg), f.n_tiles, kFwdFill), fwd_launch, f, cfg, rec, bins, rgb, Tfin, ncontrib, kept, s);
     return hipGetLastError();
 }
 
@@ -770,7 +782,7 @@ hipError_t launch_render_bwd(const gs_frame& f, const gs_raster_cfg& cfg, const 
                              const gs_bins& bins, const T* rgb, const uint32_t* nc, gs_loss_mode mode, const T* gin,
                              T* loss, T* pg, hipStream_t s) {
     if (f.n_tiles == 0) return hipSuccess;
-    GS_TILE_DISPATCH(launch_waves(cfg, bwd_waves(cfg), f.n_tiles, kBwdFill4, kBwdFill2), bwd_launch, f, cfg, rec, meta, bins, rgb, nc, int(mode), gin, loss, pg, s);
+    GS_TILE_DISPATCH(launch_waves(cfg, bwd_waves(cfg), f.n_tiles, kBwdFill), bwd_launch, f, cfg, rec, meta, bins, rgb, nc, int(mode), gin, loss, pg, s);
     return hipGetLastError();
 }
 

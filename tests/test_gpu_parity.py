@@ -672,3 +672,37 @@ def test_disjoint_and_shared_job_paths_agree(cfg1, gpu1):
     gs.render_bwd(params, f2, cfg, b2, g2, gs.LOSS_L1, target[: 3 * 128 * 128])
     assert torch.count_nonzero(g2[:, n // 2:]).item() == 0
     assert torch.count_nonzero(g2[:, : n // 2]).item() > 0
+
+
+@pytest.mark.parametrize("tile", [(16, 16), (16, 16, -1), (32, 8, 1), (16, 8), (8, 8, -1)])
+@pytest.mark.parametrize("size", [(16, 8, 1), (250, 130, 1), (512, 513, 1), (608, 592, 1), (900, 480, 2)])
+def test_wavefronts_by_tile_count(cfg1, tile, size):
+    """Frames on both sides of the tile counts where the launch's wavefronts
+    per tile change: images as with two wavefronts per tile set outright
+    (bit for bit; 8x8 tiles: with the plan), gradients equal up to the order
+    of their sums, and the same loss.  2,000 Gaussians of the parity scene,
+    one of them spanning the image."""
+    w, h, views = size
+    p = cfg1.params.copy()
+    p[scenes.LOGSCALE:scenes.LOGSCALE + 3, 7] = -0.5
+    params = torch.from_numpy(p).cuda()
+    cams = [scenes.look_at([3 * math.sin(a), 0.0, 3 * math.cos(a)], [0, 0, 0], w, h, 1.2 * w, 1.2 * w)
+            for a in (0.3, 1.7)[:views]]
+    gen = torch.Generator().manual_seed(5)
+    target = torch.rand(3 * w * h * views, generator=gen).cuda()
+    out = []
+    for t in (tile, (16, 16, 2) if tile[:2] == (16, 16) else (8, 8, 1)):
+        cfg = gs.raster_cfg(t)
+        frame = gs.Frame(cams, [gs.JobSpec(k, 0, p.shape[1], 0.5) for k in range(views)], cfg)
+        buf = gs.rasterize(params, frame, cfg)
+        grad = torch.full_like(params, float("nan"))
+        loss = torch.zeros(views, device="cuda")
+        gs.render_bwd(params, frame, cfg, buf, grad, gs.LOSS_L1, target, loss)
+        out.append((buf.rgb.clone(), buf.T.clone(), buf.ncontrib.clone(), grad, loss))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    if tile[:2] == (16, 16):
+        assert torch.equal(out[0][2], out[1][2])
+    # the same FP32 terms in another order: per plane, against the plane's norm
+    a, b = out[0][3].double(), out[1][3].double()
+    assert ((a - b).norm(dim=1) <= 1e-4 * b.norm(dim=1) + 1e-12).all()
+    torch.testing.assert_close(out[0][4], out[1][4], rtol=1e-5, atol=0)
