@@ -135,12 +135,14 @@ gs_status render_bwd_impl(const gs_params* params, const gs_frame* frame, const 
                     bwd_ws(bins->capacity, sizeof(T) == 8));
     T* pg = static_cast<T*>(ws);
     hipStream_t s = (hipStream_t)stream;
+    const gs::LossSum<T> ls = gs::loss_sum(pg, mode == GS_LOSS_L1 ? loss : nullptr, bins->counters, bins->capacity,
+                                           frame->n_tiles);
     hipError_t e = gs::launch_render_bwd<T>(*frame, *cfg, static_cast<const T*>(rec), meta, *bins,
-                                            static_cast<const T*>(rgb), nc, mode, static_cast<const T*>(gin), loss,
+                                            static_cast<const T*>(rgb), nc, mode, static_cast<const T*>(gin), ls,
                                             pg, s);
     if (e != hipSuccess) return check_hip(e, "gs_render_bwd (composite)");
     return check_hip(gs::launch_project_bwd<T>(*params, *frame, *cfg, static_cast<const T*>(rec), meta, *bins, pg,
-                                               *grad, s),
+                                               *grad, ls, s),
                      "gs_render_bwd (projection)");
 }
 
@@ -434,12 +436,14 @@ gs_status gs_render_bwd_adam(gs_params* x, const gs_frame* frame, const gs_raste
         return fail(GS_E_CAPACITY, "backward workspace too small (%zu < %zu)", ws_bytes, bwd_ws(bins->capacity, 0));
     float* pg = static_cast<float*>(ws);
     hipStream_t s = (hipStream_t)stream;
+    const gs::LossSum<float> ls = gs::loss_sum(pg, mode == GS_LOSS_L1 ? loss : nullptr, bins->counters,
+                                               bins->capacity, frame->n_tiles);
     hipError_t e = gs::launch_render_bwd<float>(*frame, *cfg, static_cast<const float*>(rec), meta, *bins,
                                                 static_cast<const float*>(rgb), n_contrib, mode,
-                                                static_cast<const float*>(gin), loss, pg, s);
+                                                static_cast<const float*>(gin), ls, pg, s);
     if (e != hipSuccess) return check_hip(e, "gs_render_bwd_adam (composite)");
     return check_hip(gs::launch_project_bwd_adam(*x, *frame, *cfg, static_cast<const float*>(rec), meta, *bins, pg,
-                                                 *m, *v, w, mask, *acfg, s),
+                                                 *m, *v, w, mask, *acfg, ls, s),
                      "gs_render_bwd_adam (projection + optimiser)");
 }
 

@@ -205,6 +205,30 @@ __host__ __device__ inline int64_t partial_slot(uint64_t capacity, uint64_t e, i
     return sub == 0 ? int64_t(e) * 9 : (int64_t(capacity) + int64_t(e) * 3 + (sub - 1)) * 9;
 }
 
+// Where the compositing backward leaves the L1 loss of wavefront `sub` of a
+// tile: the last 4 n_tiles values of the partials' workspace (4 per tile),
+// free when the frame's pairs leave that much of the further slots unused;
+// the projection backward's launch then adds them up, a workgroup per job, in
+// a fixed order.  Without the room every wavefront adds its own sum to the
+// job's loss: some thousand same-address FP32 atomics in no fixed order,
+// whose rounding reached 1e-6 of the loss.
+template <typename T>
+struct LossSum {
+    T* slots;                   // 4 per tile
+    T* out;                     // per job; null: no loss wanted
+    const uint32_t* counters;
+    uint64_t capacity;
+    __device__ bool room(int n_tiles) const {
+        const uint64_t pairs = counters[GS_CTR_PAIRS];   // 0: none, or the caller has cleared the counters since
+        return pairs > 0 && pairs < capacity && (capacity - pairs) * 27u >= 4ull * uint64_t(n_tiles);
+    }
+};
+template <typename T>
+inline LossSum<T> loss_sum(T* ws, T* out, const uint32_t* counters, uint64_t capacity, int n_tiles) {
+    const int64_t at = int64_t(capacity) * 36 - 4 * int64_t(n_tiles);
+    return {out && at > 0 ? ws + at : ws, out, counters, capacity};
+}
+
 // quadrants (bit k = quadrant k of the tile) owned by wavefront `sub` of `waves`
 __device__ inline uint32_t owned_quadrants(int quads, int waves, int sub) {
     const int per = quads / waves;
@@ -340,6 +364,27 @@ __device__ inline uint32_t wave_incl_scan(uint32_t v) {
         if (lane >= off) v += t;
     }
     return v;
+}
+
+// One workgroup (of up to 1024 threads): adds job j's loss, left per tile and
+// wavefront by the compositing backward, to out[j].
+template <typename T>
+__device__ inline void add_job_loss(const gs_frame& frame, const LossSum<T>& L, int j) {
+    __shared__ T s_sum[16];
+    if (!L.room(frame.n_tiles)) return;     // uniform: the wavefronts added theirs themselves
+    const gs_job& job = frame.jobs[j];
+    const T* src = L.slots + 4 * int64_t(job.tile0);
+    const int64_t n = 4 * int64_t(job.tiles_x) * job.tiles_y;
+    T acc = T(0);
+    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) acc += src[i];
+    acc = wave_sum(acc);
+    if (lane_id() == 0) s_sum[threadIdx.x / kWave] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        T t = T(0);
+        for (int w = 0; w < int(blockDim.x) / kWave; w++) t += s_sum[w];
+        atomicAdd(L.out + j, t);
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -8,6 +8,7 @@
 #include <string>
 
 #include "gs.h"
+#include "gs_device.hpp"
 
 namespace gs {
 
@@ -45,13 +46,15 @@ hipError_t launch_project(const gs_params& p, const gs_frame& f, const gs_raster
                           uint32_t* meta, uint32_t* status, hipStream_t s);
 template <typename T>
 hipError_t launch_project_bwd(const gs_params& p, const gs_frame& f, const gs_raster_cfg& cfg, const T* rec,
-                              const uint32_t* meta, const gs_bins& bins, const T* pg, gs_params& grad, hipStream_t s);
+                              const uint32_t* meta, const gs_bins& bins, const T* pg, gs_params& grad,
+                              const LossSum<T>& loss, hipStream_t s);
 
 // fused projection backward + Adam/ADMM (FP32, jobs over disjoint ranges)
 hipError_t launch_project_bwd_adam(gs_params& x, const gs_frame& f, const gs_raster_cfg& cfg, const float* rec,
                                    const uint32_t* meta,
                                    const gs_bins& bins, const float* pg, gs_params& m, gs_params& v,
-                                   const gs_params* w, const float* mask, const gs_adam_cfg& acfg, hipStream_t s);
+                                   const gs_params* w, const float* mask, const gs_adam_cfg& acfg,
+                                   const LossSum<float>& loss, hipStream_t s);
 
 // binning.hip
 size_t bin_workspace_size(int64_t n_records, uint64_t capacity, int32_t n_tiles);
@@ -65,7 +68,7 @@ hipError_t launch_render_fwd(const gs_frame& f, const gs_raster_cfg& cfg, const 
 template <typename T>
 hipError_t launch_render_bwd(const gs_frame& f, const gs_raster_cfg& cfg, const T* rec, const uint32_t* meta,
                              const gs_bins& bins, const T* rgb, const uint32_t* ncontrib, gs_loss_mode mode,
-                             const T* grad_in, T* loss_out, T* pg, hipStream_t s);
+                             const T* grad_in, const LossSum<T>& loss, T* pg, hipStream_t s);
 
 // ssim.hip
 size_t ssim_workspace_size(int64_t n_pixels);

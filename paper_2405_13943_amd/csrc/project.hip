@@ -600,9 +600,13 @@ __global__ __launch_bounds__(128) void k_project_bwd_rec(const T* __restrict__ P
                                                           const uint4* __restrict__ meta,
                                                           const uint32_t* __restrict__ pair_off, uint64_t capacity,
                                                           const T* __restrict__ pg, T* __restrict__ grad,
-                                                          int64_t gstride) {
+                                                          int64_t gstride, LossSum<T> loss, unsigned loss_blocks) {
     constexpr int A = 11 + 3 * (D + 1) * (D + 1);
-    const int64_t r = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (blockIdx.x < loss_blocks) {     // uniform
+        add_job_loss(frame, loss, int(blockIdx.x));
+        return;
+    }
+    const int64_t r = int64_t(blockIdx.x - loss_blocks) * blockDim.x + threadIdx.x;
     const bool active = r < frame.n_records;   // no early return before the wave-wide sums
     const int j = job_of_record(frame.jobs, frame.n_jobs, active ? r : 0);
     const gs_job job = frame.jobs[j];
@@ -631,9 +635,13 @@ __global__ __launch_bounds__(128) void k_project_bwd_acc(const T* __restrict__ P
                                                           const T* __restrict__ rec, const uint4* __restrict__ meta,
                                                           const uint32_t* __restrict__ pair_off, uint64_t capacity,
                                                           const T* __restrict__ pg, T* __restrict__ grad,
-                                                          int64_t gstride) {
+                                                          int64_t gstride, LossSum<T> loss, unsigned loss_blocks) {
     constexpr int A = 11 + 3 * (D + 1) * (D + 1);
-    const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (blockIdx.x < loss_blocks) {     // uniform
+        add_job_loss(frame, loss, int(blockIdx.x));
+        return;
+    }
+    const int64_t g = int64_t(blockIdx.x - loss_blocks) * blockDim.x + threadIdx.x;
     const bool active = g < n;
     T* gout = grad + (active ? g : 0);
     if (active)
@@ -793,13 +801,18 @@ __global__ __launch_bounds__(kFusedBlock) void k_project_bwd_adam(
     float* __restrict__ M,
     int64_t sm, float* __restrict__ V, int64_t sv, const float* __restrict__ Wp, int64_t sw,
     const float* __restrict__ mask, AdamConsts c, uint32_t* __restrict__ status, unsigned rec_blocks, int64_t n,
-    int64_t n_unc) {
+    int64_t n_unc, LossSum<float> loss, unsigned loss_blocks) {
     constexpr int NK = (D + 1) * (D + 1);
     constexpr int A = 11 + 3 * NK;
+    if (blockIdx.x < loss_blocks) {     // uniform
+        add_job_loss(frame, loss, int(blockIdx.x));
+        return;
+    }
     if (adam_skipped(status)) return;   // uniform over the grid: no wavefront reaches the barrier
-    if (blockIdx.x >= rec_blocks) {     // uniform: a plane of 256 uncovered columns
+    const unsigned block = blockIdx.x - loss_blocks;
+    if (block >= rec_blocks) {          // uniform: a plane of 256 uncovered columns
         const unsigned per_plane = uncovered_blocks(n_unc);
-        const unsigned b = blockIdx.x - rec_blocks;
+        const unsigned b = block - rec_blocks;
         const int a = int(b / per_plane);
         const int grp = plane_group(a);
         float fin = 0.f;
@@ -822,7 +835,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_project_bwd_adam(
     __shared__ __align__(16) float s_Y[NK][kFusedBlock];
     __shared__ __align__(16) float s_dc[3][kFusedBlock];
     const int t = threadIdx.x;
-    const int64_t r0 = int64_t(blockIdx.x) * kFusedBlock;
+    const int64_t r0 = int64_t(block) * kFusedBlock;
     const int64_t r = r0 + t;
     const bool active = r < frame.n_records;   // no early return before the wave-wide sums and the barrier
     const int j = job_of_record(frame.jobs, frame.n_jobs, active ? r : 0);
@@ -899,40 +912,48 @@ hipError_t launch_project(const gs_params& p, const gs_frame& f, const gs_raster
     return hipGetLastError();
 }
 
+// workgroups in front of a projection backward's own that add up the loss
+template <typename T>
+static unsigned loss_blocks(const gs_frame& f, const LossSum<T>& loss) {
+    return loss.out && f.n_tiles > 0 ? unsigned(f.n_jobs) : 0u;
+}
+
 template <typename T, int D>
 static void project_bwd_dispatch(const gs_params& p, const gs_frame& f, const gs_raster_cfg& cfg, const T* rec,
                                  const uint4* M,
                                  const uint32_t* pair_off, uint64_t capacity, const T* pg,
-                                 gs_params& grad, hipStream_t s) {
+                                 gs_params& grad, const LossSum<T>& loss, hipStream_t s) {
     const T* P = static_cast<const T*>(p.data);
     T* Gd = static_cast<T*>(grad.data);
+    const unsigned lb = loss_blocks(f, loss);
     if (f.jobs_disjoint) {
         const int64_t n_unc = p.n - f.n_records;   // disjoint jobs: every record is another column
         if (n_unc > 0)
             GS_LAUNCH("k_zero_uncovered", (k_zero_uncovered<T>),
                       dim3(uncovered_blocks(n_unc), 11 + 3 * (D + 1) * (D + 1)), dim3(256), 0, s, p.n, n_unc, f, Gd,
                       grad.stride);
-        if (f.n_records > 0)
-            GS_LAUNCH("k_project_bwd_rec", (k_project_bwd_rec<T, D>), dim3(unsigned((f.n_records + 127) / 128)), dim3(128), 0, s,
-                               P, p.stride, f, cfg, rec, M, pair_off, capacity, pg, Gd, grad.stride);
+        if (f.n_records > 0 || lb > 0)
+            GS_LAUNCH("k_project_bwd_rec", (k_project_bwd_rec<T, D>), dim3(lb + unsigned((f.n_records + 127) / 128)),
+                      dim3(128), 0, s, P, p.stride, f, cfg, rec, M, pair_off, capacity, pg, Gd, grad.stride, loss, lb);
     } else {
-        GS_LAUNCH("k_project_bwd_acc", (k_project_bwd_acc<T, D>), dim3(unsigned((p.n + 127) / 128)), dim3(128), 0, s, P,
-                           p.stride, p.n, f, cfg, rec, M, pair_off, capacity, pg, Gd, grad.stride);
+        GS_LAUNCH("k_project_bwd_acc", (k_project_bwd_acc<T, D>), dim3(lb + unsigned((p.n + 127) / 128)), dim3(128), 0,
+                  s, P, p.stride, p.n, f, cfg, rec, M, pair_off, capacity, pg, Gd, grad.stride, loss, lb);
     }
 }
 
 template <typename T>
 hipError_t launch_project_bwd(const gs_params& p, const gs_frame& f, const gs_raster_cfg& cfg, const T* rec,
-                              const uint32_t* meta, const gs_bins& bins, const T* pg, gs_params& grad, hipStream_t s) {
-    if (p.n == 0) return hipSuccess;
+                              const uint32_t* meta, const gs_bins& bins, const T* pg, gs_params& grad,
+                              const LossSum<T>& loss, hipStream_t s) {
+    if (p.n == 0) return hipSuccess;    // no pairs either: the compositing backward has added the loss
     const uint4* M = reinterpret_cast<const uint4*>(meta);
     const uint32_t* po = bins.pair_off;
     const uint64_t cap = bins.capacity;
     switch (p.sh_degree) {
-        case 0: project_bwd_dispatch<T, 0>(p, f, cfg, rec, M, po, cap, pg, grad, s); break;
-        case 1: project_bwd_dispatch<T, 1>(p, f, cfg, rec, M, po, cap, pg, grad, s); break;
-        case 2: project_bwd_dispatch<T, 2>(p, f, cfg, rec, M, po, cap, pg, grad, s); break;
-        default: project_bwd_dispatch<T, 3>(p, f, cfg, rec, M, po, cap, pg, grad, s); break;
+        case 0: project_bwd_dispatch<T, 0>(p, f, cfg, rec, M, po, cap, pg, grad, loss, s); break;
+        case 1: project_bwd_dispatch<T, 1>(p, f, cfg, rec, M, po, cap, pg, grad, loss, s); break;
+        case 2: project_bwd_dispatch<T, 2>(p, f, cfg, rec, M, po, cap, pg, grad, loss, s); break;
+        default: project_bwd_dispatch<T, 3>(p, f, cfg, rec, M, po, cap, pg, grad, loss, s); break;
     }
     return hipGetLastError();
 }
@@ -943,7 +964,8 @@ template <int D, bool PEN, bool MASK>
 static void project_bwd_adam_launch(gs_params& x, const gs_frame& f, const gs_raster_cfg& cfg, const float* rec,
                                     const uint4* M,
                                     const uint32_t* pair_off, uint64_t capacity, const float* pg, gs_params& m, gs_params& v, const gs_params* w,
-                                    const float* mask, const AdamConsts& c, uint32_t* status, hipStream_t s) {
+                                    const float* mask, const AdamConsts& c, uint32_t* status, const LossSum<float>& loss,
+                                    hipStream_t s) {
     float* X = static_cast<float*>(x.data);
     float* Mo = static_cast<float*>(m.data);
     float* Vo = static_cast<float*>(v.data);
@@ -955,15 +977,16 @@ static void project_bwd_adam_launch(gs_params& x, const gs_frame& f, const gs_ra
     constexpr unsigned A = 11 + 3 * (D + 1) * (D + 1);
     const unsigned rec_blocks = unsigned((f.n_records + kFusedBlock - 1) / kFusedBlock);
     const int64_t n_unc = x.n > f.n_records ? x.n - f.n_records : 0;   // disjoint jobs: every record is another column
-    const dim3 grid(rec_blocks + A * uncovered_blocks(n_unc)), block(kFusedBlock);
+    const unsigned lb = loss_blocks(f, loss);
+    const dim3 grid(lb + rec_blocks + A * uncovered_blocks(n_unc)), block(kFusedBlock);
     if (vec)
         GS_LAUNCH("k_project_bwd_adam", (k_project_bwd_adam<D, PEN, MASK, true>), grid, block, 0, s, X, x.stride, f,
                   cfg, rec, M, pair_off, capacity, pg, Mo, m.stride, Vo, v.stride, Wd, sw, mask, c, status,
-                  rec_blocks, x.n, n_unc);
+                  rec_blocks, x.n, n_unc, loss, lb);
     else
         GS_LAUNCH("k_project_bwd_adam", (k_project_bwd_adam<D, PEN, MASK, false>), grid, block, 0, s, X, x.stride,
                   f, cfg, rec, M, pair_off, capacity, pg, Mo, m.stride, Vo, v.stride, Wd, sw, mask, c, status,
-                  rec_blocks, x.n, n_unc);
+                  rec_blocks, x.n, n_unc, loss, lb);
 }
 
 template <int D>
@@ -971,34 +994,35 @@ static void project_bwd_adam_pen(gs_params& x, const gs_frame& f, const gs_raste
                                  const uint4* M,
                                  const uint32_t* po, uint64_t cap, const float* pg,
                                  gs_params& m, gs_params& v, const gs_params* w, const float* mask,
-                                 const AdamConsts& c, uint32_t* st, hipStream_t s) {
-    if (w && mask) project_bwd_adam_launch<D, true, true>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, s);
-    else if (w) project_bwd_adam_launch<D, true, false>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, s);
-    else project_bwd_adam_launch<D, false, false>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, s);
+                                 const AdamConsts& c, uint32_t* st, const LossSum<float>& ls, hipStream_t s) {
+    if (w && mask) project_bwd_adam_launch<D, true, true>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, ls, s);
+    else if (w) project_bwd_adam_launch<D, true, false>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, ls, s);
+    else project_bwd_adam_launch<D, false, false>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, ls, s);
 }
 
 hipError_t launch_project_bwd_adam(gs_params& x, const gs_frame& f, const gs_raster_cfg& cfg, const float* rec,
                                    const uint32_t* meta,
                                    const gs_bins& bins, const float* pg, gs_params& m, gs_params& v,
-                                   const gs_params* w, const float* mask, const gs_adam_cfg& acfg, hipStream_t s) {
-    if (x.n == 0) return hipSuccess;
+                                   const gs_params* w, const float* mask, const gs_adam_cfg& acfg,
+                                   const LossSum<float>& ls, hipStream_t s) {
+    if (x.n == 0) return hipSuccess;    // no pairs either: the compositing backward has added the loss
     const uint4* M = reinterpret_cast<const uint4*>(meta);
     const AdamConsts c = adam_consts(acfg);
     const uint32_t* po = bins.pair_off;
     const uint64_t cap = bins.capacity;
     uint32_t* st = bins.counters + GS_CTR_STATUS;
     switch (x.sh_degree) {
-        case 0: project_bwd_adam_pen<0>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, s); break;
-        case 1: project_bwd_adam_pen<1>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, s); break;
-        case 2: project_bwd_adam_pen<2>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, s); break;
-        default: project_bwd_adam_pen<3>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, s); break;
+        case 0: project_bwd_adam_pen<0>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, ls, s); break;
+        case 1: project_bwd_adam_pen<1>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, ls, s); break;
+        case 2: project_bwd_adam_pen<2>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, ls, s); break;
+        default: project_bwd_adam_pen<3>(x, f, cfg, rec, M, po, cap, pg, m, v, w, mask, c, st, ls, s); break;
     }
     return hipGetLastError();
 }
 
 template hipError_t launch_project<float>(const gs_params&, const gs_frame&, const gs_raster_cfg&, float*, uint32_t*, uint32_t*, hipStream_t);
 template hipError_t launch_project<double>(const gs_params&, const gs_frame&, const gs_raster_cfg&, double*, uint32_t*, uint32_t*, hipStream_t);
-template hipError_t launch_project_bwd<float>(const gs_params&, const gs_frame&, const gs_raster_cfg&, const float*, const uint32_t*, const gs_bins&, const float*, gs_params&, hipStream_t);
-template hipError_t launch_project_bwd<double>(const gs_params&, const gs_frame&, const gs_raster_cfg&, const double*, const uint32_t*, const gs_bins&, const double*, gs_params&, hipStream_t);
+template hipError_t launch_project_bwd<float>(const gs_params&, const gs_frame&, const gs_raster_cfg&, const float*, const uint32_t*, const gs_bins&, const float*, gs_params&, const LossSum<float>&, hipStream_t);
+template hipError_t launch_project_bwd<double>(const gs_params&, const gs_frame&, const gs_raster_cfg&, const double*, const uint32_t*, const gs_bins&, const double*, gs_params&, const LossSum<double>&, hipStream_t);
 
 }  // namespace gs

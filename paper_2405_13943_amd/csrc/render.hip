@@ -375,7 +375,7 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
     gs_frame frame, gs_raster_cfg cfg, const T* __restrict__ rec, const uint4* __restrict__ meta,
     const uint32_t* __restrict__ pair_off, const uint32_t* __restrict__ vals, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ order, uint64_t capacity, const T* __restrict__ rgb,
-    const uint32_t* __restrict__ ncontrib, int mode, const T* __restrict__ gin, T* __restrict__ loss_out,
+    const uint32_t* __restrict__ ncontrib, int mode, const T* __restrict__ gin, LossSum<T> loss_to,
     T* __restrict__ pg, const uint8_t* __restrict__ qmask) {
     constexpr int PPL = QX * QY;
     // NS wavefronts per tile, wave `sub` owning the tile's sub-tile of QX x QY
@@ -392,36 +392,7 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
     int tile = 0, sub = 0, nwaves = NSD;
     uint32_t owned = (1u << PPL) - 1u;
     bool valid = true;   // no early return: the workgroup may meet at a barrier below
-    // L1 loss: the workgroup's wavefronts leave their sums in LDS and the
-    // last to arrive adds them per job, one global atomic per job and
-    // workgroup instead of one per wavefront (same-address atomics from
-    // every wavefront of the launch cost it about a sixth of its time)
-    __shared__ T s_loss[kRenderWaves];
-    __shared__ int s_ljob[kRenderWaves];
-    __shared__ uint32_t s_larrived;
     __shared__ uint32_t s_wend[kRenderWaves];   // per wavefront: list entries its pixels need (the fold reads as many)
-    const bool wg_loss = mode == GS_LOSS_L1 && loss_out != nullptr;
-    auto arrive = [&](T l, int jl) {
-        if (lane != 0) return;
-        s_loss[wave] = l;
-        s_ljob[wave] = jl;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        if (atomicAdd(&s_larrived, 1u) != uint32_t(kRenderWaves - 1)) return;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        for (int a = 0; a < kRenderWaves; a++) {
-            const int ja = s_ljob[a];
-            bool first = ja >= 0;
-            for (int b = 0; b < a; b++) first = first && s_ljob[b] != ja;
-            if (!first) continue;
-            T sum = T(0);
-            for (int b = a; b < kRenderWaves; b++) sum += s_ljob[b] == ja ? s_loss[b] : T(0);
-            atomicAdd(loss_out + ja, sum);
-        }
-    };
-    if (wg_loss) {
-        if (threadIdx.x == 0) s_larrived = 0u;
-        __syncthreads();
-    }
     if (ADAPT) {
         valid = plan_wave<true>(order, frame.n_tiles, blockIdx.x * kRenderWaves + wave, tile, sub, nwaves);
         owned = valid ? owned_quadrants(PPL, nwaves, sub) : 0u;
@@ -431,7 +402,6 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
         sub = gw % NSD;
         valid = tile < frame.n_tiles;
     }
-    if (wg_loss && !valid) arrive(T(0), -1);
     auto pslot = [&](uint32_t e) { return partial_slot(capacity, e, NS == 1 ? 0 : sub); };
     do {
     if (!valid) break;
@@ -484,9 +454,18 @@ __global__ __launch_bounds__(kWave * kRenderWaves) void k_render_bwd(
             }
         }
     }
-    if (mode == GS_LOSS_L1 && loss_out) {
+    if (mode == GS_LOSS_L1 && loss_to.out) {
         const T l = wave_sum(loss);
-        arrive(l, j);
+        if (lane == 0) {
+            if (loss_to.room(frame.n_tiles)) {
+                T* slot = loss_to.slots + 4 * int64_t(tile);
+                slot[sub] = l;
+                if (sub == 0)
+                    for (int q = nwaves; q < 4; q++) slot[q] = T(0);
+            } else {
+                atomicAdd(loss_to.out + j, l);
+            }
+        }
     }
 
     const uint2 range = ranges[tile];
@@ -733,8 +712,8 @@ static void fwd_launch(const gs_frame& f, const gs_raster_cfg& cfg, const T* rec
 
 template <typename T, int QX, int QY, int NS>
 static void bwd_launch(const gs_frame& f, const gs_raster_cfg& cfg, const T* rec, const uint32_t* meta,
-                       const gs_bins& b, const T* rgb, const uint32_t* nc, int mode, const T* gin, T* loss, T* pg,
-                       hipStream_t s) {
+                       const gs_bins& b, const T* rgb, const uint32_t* nc, int mode, const T* gin,
+                       const LossSum<T>& loss, T* pg, hipStream_t s) {
     dim3 grid, block;
     compositing_grid<NS>(f, grid, block);
     GS_LAUNCH("k_render_bwd", (k_render_bwd<T, QX, QY, NS>), grid, block, 0, s, f, cfg, rec,
@@ -780,7 +759,7 @@ hipError_t launch_render_fwd(const gs_frame& f, const gs_raster_cfg& cfg, const 
 template <typename T>
 hipError_t launch_render_bwd(const gs_frame& f, const gs_raster_cfg& cfg, const T* rec, const uint32_t* meta,
                              const gs_bins& bins, const T* rgb, const uint32_t* nc, gs_loss_mode mode, const T* gin,
-                             T* loss, T* pg, hipStream_t s) {
+                             const LossSum<T>& loss, T* pg, hipStream_t s) {
     if (f.n_tiles == 0) return hipSuccess;
     GS_TILE_DISPATCH(launch_waves(cfg, bwd_waves(cfg), f.n_tiles, kBwdFill), bwd_launch, f, cfg, rec, meta, bins, rgb, nc, int(mode), gin, loss, pg, s);
     return hipGetLastError();
@@ -788,7 +767,7 @@ hipError_t launch_render_bwd(const gs_frame& f, const gs_raster_cfg& cfg, const 
 
 template hipError_t launch_render_fwd<float>(const gs_frame&, const gs_raster_cfg&, const float*, const gs_bins&, float*, float*, uint32_t*, unsigned long long*, hipStream_t);
 template hipError_t launch_render_fwd<double>(const gs_frame&, const gs_raster_cfg&, const double*, const gs_bins&, double*, double*, uint32_t*, unsigned long long*, hipStream_t);
-template hipError_t launch_render_bwd<float>(const gs_frame&, const gs_raster_cfg&, const float*, const uint32_t*, const gs_bins&, const float*, const uint32_t*, gs_loss_mode, const float*, float*, float*, hipStream_t);
-template hipError_t launch_render_bwd<double>(const gs_frame&, const gs_raster_cfg&, const double*, const uint32_t*, const gs_bins&, const double*, const uint32_t*, gs_loss_mode, const double*, double*, double*, hipStream_t);
+template hipError_t launch_render_bwd<float>(const gs_frame&, const gs_raster_cfg&, const float*, const uint32_t*, const gs_bins&, const float*, const uint32_t*, gs_loss_mode, const float*, const LossSum<float>&, float*, hipStream_t);
+template hipError_t launch_render_bwd<double>(const gs_frame&, const gs_raster_cfg&, const double*, const uint32_t*, const gs_bins&, const double*, const uint32_t*, gs_loss_mode, const double*, const LossSum<double>&, double*, hipStream_t);
 
 }  // namespace gs

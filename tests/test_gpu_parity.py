@@ -706,3 +706,31 @@ def test_wavefronts_by_tile_count(cfg1, tile, size):
     a, b = out[0][3].double(), out[1][3].double()
     assert ((a - b).norm(dim=1) <= 1e-4 * b.norm(dim=1) + 1e-12).all()
     torch.testing.assert_close(out[0][4], out[1][4], rtol=1e-5, atol=0)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("views", [1, 4])
+def test_l1_loss_with_and_without_room_for_its_sum(cfg1, dtype, views):
+    """The loss summed per tile in the free end of the backward workspace
+    (the same bits every call) and, with a pair capacity of exactly the
+    frame's pairs, by the wavefronts' own atomics: both add w mean |C -
+    target| to what loss_out holds, and the gradients are the same."""
+    cfg = gs.raster_cfg((16, 16))
+    frame = make_frame(cfg1, cfg, list(range(views)))
+    params = torch.from_numpy(cfg1.params).to("cuda", dtype)
+    target = frame_target(frame, cfg1, range(views)).to(dtype)
+    pairs = gs.read_counters(gs.rasterize(params, frame, cfg))["pairs"]
+    got = []
+    for capacity in (pairs, pairs + 1, 4 * pairs, 4 * pairs):
+        buf = gs.rasterize(params, frame, cfg, gs.Buffers(frame, capacity, dtype))
+        assert buf.capacity == capacity
+        loss = torch.full((views,), 0.25, dtype=dtype, device="cuda")
+        grad = torch.empty_like(params)
+        gs.render_bwd(params, frame, cfg, buf, grad, gs.LOSS_L1, target, loss)
+        got.append((loss, grad))
+    ref = [0.25 + (frame.image(buf.rgb, k).double() - frame.image(target, k).double()).abs().mean().item() / views
+           for k in range(views)]
+    for loss, grad in got:
+        np.testing.assert_allclose(loss.cpu().numpy(), ref, rtol=2e-6 if dtype == torch.float32 else 1e-13)
+        assert torch.equal(grad, got[0][1])
+    assert torch.equal(got[2][0], got[3][0])
