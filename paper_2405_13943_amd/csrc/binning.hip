@@ -626,11 +626,10 @@ __device__ void tile_plan(const uint2* __restrict__ ranges, const uint32_t* __re
             nf += bucket >= bf ? c : 0u;
             nb += bucket >= bb ? c : 0u;
         }
-        // shares in 1/65536, rounded up so that a single tile counts
-        auto share = [&](uint32_t n) {
-            return n_tiles > 0 ? uint32_t(min((uint64_t(n) * 65536u + uint64_t(n_tiles) - 1u) / uint64_t(n_tiles),
-                                              uint64_t(0xffff))) : 0u;
-        };
+        // shares in 1/65536, rounded up so that a single tile counts (any
+        // share is a valid split: the passes only need the same number)
+        const float per = n_tiles > 0 ? 65536.0f / float(n_tiles) : 0.0f;
+        auto share = [&](uint32_t n) { return n > 0 ? min(uint32_t(float(n) * per) + 1u, 0xffffu) : 0u; };
         order[3] = share(nf) | share(nb) << 16;
         order[0] = tot[0];
         order[1] = tot[1];

@@ -127,8 +127,8 @@ __device__ inline int adaptive_waves(uint32_t count, uint32_t pairs, int n_tiles
 // plan's first group and 2 beyond.  A tile is worth splitting when its list
 // alone would outlast the launch: when it is longer than the entries per
 // resident wavefront by some factor, so the line moves with n_tiles / resident
-// wavefronts, in units of the mean list length; below some 3,000 tiles lines
-// of 1.5 (forward) and 2 (backward) times the mean take over.  Splitting
+// wavefronts, in units of the mean list length; below some 5,000 tiles the
+// plan's 1.25 (forward) and 2 (backward) times the mean take over.  Splitting
 // below the line repeats staging and, in the backward, each record's
 // reduction and store for nothing.  Measured, us with every tile above 1.25x
 // the mean split / with the line here / with no split (1600x1066 unless
@@ -141,7 +141,7 @@ __device__ inline int adaptive_waves(uint32_t count, uint32_t pairs, int n_tiles
 // Line in half means, rounded: the bucket from which tiles are split.
 __host__ __device__ inline int fwd_split_bucket(int n_tiles) {
     const int b = (n_tiles + 1080) / 2160;     // 1.66 x entries per wavefront at 7 per SIMD
-    return b < 3 ? 3 : b;
+    return b < 3 ? 2 : b;                      // 2: every tile of the plan's groups
 }
 __host__ __device__ inline int bwd_split_bucket(int n_tiles) {
     const int b = (n_tiles + 560) / 1120;      // 1.83 x entries per wavefront at 4 per SIMD
