@@ -110,6 +110,7 @@ class Slot:
 
 class RenderServer:
     MAX_TRIES = 4      # overflowing launches of one request before the server gives up
+    GATHER = 100e-6    # run_open_loop: an arrival due this soon is waited for (a launch takes longer)
 
     def __init__(self, params: torch.Tensor, cfg: gs.GsRasterCfg, hbm_budget: float = 32e9, n_slots: int = 3,
                  max_batch: int = 16, resolutions=None, pair_headroom: float = 1.5, spatial_order: bool = True):
@@ -269,6 +270,10 @@ class RenderServer:
 
     def run_open_loop(self, cams, arrivals, warmup=0.0, keep=()):
         """Serve requests arriving at the given times (seconds from start).
+        Submitting and launching share this thread, and a launch keeps it for
+        some 200 us: what falls due meanwhile would wait for it and then for
+        a launch of its own, so an arrival due within ``GATHER`` seconds of
+        a submission is waited for and joins its batch.
         Returns latency / throughput statistics over requests arriving after
         ``warmup``; the images of request ids in ``keep`` are kept (copied out
         of the pinned pool), all others are released when done."""
@@ -280,10 +285,14 @@ class RenderServer:
         n_done = 0
         while nxt < len(arrivals) or not self.idle():
             now = time.perf_counter() - t0
-            while nxt < len(arrivals) and arrivals[nxt] <= now:
+            due = now                       # moved on by GATHER past each request submitted
+            while nxt < len(arrivals) and arrivals[nxt] <= due:
+                while now < arrivals[nxt]:
+                    now = time.perf_counter() - t0
                 r = self.submit(nxt, cams[nxt], t0 + arrivals[nxt])
                 reqs.append(r)
                 nxt += 1
+                due = max(now, arrivals[nxt - 1] + self.GATHER)
             self.poll(now)
             for r in self.finished[n_done:]:
                 if r.rid in keep:
