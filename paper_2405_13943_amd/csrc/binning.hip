@@ -459,30 +459,52 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ tke
 
 // ---------------------------------------------------------------------------
 // per-tile depth order: each tile's list (record ids, any order) sorted by the
-// unique key (depth bits, record id).  k_tile_sort<ITEMS> (persistent grid,
-// one list per workgroup at a time) takes lists of up to kSortBlock * ITEMS
-// entries: up to one workgroup's width a rank sort in LDS (each thread
-// counts the keys below its own), longer ones a merge sort in LDS (4 keys
-// per thread up to 1024 entries, ITEMS beyond).  ITEMS is 8 (16 KB of LDS
-// per workgroup, twice as many workgroups resident) unless the frame's
-// lists are long on average (ITEMS 16, lists up to 4096 on chip).
-// k_tile_sort_long takes the longer lists, one large workgroup each.
+// unique key (depth bits, record id).
 //
-// The merge sort: every thread sorts E consecutive keys in registers (a
-// sorting network), then rounds of pairwise merges double the sorted runs;
-// in a round each thread produces E consecutive outputs of its pair of runs,
-// finding where they start in the two inputs by binary search along the
-// merge path and then merging sequentially (ties go to the first run).  The
-// work is O(n log n) with one LDS read and write per key and round.
+// Bucket sort on chip: the depths' bit patterns, scaled linearly over the
+// list's own range, pick one of a few buckets per key; LDS atomics count the
+// buckets, a scan places them, and each key's place inside its bucket is the
+// number of smaller keys there (two or three to compare with on average).
+// That is a constant number of LDS round trips per key, where merging sorted
+// runs takes one dependent pair per key and round of log2(n / 8) rounds, with
+// a binary search each: at lists of 1,300 (the 6M-Gaussian view) 165 -> 84 us
+// a launch, at 760 (three 640x417 views of 100k) 41 -> 24.  Depths so clustered that a bucket holds more than kBucketMost
+// keys are merge-sorted instead (workgroups) or ranked by comparison
+// (wavefronts).
+//
+// Three forms, by the frame's mean list length (pair capacity / tiles, which
+// includes the caller's headroom):
+//   kSortWaves  lists of up to 512 by one wavefront each, without a barrier,
+//               four to a workgroup, which takes longer ones as a whole.
+//               Such lists are bound by the latency of the loads they hang
+//               on (range, ids, depths), so what counts is how many are in
+//               flight: at a mean of 108 (500k, 1600x1066) every list is, and
+//               the launch takes 12 us (19 as a workgroup a list, ranked by
+//               comparison; 17 with 256 to a wavefront, as the workgroups
+//               with longer lists then go round twice).  At a mean of 220
+//               (three served views, capacity 287 a tile) 58 -> 36 us;
+//   kSortBlocks one list per workgroup of 256;
+//   kSortDense  one list per workgroup of 512, up to 4096 on chip.
+// k_tile_sort_long takes the longer lists, one large workgroup each, by
+// merging: every thread sorts E consecutive keys in registers (a sorting
+// network), then rounds of pairwise merges double the sorted runs; in a round
+// each thread produces E consecutive outputs of its pair of runs, finding
+// where they start in the two inputs by binary search along the merge path
+// and then merging sequentially (ties go to the first run).
 
-constexpr int kSortBlock = 256;
-constexpr int kSortItems = 8;                           // lists up to 2048 on chip
-constexpr int kSortItemsDense = 16;                     // lists up to 4096 on chip
-constexpr uint64_t kDenseList = 1024;                   // mean list length (capacity / tiles) above which: dense
-constexpr int kSortItemsShort = 4;                      // lists up to 1024: more threads, shorter merges
+constexpr int kSortWaves = 0, kSortBlocks = 1, kSortDense = 2;
+constexpr uint64_t kWaveList = 400;                     // mean list length up to which: kSortWaves
+constexpr uint64_t kDenseList = 1024;                   // and above which: kSortDense
+constexpr int kSortItems = 8;                           // keys per thread: lists up to 2048 (dense: 4096) on chip
+constexpr int kWaveItems = 8;                           // keys per lane of a wavefront's list
+constexpr int kWaveMost = kWaveItems * kWave;           // 512
+constexpr uint32_t kBucketMost = 32;
 constexpr int kLongBlock = 1024;
 constexpr int kLongItems = 8;
 constexpr int kLongChunk = kLongBlock * kLongItems;     // 8192
+__host__ __device__ constexpr int sort_block(int form) { return form == kSortDense ? 512 : 256; }
+__host__ __device__ constexpr int sort_chunk(int form) { return sort_block(form) * kSortItems; }
+__host__ __device__ constexpr int sort_buckets(int form) { return sort_chunk(form) / 2; }
 
 __device__ __forceinline__ uint64_t depth_key(const uint4* __restrict__ meta, uint32_t r) {
     return (uint64_t(meta[r].x) << 32) | r;
@@ -575,143 +597,399 @@ __device__ void block_merge_sort(uint64_t* sk, uint32_t n) {
     }
 }
 
-// Compositing plan for adaptive wavefronts: every tile's wavefront count
-// (adaptive_waves of its list length) and the tiles grouped by it, 4-wave
-// tiles first (one workgroup each), then 2-wave, then 1-wave tiles; inside
-// a group the longer lists first, by buckets of half the frame's mean list
-// length (the last bucket open-ended), so that the heaviest tiles of each
-// group do not start last; and the leading share of that list which each
-// pass splits (pass_plan).  One workgroup (of any multiple of the
-// wavefront); the order inside a bucket is whatever the LDS atomics give,
-// which changes no result (each tile is composited on its own).  The first
-// pass counts the buckets and keeps each tile's bucket in `cache` (LDS, when
-// n_tiles <= cache_cap) for the second, which places the tiles.
+// Compositing plan for adaptive wavefronts: the tiles grouped by the most
+// wavefronts they may take (adaptive_waves of the list length), 4-wave tiles
+// first (one workgroup each), then 2-wave, then 1-wave tiles; inside a group
+// the longer lists first, by buckets of half the frame's mean list length (the
+// last bucket open-ended), so that the heaviest tiles of each group do not
+// start last; and the leading share of that list which each pass splits
+// (pass_plan).  A counting sort by bin = (group, bucket) over chunks of the
+// tiles, in two parts that ride on launches of their own length: workgroups
+// of k_tile_sort count each chunk's bins (plan_count), workgroups of
+// k_tile_sort_long add the counts up and place their chunk's tiles
+// (plan_place).  As one workgroup of 256 beside the sorts the plan kept that
+// launch at 20 us at 6,700 tiles (14 without it) and 59 at 13,660 (38).  The
+// order inside a bin is whatever the LDS atomics give, which changes no
+// result (each tile is composited on its own).
 constexpr int kPlanBuckets = 16;
+constexpr int kPlanBins = 3 * kPlanBuckets;
+constexpr int kPlanBlocks = 1024;           // most chunks
+static_assert(kPlanBins <= kWave, "a bin per lane, six bits a bin");
+static_assert(kPlanBins * kPlanBlocks <= 256 * kMaxGrid, "the chunks' counts fit the radix histograms' place");
 
-__device__ void tile_plan(const uint2* __restrict__ ranges, const uint32_t* __restrict__ counters, int n_tiles,
-                          int quads, uint32_t* __restrict__ order, uint8_t* cache, int cache_cap) {
-    constexpr int NB = 3 * kPlanBuckets;
-    static_assert(NB <= 256, "a tile's bin fits a byte");
-    __shared__ uint32_t cnt[NB];
-    const bool cached = cache != nullptr && n_tiles <= cache_cap;
-    const uint64_t pairs = counters[GS_CTR_PAIRS];
-    for (int k = threadIdx.x; k < NB; k += blockDim.x) cnt[k] = 0u;
-    __syncthreads();
-    // bin: group (4, 2, 1 wavefronts) major, then the length bucket, longest first
-    auto bin = [&](int t) {
-        const uint32_t n = ranges[t].y - ranges[t].x;
-        const int w = adaptive_waves(n, uint32_t(pairs), n_tiles, quads);
-        const int grp = w == 4 ? 0 : (w == 2 ? 1 : 2);
-        const uint64_t q = pairs ? (2ull * n * uint64_t(n_tiles)) / pairs : 0ull;   // n / (mean / 2)
-        const int bucket = q < uint64_t(kPlanBuckets - 1) ? int(q) : kPlanBuckets - 1;
-        return grp * kPlanBuckets + (kPlanBuckets - 1 - bucket);
-    };
-    for (int t = threadIdx.x; t < n_tiles; t += blockDim.x) {
-        const int b = bin(t);
-        if (cached) cache[t] = uint8_t(b);
-        atomicAdd(&cnt[b], 1u);
+__host__ __device__ inline int plan_blocks(int n_tiles) {
+    const int b = (n_tiles + 1023) / 1024;
+    return b < kPlanBlocks ? b : kPlanBlocks;
+}
+
+struct Plan {
+    const uint2* ranges;
+    const uint32_t* counters;
+    uint32_t* part;             // counts [chunk][kPlanBins]
+    uint32_t* order;            // null: no plan
+    int n_tiles, quads, blocks;
+};
+
+// bin of a tile: group (4, 2, 1 wavefronts) major, then the length bucket,
+// longest first.  The bucket is floor(n / (mean / 2)), from a float quotient
+// put right in integers
+__device__ inline uint32_t plan_bin(const Plan& p, uint32_t pairs, uint2 rg) {
+    const uint32_t n = rg.y - rg.x;
+    const int w = adaptive_waves(n, pairs, p.n_tiles, p.quads);
+    const int grp = w == 4 ? 0 : (w == 2 ? 1 : 2);
+    constexpr uint32_t last = kPlanBuckets - 1;
+    const uint64_t twice = 2ull * n * uint64_t(p.n_tiles);
+    const float half = pairs ? 2.0f * float(p.n_tiles) / float(pairs) : 0.0f;
+    uint32_t q = uint32_t(fminf(float(n) * half, float(last)));
+    if (q < last && uint64_t(q + 1) * pairs <= twice) q++;
+    if (q > 0 && uint64_t(q) * pairs > twice) q--;
+    return uint32_t(grp * kPlanBuckets) + last - q;
+}
+
+// Adds one to cnt[b] for every active lane and returns the lane's place among
+// them: one LDS atomic per distinct b of the wavefront (most tiles share a
+// few bins, whose same-address atomics would serialise).
+__device__ inline uint32_t plan_slot(uint32_t* cnt, uint32_t b) {
+    uint64_t peers = __ballot(1);
+    for (int bit = 0; bit < 6; bit++) {
+        const uint64_t m = __ballot((b >> bit) & 1u);
+        peers &= ((b >> bit) & 1u) ? m : ~m;
     }
+    const int leader = __ffsll((long long)peers) - 1;
+    uint32_t base = 0u;
+    if (lane_id() == leader) base = atomicAdd(&cnt[b], uint32_t(__popcll(peers)));
+    base = __shfl(base, leader, kWave);
+    return base + uint32_t(__popcll(peers & lanemask_lt()));
+}
+
+// tiles of chunk c
+__device__ inline void plan_chunk(const Plan& p, int c, int& t0, int& t1) {
+    const int per = (p.n_tiles + p.blocks - 1) / p.blocks;
+    t0 = min(p.n_tiles, c * per);
+    t1 = min(p.n_tiles, t0 + per);
+}
+
+// one workgroup: the bins of chunk c counted; cnt: kPlanBins words of LDS
+__device__ inline void plan_count(const Plan& p, int c, uint32_t* cnt) {
+    if (threadIdx.x < kPlanBins) cnt[threadIdx.x] = 0u;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t run = 0u, tot[3] = {0u, 0u, 0u};
-        const int bf = min(fwd_split_bucket(n_tiles), kPlanBuckets - 1);
-        const int bb = min(bwd_split_bucket(n_tiles), kPlanBuckets - 1);
-        uint32_t nf = 0u, nb = 0u;
-        for (int k = 0; k < NB; k++) {
-            const uint32_t c = cnt[k];
-            cnt[k] = run;                  // first place of the bin
-            run += c;
-            tot[k / kPlanBuckets] += c;
-            const int bucket = kPlanBuckets - 1 - k % kPlanBuckets;
-            nf += bucket >= bf ? c : 0u;
-            nb += bucket >= bb ? c : 0u;
+    const uint32_t pairs = p.counters[GS_CTR_PAIRS];
+    int t0, t1;
+    plan_chunk(p, c, t0, t1);
+    for (int t = t0 + int(threadIdx.x); t < t1; t += int(blockDim.x)) plan_slot(cnt, plan_bin(p, pairs, p.ranges[t]));
+    __syncthreads();
+    if (threadIdx.x < kPlanBins) p.part[c * kPlanBins + int(threadIdx.x)] = cnt[threadIdx.x];
+}
+
+// one workgroup (at most 1024 threads): the tiles of chunk c placed; chunk 0
+// also writes the counts and shares.  cnt: 2 * kPlanBins words of LDS
+__device__ inline void plan_place(const Plan& p, int c, uint32_t* cnt) {
+    uint32_t* all = cnt + kPlanBins;
+    if (threadIdx.x < 2 * kPlanBins) cnt[threadIdx.x] = 0u;
+    __syncthreads();
+    const int lane = lane_id(), waves = int(blockDim.x) / kWave;
+    uint32_t total = 0u, before = 0u;       // of bin `lane`, over this wavefront's share of the chunks
+    if (lane < kPlanBins)
+        for (int b = int(threadIdx.x) / kWave; b < p.blocks; b += waves) {
+            const uint32_t n = p.part[b * kPlanBins + lane];
+            total += n;
+            before += b < c ? n : 0u;
         }
-        // shares in 1/65536, rounded up so that a single tile counts (any
-        // share is a valid split: the passes only need the same number)
-        const float per = n_tiles > 0 ? 65536.0f / float(n_tiles) : 0.0f;
-        auto share = [&](uint32_t n) { return n > 0 ? min(uint32_t(float(n) * per) + 1u, 0xffffu) : 0u; };
-        order[3] = share(nf) | share(nb) << 16;
-        order[0] = tot[0];
-        order[1] = tot[1];
-        order[2] = tot[2];
+    if (lane < kPlanBins) {
+        if (total) atomicAdd(&all[lane], total);
+        if (before) atomicAdd(&cnt[lane], before);
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < n_tiles; t += blockDim.x) {
-        const int b = cached ? int(cache[t]) : bin(t);
-        order[4 + atomicAdd(&cnt[b], 1u)] = uint32_t(t);
+    if (threadIdx.x < kWave) {
+        const uint32_t n = lane < kPlanBins ? all[lane] : 0u;
+        const uint32_t first = wave_incl_scan_dpp(n) - n;
+        if (lane < kPlanBins) cnt[lane] += first;
+        if (c == 0) {
+            const int bucket = kPlanBuckets - 1 - lane % kPlanBuckets;
+            const int bf = min(fwd_split_bucket(p.n_tiles), kPlanBuckets - 1);
+            const int bb = min(bwd_split_bucket(p.n_tiles), kPlanBuckets - 1);
+            const uint32_t nf = wave_sum_u32(bucket >= bf ? n : 0u), nb = wave_sum_u32(bucket >= bb ? n : 0u);
+            const uint32_t n4 = __shfl(first, kPlanBuckets, kWave), n42 = __shfl(first, 2 * kPlanBuckets, kWave);
+            if (lane == 0) {
+                p.order[0] = n4;
+                p.order[1] = n42 - n4;
+                p.order[2] = uint32_t(p.n_tiles) - n42;
+                // shares in 1/65536, rounded up so that a single tile counts (any
+                // share is a valid split: the passes only need the same number)
+                const float per = p.n_tiles > 0 ? 65536.0f / float(p.n_tiles) : 0.0f;
+                auto share = [&](uint32_t m) { return m > 0 ? min(uint32_t(float(m) * per) + 1u, 0xffffu) : 0u; };
+                p.order[3] = share(nf) | share(nb) << 16;
+            }
+        }
     }
+    __syncthreads();
+    const uint32_t pairs = p.counters[GS_CTR_PAIRS];
+    int t0, t1;
+    plan_chunk(p, c, t0, t1);
+    for (int t = t0 + int(threadIdx.x); t < t1; t += int(blockDim.x))
+        p.order[4 + plan_slot(cnt, plan_bin(p, pairs, p.ranges[t]))] = uint32_t(t);
 }
 
-__global__ __launch_bounds__(1024) void k_tile_plan(const uint2* __restrict__ ranges,
-                                                    const uint32_t* __restrict__ counters, int n_tiles, int quads,
-                                                    uint32_t* __restrict__ order) {
-    tile_plan(ranges, counters, n_tiles, quads, order, nullptr, 0);
+// the plan of a frame whose lists are all empty
+__global__ __launch_bounds__(1024) void k_tile_plan(Plan p) {
+    __shared__ uint32_t cnt[2 * kPlanBins];
+    plan_count(p, int(blockIdx.x), cnt);
+}
+__global__ __launch_bounds__(1024) void k_tile_plan_place(Plan p) {
+    __shared__ uint32_t cnt[2 * kPlanBins];
+    plan_place(p, int(blockIdx.x), cnt);
 }
 
-// With order set, workgroup 0 makes the compositing plan (tile_plan) and the
-// others sort; the plan only reads the ranges, so it runs beside the sorts.
-template <int ITEMS>
-__global__ __launch_bounds__(kSortBlock) void k_tile_sort(const uint4* __restrict__ meta,
-                                                          const uint2* __restrict__ ranges, int n_tiles,
-                                                          uint32_t* __restrict__ vals, uint32_t* __restrict__ longq,
-                                                          const uint32_t* __restrict__ counters, int quads,
-                                                          uint32_t* __restrict__ order) {
-    constexpr int kSortChunk = kSortBlock * ITEMS;
-    __shared__ uint64_t sk[kSortChunk];
-    const int first = order != nullptr ? 1 : 0;
-    if (int(blockIdx.x) < first) {
-        tile_plan(ranges, counters, n_tiles, quads, order, reinterpret_cast<uint8_t*>(sk), int(sizeof(sk)));
+__device__ inline void wave_lds_order() {    // the wavefront's LDS accesses before against those after
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Bucket of depth bits d for a list whose depths span [lo, lo + range]: linear
+// over the range, monotone in d, below nb.
+struct BucketMap {
+    uint32_t lo, mult;     // mult 0: the range is shorter than the buckets, one value each
+    __device__ BucketMap(uint32_t lo_, uint32_t range, int nb)
+        : lo(lo_), mult(range < uint32_t(nb) ? 0u : uint32_t(float(nb) * 4294967296.0f * 0.9999f / (float(range) + 1.0f))) {}
+    __device__ uint32_t operator()(uint32_t d) const { return mult ? __umulhi(d - lo, mult) : d - lo; }
+};
+
+// place of key k among the keys [s, e) of its bucket
+__device__ __forceinline__ uint32_t bucket_rank(const uint64_t* sk, uint32_t s, uint32_t e, uint64_t k) {
+    uint32_t rank = s;
+    if (e - s > 1)
+        for (uint32_t j = s; j < e; j++) rank += sk[j] < k ? 1u : 0u;
+    return rank;
+}
+
+// one list of 2 .. kWaveMost entries by one wavefront: sk [kWaveMost] and
+// cnt [kWaveMost + 1] are the wavefront's own LDS
+__device__ void wave_sort(const uint4* __restrict__ meta, uint32_t* __restrict__ v, uint32_t n, uint64_t* sk,
+                          uint32_t* cnt) {
+    const uint32_t lane = uint32_t(lane_id());
+    uint32_t r[kWaveItems], d[kWaveItems], rank[kWaveItems];
+#pragma unroll
+    for (int k = 0; k < kWaveItems; k++) {
+        const uint32_t i = lane + uint32_t(k) * kWave;
+        r[k] = i < n ? v[i] : 0u;
+        cnt[i] = 0u;
+    }
+    uint32_t lo = ~0u, hi = 0u;
+#pragma unroll
+    for (int k = 0; k < kWaveItems; k++) {
+        const bool in = lane + uint32_t(k) * kWave < n;
+        d[k] = in ? meta[r[k]].x : 0u;
+        lo = in ? min(lo, d[k]) : lo;
+        hi = in ? max(hi, d[k]) : hi;
+    }
+    lo = wave_min_u32_dpp(lo);
+    hi = wave_max_u32_dpp(hi);
+    const BucketMap bucket(lo, hi - lo, kWaveMost);
+    wave_lds_order();
+#pragma unroll
+    for (int k = 0; k < kWaveItems; k++)
+        if (lane + uint32_t(k) * kWave < n) rank[k] = atomicAdd(&cnt[bucket(d[k])], 1u);
+    wave_lds_order();
+    // lane: buckets 4 lane .. 4 lane + 3
+    uint32_t c[kWaveItems], sum = 0u, most = 0u;
+#pragma unroll
+    for (int k = 0; k < kWaveItems; k++) {
+        c[k] = cnt[kWaveItems * lane + k];
+        sum += c[k];
+        most = max(most, c[k]);
+    }
+    uint32_t run = wave_incl_scan_dpp(sum) - sum;
+    most = wave_max_u32_dpp(most);
+    wave_lds_order();
+#pragma unroll
+    for (int k = 0; k < kWaveItems; k++) {
+        cnt[kWaveItems * lane + k] = run;
+        run += c[k];
+    }
+    if (lane == kWave - 1) cnt[kWaveMost] = run;
+    wave_lds_order();
+#pragma unroll
+    for (int k = 0; k < kWaveItems; k++)
+        if (lane + uint32_t(k) * kWave < n) sk[cnt[bucket(d[k])] + rank[k]] = uint64_t(d[k]) << 32 | r[k];
+    wave_lds_order();
+#pragma unroll
+    for (int k = 0; k < kWaveItems; k++) {
+        const uint32_t i = lane + uint32_t(k) * kWave;
+        if (i >= n) break;
+        const uint64_t key = sk[i];
+        const uint32_t b = bucket(uint32_t(key >> 32));
+        const bool wide = most > kBucketMost;    // uniform: against all keys
+        v[bucket_rank(sk, wide ? 0u : cnt[b], wide ? n : cnt[b + 1], key)] = uint32_t(key);
+    }
+    wave_lds_order();
+}
+
+// one list of 2 .. BLOCK * ITEMS entries by the workgroup: sk [BLOCK * ITEMS],
+// cnt [NB + 1], s_tmp [2 * BLOCK / kWave] (all LDS); ends with a barrier
+template <int BLOCK, int ITEMS, int NB>
+__device__ void block_sort(const uint4* __restrict__ meta, uint32_t* __restrict__ v, uint32_t n, uint64_t* sk,
+                           uint32_t* cnt, uint32_t* s_tmp) {
+    constexpr int NW = BLOCK / kWave, PER = NB / BLOCK;
+    const uint32_t t = threadIdx.x;
+    const int wave = int(t / kWave);
+    uint32_t r[ITEMS], d[ITEMS], rank[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; k++) {
+        const uint32_t i = t + uint32_t(k) * BLOCK;
+        r[k] = i < n ? v[i] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < PER; k++) cnt[t + uint32_t(k) * BLOCK] = 0u;
+    uint32_t lo = ~0u, hi = 0u;
+#pragma unroll
+    for (int k = 0; k < ITEMS; k++) {
+        const bool in = t + uint32_t(k) * BLOCK < n;
+        d[k] = in ? meta[r[k]].x : 0u;
+        lo = in ? min(lo, d[k]) : lo;
+        hi = in ? max(hi, d[k]) : hi;
+    }
+    lo = wave_min_u32_dpp(lo);
+    hi = wave_max_u32_dpp(hi);
+    if (lane_id() == 0) {
+        s_tmp[wave] = lo;
+        s_tmp[NW + wave] = hi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NW; w++) {
+        lo = min(lo, s_tmp[w]);
+        hi = max(hi, s_tmp[NW + w]);
+    }
+    const BucketMap bucket(lo, hi - lo, NB);
+#pragma unroll
+    for (int k = 0; k < ITEMS; k++)
+        if (t + uint32_t(k) * BLOCK < n) rank[k] = atomicAdd(&cnt[bucket(d[k])], 1u);
+    __syncthreads();
+    // thread: buckets PER t .. PER t + PER - 1
+    uint32_t c[PER], sum = 0u, most = 0u;
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+        c[k] = cnt[PER * t + k];
+        sum += c[k];
+        most = max(most, c[k]);
+    }
+    const uint32_t incl = wave_incl_scan_dpp(sum);
+    most = wave_max_u32_dpp(most);
+    if (lane_id() == kWave - 1) {
+        s_tmp[wave] = incl;
+        s_tmp[NW + wave] = most;
+    }
+    __syncthreads();
+    uint32_t run = incl - sum;
+#pragma unroll
+    for (int w = 0; w < NW; w++) {
+        run += w < wave ? s_tmp[w] : 0u;
+        most = max(most, s_tmp[NW + w]);
+    }
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+        cnt[PER * t + k] = run;
+        run += c[k];
+    }
+    if (t == BLOCK - 1) cnt[NB] = run;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ITEMS; k++)
+        if (t + uint32_t(k) * BLOCK < n) sk[cnt[bucket(d[k])] + rank[k]] = uint64_t(d[k]) << 32 | r[k];
+    __syncthreads();
+    if (most > kBucketMost) {          // uniform
+        block_merge_sort<BLOCK, ITEMS>(sk, n);
+        for (uint32_t i = t; i < n; i += BLOCK) v[i] = uint32_t(sk[i]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < ITEMS; k++) {
+            const uint32_t i = t + uint32_t(k) * BLOCK;
+            if (i >= n) break;
+            const uint64_t key = sk[i];
+            const uint32_t b = bucket(uint32_t(key >> 32));
+            v[bucket_rank(sk, cnt[b], cnt[b + 1], key)] = uint32_t(key);
+        }
+    }
+    __syncthreads();
+}
+
+template <int FORM>
+__global__ __launch_bounds__(sort_block(FORM)) void k_tile_sort(const uint4* __restrict__ meta,
+                                                                const uint2* __restrict__ ranges, int n_tiles,
+                                                                uint32_t* __restrict__ vals,
+                                                                uint32_t* __restrict__ longq, Plan plan) {
+    constexpr int BLOCK = sort_block(FORM), CHUNK = sort_chunk(FORM), NB = sort_buckets(FORM), NW = BLOCK / kWave;
+    __shared__ uint64_t sk[CHUNK];
+    __shared__ uint32_t cnt[FORM == kSortWaves ? NW * (kWaveMost + 1) : NB + 1];
+    __shared__ uint32_t s_tmp[2 * NW];
+    static_assert(FORM != kSortWaves || (NW * kWaveMost <= CHUNK && NB < NW * (kWaveMost + 1)),
+                  "the wavefronts' buffers and the workgroup's are the same LDS");
+    const int first = plan.order != nullptr ? plan.blocks : 0;
+    if (int(blockIdx.x) < first) {          // uniform
+        plan_count(plan, int(blockIdx.x), cnt);
         return;
     }
-    const int nsort = int(gridDim.x) - first;
-    for (int tile = int(blockIdx.x) - first; tile < n_tiles; tile += nsort) {
-        const uint2 rg = ranges[tile];
+    const int wg = int(blockIdx.x) - first, wgs = int(gridDim.x) - first;
+    auto take = [&](int tile, uint2 rg) {       // uniform: a list for the whole workgroup
         const uint32_t n = rg.y - rg.x;
-        if (n < 2) continue;                                   // uniform per workgroup
-        if (n > uint32_t(kSortChunk)) {                         // for k_tile_sort_long
+        if (n > uint32_t(CHUNK)) {              // for k_tile_sort_long
             if (threadIdx.x == 0) longq[1 + atomicAdd(&longq[0], 1u)] = uint32_t(tile);
-            continue;
+            return;
         }
-        uint32_t* v = vals + rg.x;
-        if (n <= kSortBlock) {
-            const uint32_t i = threadIdx.x;
-            const uint64_t k = i < n ? depth_key(meta, v[i]) : 0;
-            if (i < n) sk[i] = k;
-            __syncthreads();
-            if (i < n) {
-                uint32_t rank = 0;
-                for (uint32_t j = 0; j < n; j++) rank += sk[j] < k ? 1u : 0u;
-                v[rank] = uint32_t(k);
+        block_sort<BLOCK, kSortItems, NB>(meta, vals + rg.x, n, sk, cnt, s_tmp);
+    };
+    if (FORM == kSortWaves) {
+        const int wave = int(threadIdx.x / kWave);
+        for (int g = wg; g * NW < n_tiles; g += wgs) {
+            const int tile = g * NW + wave;
+            const uint2 rg = tile < n_tiles ? ranges[tile] : make_uint2(0u, 0u);
+            const uint32_t n = rg.y - rg.x;
+            if (n >= 2 && n <= uint32_t(kWaveMost))
+                wave_sort(meta, vals + rg.x, n, sk + wave * kWaveMost, cnt + wave * (kWaveMost + 1));
+            if (__syncthreads_or(n > uint32_t(kWaveMost))) {
+                for (int w = 0; w < NW && g * NW + w < n_tiles; w++) {
+                    const uint2 rw = ranges[g * NW + w];
+                    if (rw.y - rw.x > uint32_t(kWaveMost)) take(g * NW + w, rw);
+                }
             }
-            __syncthreads();
-            continue;
         }
-        for (uint32_t i = threadIdx.x; i < n; i += kSortBlock) sk[i] = depth_key(meta, v[i]);
-        __syncthreads();
-        if (n <= kSortBlock * kSortItemsShort) block_merge_sort<kSortBlock, kSortItemsShort>(sk, n);
-        else block_merge_sort<kSortBlock, ITEMS>(sk, n);
-        for (uint32_t i = threadIdx.x; i < n; i += kSortBlock) v[i] = uint32_t(sk[i]);
-        __syncthreads();
+    } else {
+        for (int tile = wg; tile < n_tiles; tile += wgs) {
+            const uint2 rg = ranges[tile];
+            if (rg.y - rg.x >= 2) take(tile, rg);
+        }
     }
 }
 
 // Lists longer than k_tile_sort takes (queued by it, in any order): one
-// workgroup of kLongBlock threads per list,
-// chunks of kLongChunk keys merge-sorted in LDS, then (lists longer than a
-// chunk) pairwise merges of sorted runs through two scratch ranges (each
-// key's place is its index in its run plus the number of smaller keys in the
-// other run, by binary search).
+// workgroup of kLongBlock threads per list; lists of one chunk of kLongChunk
+// keys by buckets, longer ones as chunks merge-sorted in LDS, then pairwise
+// merges of sorted runs through two scratch ranges (each key's place is its
+// index in its run plus the number of smaller keys in the other run, by
+// binary search).
 __global__ __launch_bounds__(kLongBlock) void k_tile_sort_long(const uint4* __restrict__ meta,
                                                                const uint2* __restrict__ ranges,
                                                                const uint32_t* __restrict__ longq,
                                                                uint32_t* __restrict__ vals, uint64_t* __restrict__ ka,
-                                                               uint64_t* __restrict__ kb) {
+                                                               uint64_t* __restrict__ kb, Plan plan) {
     __shared__ uint64_t sk[kLongChunk];
+    __shared__ uint32_t cnt[kLongChunk / 2 + 1];
+    __shared__ uint32_t s_tmp[2 * kLongBlock / kWave];
+    const uint32_t first = plan.order != nullptr ? uint32_t(plan.blocks) : 0u;
+    if (blockIdx.x < first) {               // uniform
+        plan_place(plan, int(blockIdx.x), cnt);
+        return;
+    }
     const uint32_t nq = longq[0];
-    for (uint32_t q = blockIdx.x; q < nq; q += gridDim.x) {
+    for (uint32_t q = blockIdx.x - first; q < nq; q += gridDim.x - first) {
         const uint2 rg = ranges[longq[1 + q]];
         const uint32_t n = rg.y - rg.x;
         uint32_t* v = vals + rg.x;
+        if (n <= uint32_t(kLongChunk)) {
+            block_sort<kLongBlock, kLongItems, kLongChunk / 2>(meta, v, n, sk, cnt, s_tmp);
+            continue;
+        }
         uint64_t* src = ka + rg.x;
         uint64_t* dst = kb + rg.x;
         for (uint32_t c0 = 0; c0 < n; c0 += kLongChunk) {
@@ -719,14 +997,9 @@ __global__ __launch_bounds__(kLongBlock) void k_tile_sort_long(const uint4* __re
             for (uint32_t i = threadIdx.x; i < m; i += kLongBlock) sk[i] = depth_key(meta, v[c0 + i]);
             __syncthreads();
             block_merge_sort<kLongBlock, kLongItems>(sk, m);
-            if (n <= uint32_t(kLongChunk)) {
-                for (uint32_t i = threadIdx.x; i < m; i += kLongBlock) v[i] = uint32_t(sk[i]);
-            } else {
-                for (uint32_t i = threadIdx.x; i < m; i += kLongBlock) src[c0 + i] = sk[i];
-            }
+            for (uint32_t i = threadIdx.x; i < m; i += kLongBlock) src[c0 + i] = sk[i];
             __syncthreads();
         }
-        if (n <= uint32_t(kLongChunk)) continue;
         for (uint32_t run = kLongChunk; run < n; run <<= 1) {
             for (uint32_t i = threadIdx.x; i < n; i += kLongBlock) {
                 const uint32_t a0 = (i / (2 * run)) * (2 * run), b0 = a0 + run, b1 = min(a0 + 2 * run, n);
@@ -820,16 +1093,16 @@ hipError_t launch_bin_sort(const gs_frame& f, const gs_raster_cfg& cfg, const ui
     const int64_t nt = f.n_tiles;
     const bool want_plan = bins.tile_order && (fwd_waves(cfg) == 0 || bwd_waves(cfg) == 0);
     const int quads = (cfg.tile_w / 8) * (cfg.tile_h / 8);
-    auto plan = [&]() {
-        if (want_plan)
-            GS_LAUNCH("k_tile_plan", k_tile_plan, dim3(1), dim3(1024), 0, s, ranges, bins.counters, f.n_tiles, quads,
-                      bins.tile_order);
-    };
+    const Plan plan{ranges, bins.counters, w.hist, want_plan && nt > 0 ? bins.tile_order : nullptr, f.n_tiles, quads,
+                    plan_blocks(f.n_tiles)};
     if (nrec == 0) {
         GS_LAUNCH("k_counters_empty", k_counters_empty, dim3(1), dim3(64), 0, s, bins.counters);
         GS_LAUNCH("k_fill_u32", k_fill_u32, dim3(unsigned(std::min<int64_t>((2 * nt + 255) / 256, 2048))), dim3(256), 0,
                   s, bins.ranges, 0u, 2 * nt);
-        plan();
+        if (plan.order) {
+            GS_LAUNCH("k_tile_plan", k_tile_plan, dim3(unsigned(plan.blocks)), dim3(1024), 0, s, plan);
+            GS_LAUNCH("k_tile_plan", k_tile_plan_place, dim3(unsigned(plan.blocks)), dim3(1024), 0, s, plan);
+        }
         return hipGetLastError();
     }
 
@@ -871,21 +1144,19 @@ hipError_t launch_bin_sort(const gs_frame& f, const gs_raster_cfg& cfg, const ui
     }
     // 3. per-tile [start, end)
     GS_LAUNCH("k_ranges", k_ranges, dim3(2048), dim3(256), 0, s, tk_final, bins.counters, bins.capacity, ranges);
-    // 4. each tile's list in (depth bits, record) order, and (5.) beside it
+    // 4. each tile's list in (depth bits, record) order, and (5.) beside them
     //    the compositing plan, when a pass splits tiles adaptively
     if (nt > 0) {
-        uint32_t* order = want_plan ? bins.tile_order : nullptr;
-        const dim3 grid(unsigned(std::min<int64_t>(nt, 4096) + (want_plan ? 1 : 0)));
-        if (bins.capacity > uint64_t(nt) * kDenseList)
-            GS_LAUNCH("k_tile_sort", k_tile_sort<kSortItemsDense>, grid, dim3(kSortBlock), 0, s, meta, ranges,
-                      f.n_tiles, bins.vals, w.longq, bins.counters, quads, order);
-        else
-            GS_LAUNCH("k_tile_sort", k_tile_sort<kSortItems>, grid, dim3(kSortBlock), 0, s, meta, ranges, f.n_tiles,
-                      bins.vals, w.longq, bins.counters, quads, order);
-        GS_LAUNCH("k_tile_sort_long", k_tile_sort_long, dim3(unsigned(std::min<int64_t>(nt, 256))), dim3(kLongBlock), 0,
-                  s, meta, ranges, w.longq, bins.vals, w.key[0], w.key[1]);
-    } else {
-        plan();
+        const unsigned plan_wgs = plan.order ? unsigned(plan.blocks) : 0u;
+        auto sort = [&](auto kernel, int form, int64_t lists) {
+            GS_LAUNCH("k_tile_sort", kernel, dim3(plan_wgs + unsigned(std::min<int64_t>(lists, 4096))),
+                      dim3(sort_block(form)), 0, s, meta, ranges, f.n_tiles, bins.vals, w.longq, plan);
+        };
+        if (bins.capacity <= uint64_t(nt) * kWaveList) sort(k_tile_sort<kSortWaves>, kSortWaves, (nt + 3) / 4);
+        else if (bins.capacity <= uint64_t(nt) * kDenseList) sort(k_tile_sort<kSortBlocks>, kSortBlocks, nt);
+        else sort(k_tile_sort<kSortDense>, kSortDense, nt);
+        GS_LAUNCH("k_tile_sort_long", k_tile_sort_long, dim3(plan_wgs + unsigned(std::min<int64_t>(nt, 256))),
+                  dim3(kLongBlock), 0, s, meta, ranges, w.longq, bins.vals, w.key[0], w.key[1], plan);
     }
     return hipGetLastError();
 }

@@ -343,6 +343,36 @@ __device__ inline double wave_sum(double v) {
     return v;
 }
 
+// DPP move of a 32-bit word; lanes without a source (or outside the row mask)
+// read `old`
+template <int CTRL, int ROW_MASK>
+__device__ inline uint32_t dpp_u32(uint32_t old, uint32_t v) {
+    return uint32_t(__builtin_amdgcn_update_dpp(int(old), int(v), CTRL, ROW_MASK, 0xf, false));
+}
+
+// smallest / largest value over the wave (wave-uniform)
+__device__ inline uint32_t wave_min_u32_dpp(uint32_t v) {
+    v = min(v, dpp_u32<0xb1, 0xf>(v, v));     // quad_perm [1,0,3,2]
+    v = min(v, dpp_u32<0x4e, 0xf>(v, v));     // quad_perm [2,3,0,1]
+    v = min(v, dpp_u32<0x124, 0xf>(v, v));    // row_ror:4
+    v = min(v, dpp_u32<0x128, 0xf>(v, v));    // row_ror:8
+    v = min(v, dpp_u32<0x142, 0xa>(v, v));    // row_bcast:15 into rows 1 and 3
+    v = min(v, dpp_u32<0x143, 0xc>(v, v));    // row_bcast:31 into rows 2 and 3
+    return uint32_t(__builtin_amdgcn_readlane(int(v), 63));
+}
+__device__ inline uint32_t wave_max_u32_dpp(uint32_t v) { return ~wave_min_u32_dpp(~v); }
+
+// inclusive prefix sum over the lanes of a wave
+__device__ inline uint32_t wave_incl_scan_dpp(uint32_t v) {
+    v += dpp_u32<0x111, 0xf>(0u, v);          // row_shr:1
+    v += dpp_u32<0x112, 0xf>(0u, v);          // row_shr:2
+    v += dpp_u32<0x114, 0xf>(0u, v);          // row_shr:4
+    v += dpp_u32<0x118, 0xf>(0u, v);          // row_shr:8
+    v += dpp_u32<0x142, 0xa>(0u, v);          // row_bcast:15 into rows 1 and 3
+    v += dpp_u32<0x143, 0xc>(0u, v);          // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
 __device__ inline uint32_t wave_sum_u32(uint32_t v) {
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
     return v;

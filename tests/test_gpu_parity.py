@@ -734,3 +734,38 @@ def test_l1_loss_with_and_without_room_for_its_sum(cfg1, dtype, views):
         np.testing.assert_allclose(loss.cpu().numpy(), ref, rtol=2e-6 if dtype == torch.float32 else 1e-13)
         assert torch.equal(grad, got[0][1])
     assert torch.equal(got[2][0], got[3][0])
+
+
+@pytest.mark.parametrize("form", ["waves", "blocks", "dense"])
+@pytest.mark.parametrize("depths", ["uniform", "equal", "clusters", "octaves", "ulps"])
+def test_bins_bit_exact_list_lengths_and_depths(form, depths):
+    """Tile lists at the edges of the sort's forms (1 .. 64 .. 512 .. 2048 ..
+    4096 entries and beyond; the form follows from the pair capacity per
+    tile), with depths that spread, all coincide, crowd into two buckets,
+    span the exponent range and differ by single bits, on records written
+    here: bins against the reference."""
+    rng = np.random.default_rng(5)
+    lengths = [0, 1, 2, 3, 63, 64, 65, 127, 255, 256, 257, 511, 512, 513, 1025, 2047, 2048, 2049]
+    if form != "waves":
+        lengths += [4095, 4096, 4097, 9000]
+    cam = scenes.look_at([0.0, 0.0, 3.0], [0, 0, 0], 16 * 8, 16 * 5, 100.0, 100.0)
+    cfg = gs.raster_cfg((16, 16, -1))
+    nt = (cam.width // 16) * (cam.height // 16)
+    tiles = rng.permutation(np.repeat(np.arange(len(lengths)), lengths))      # record -> tile
+    n = len(tiles)
+    d = {"uniform": 1.0 + 3.0 * rng.random(n), "equal": np.full(n, 2.5),
+         "clusters": np.where(rng.random(n) < 0.5, 1.0, 4.0) + 1e-6 * rng.random(n),
+         "octaves": 2.0 ** rng.uniform(-2, 120, n), "ulps": np.full(n, 2.0)}[depths].astype(np.float32)
+    bits = d.view(np.uint32).copy()
+    if depths == "ulps":
+        bits += rng.integers(0, 40, n).astype(np.uint32)
+    lo = ((tiles % 8) | ((tiles // 8) << 16)).astype(np.uint32)
+    meta = np.stack([bits, np.ones(n, np.uint32), lo, lo], axis=1)
+    frame = gs.Frame([cam], [gs.JobSpec(0, 0, n, 1.0)], cfg)
+    assert frame.n_tiles == nt
+    per_tile = {"waves": 400, "blocks": 1024, "dense": 1200}[form]
+    assert n <= per_tile * nt
+    buf = gs.Buffers(frame, per_tile * nt)
+    buf.meta.copy_(torch.from_numpy(meta.view(np.int32).reshape(-1)))
+    gs.bin_sort(frame, cfg, buf)
+    _bins_check(frame, buf)
