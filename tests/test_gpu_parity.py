@@ -769,3 +769,32 @@ def test_bins_bit_exact_list_lengths_and_depths(form, depths):
     buf.meta.copy_(torch.from_numpy(meta.view(np.int32).reshape(-1)))
     gs.bin_sort(frame, cfg, buf)
     _bins_check(frame, buf)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("views", [2, 3, 4, 5, 9])
+@pytest.mark.parametrize("n", [1, 63, 64, 129, 700])
+def test_shared_gaussians_backward_adds_the_jobs(dtype, views, n):
+    """Jobs that share Gaussians, over whole and partial overlapping ranges:
+    the gradient equals the sum, in job order, of each job's own (a frame of
+    that job alone), over a buffer of NaN; Gaussians in no job get zero."""
+    p = scenes.gaussians(n, 2, 77, [-1, -1, -1], [1, 1, 1], -2.5, 0.5)
+    params = torch.from_numpy(p).to("cuda", dtype)
+    cfg = gs.raster_cfg((16, 16))
+    cams = [scenes.look_at([3 * math.sin(a), 0.2, 3 * math.cos(a)], [0, 0, 0], 48, 40, 60.0, 60.0)
+            for a in np.linspace(0.1, 5.0, views)]
+    jobs = [gs.JobSpec(k, (k % 3) * (n // 5), n - (k % 2) * (n // 7) - n // 10, 0.5 + k) for k in range(views)]
+    frame = gs.Frame(cams, jobs, cfg)
+    assert not frame.jobs_disjoint
+    dl = torch.randn(3 * frame.n_pixels, generator=torch.Generator().manual_seed(n)).to("cuda", dtype)
+    buf = gs.rasterize(params, frame, cfg)
+    grad = torch.full_like(params, float("nan"))
+    gs.render_bwd(params, frame, cfg, buf, grad, gs.LOSS_EXTERNAL, dl)
+    total = torch.zeros_like(params)
+    for k in range(views):
+        fk = gs.Frame([cams[k]], [gs.JobSpec(0, jobs[k].g0, jobs[k].g1, 1.0)], cfg)
+        bk = gs.rasterize(params, fk, cfg)
+        gk = torch.empty_like(params)
+        gs.render_bwd(params, fk, cfg, bk, gk, gs.LOSS_EXTERNAL, frame.image(dl, k).reshape(-1).contiguous())
+        total += gk
+    assert torch.equal(grad, total)
