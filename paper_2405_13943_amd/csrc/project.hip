@@ -637,11 +637,11 @@ __global__ __launch_bounds__(128) void k_project_bwd_rec(const T* __restrict__ P
 // pass is a chain of dependent loads per record (partials, then the planes),
 // so it is bound by the records in flight: a thread per Gaussian, jobs in
 // turn and every plane read and written again for each, took 195 us for three
-// views of 100k Gaussians (SH 3) and 23 us for four of 2k (SH 0), against
-// ... and ... here.
+// views of 100k Gaussians (SH 3) and 20 us for four of 2k (SH 0), against 52
+// and 7 here.
 constexpr int kAccBlock = 256;
 template <typename T, int D, int JW>
-__global__ __launch_bounds__(kAccBlock) void k_project_bwd_acc(
+__global__ __launch_bounds__(kAccBlock, sizeof(T) == 4 ? 4 : 1) void k_project_bwd_acc(
     const T* __restrict__ P, int64_t stride, int64_t n, gs_frame frame, gs_raster_cfg cfg, const T* __restrict__ rec,
     const uint4* __restrict__ meta, const uint32_t* __restrict__ pair_off, uint64_t capacity,
     const T* __restrict__ pg, T* __restrict__ grad, int64_t gstride, LossSum<T> loss, unsigned loss_blocks) {
@@ -673,8 +673,14 @@ __global__ __launch_bounds__(kAccBlock) void k_project_bwd_acc(
             const T axis = ntiles ? rec[r * GS_REC_WORDS + 9] : T(0);
             T d[9];
             record_partials(pg, m, ntiles ? pair_off[r] : 0u, capacity, d);
+            // the column made opaque: the planes' addresses are the same for
+            // every job, and were formed ahead of the loop and held in some
+            // 110 registers (240 in all, 2 wavefronts per SIMD, 105 us in the
+            // case above; 4 per SIMD and 52 us so)
+            int64_t col = g;
+            asm volatile("" : "+v"(col));
             if (ntiles != 0)
-                record_chain<T, D>(P, stride, g, frame.cams[job.cam], cfg, m.y, d, axis,
+                record_chain<T, D>(P, stride, col, frame.cams[job.cam], cfg, m.y, d, axis,
                                    [&](int a, T v) {
                                        if (a < 11) s_geo[wave][a][lane] = v;
                                    },
