@@ -10,6 +10,7 @@
 #include "gs_device.hpp"
 #include "gs_internal.hpp"
 
+#include <algorithm>
 #include <cmath>
 
 namespace gs {
@@ -112,18 +113,32 @@ hipError_t launch_adam_admm(gs_params& x, const gs_params& g, gs_params& m, gs_p
 }
 
 // ---------------------------------------------------------------------------
-// consensus.  The stream is latency bound unless many loads are in flight, so
-// a workgroup takes 64 consecutive global ids at a time (grid-stride) and
-// each of its wavefronts one chunk of 8 planes of them: a lane holds one
-// global id, issues every load of its chunk before using any, then stores.
+// consensus, a stream over every plane of z, x, u and w.
+//
+// A wavefront takes 256 consecutive global ids, 4 per lane, and a chunk of
+// planes of them.  Lanes whose four ids have the same one or two holders in
+// consecutive columns (ids numbered by holder set do, except where a set
+// ends) move 16 bytes per plane and array, at the columns' own alignment (a
+// word's is enough), and single-held ids read one copy; a lane issues every
+// load of kVecChunk planes before using any.  The other ids are spread over
+// the lanes, one each: a missing second holder reads the first holder's
+// column again and its stores are predicated off, so ids of one and two
+// holders mix without diverging; three or four holders take two half chunks;
+// more take a plain loop.
+//
+// Workgroups walk items of (chunk of planes, run of ids), chunk major, so that
+// what is in flight lies in long runs of a few planes.  With 4-byte accesses
+// and workgroups of 64 ids by all planes, 1.9M ids with 2.1M copies (SH 3,
+// relaxation and residuals) took 686 us (3.6 TB/s); 16-byte accesses 576,
+// chunks of planes side by side 563, chunk major 541 (4.6 TB/s; a large copy
+// reaches 4.8).  A workgroup per item would take 500, but each adds to the ten
+// residual sums, and FP32 sums of 14,600 additions lose digits to the 512's.
+//
 // The kernel is specialised on the SH degree, so the plane count and every
-// plane's attribute group are compile-time constants.  Global ids with one or
-// two holders (every id of a slab partition) share one branch-free path: a
-// missing second holder reads the first holder's column again and its stores
-// are predicated off, so a wavefront mixing the two does not diverge.  Three
-// or four holders take two half chunks; more take a plain loop.
+// plane's attribute group are compile-time constants.
 
-constexpr int kChunk = 8;                 // planes per wavefront
+constexpr int kVecChunk = 4;              // planes whose loads a lane issues together, grouped ids
+constexpr int kChunk = 8;                 // planes per wavefront (spread ids: loads issued together)
 
 __host__ __device__ constexpr int sh_planes(int deg) { return 11 + 3 * (deg + 1) * (deg + 1); }
 
@@ -138,6 +153,68 @@ __device__ __forceinline__ float at(const float* base, uint32_t off) {
 // not read again by it, so they need not take cache lines from the loads
 __device__ __forceinline__ void store_stream(float* base, uint32_t off, float v) {
     __builtin_nontemporal_store(v, reinterpret_cast<float*>(reinterpret_cast<char*>(base) + off));
+}
+
+typedef float f32x4w __attribute__((ext_vector_type(4), aligned(4)));   // 4 columns from any one on
+__device__ __forceinline__ f32x4w at4(const float* base, uint32_t off) {
+    return *reinterpret_cast<const f32x4w*>(reinterpret_cast<const char*>(base) + off);
+}
+__device__ __forceinline__ void store_stream4w(float* base, uint32_t off, f32x4w v) {
+    __builtin_nontemporal_store(v, reinterpret_cast<f32x4w*>(reinterpret_cast<char*>(base) + off));
+}
+
+// Planes [A0, A0 + NP) (clipped to A) of four consecutive global ids (byte
+// offset og) whose NH (1 or 2) holders' copies are four consecutive columns
+// from byte offsets ol[]: the same arithmetic per id as consensus_chunk.
+template <int A, int A0, int NP, int NH, bool RELAX, bool ZP>
+__device__ __forceinline__ void consensus_vec(const float* __restrict__ x, float* __restrict__ u, float* __restrict__ w,
+                                              float* __restrict__ z, int64_t sx, int64_t su, int64_t sw, int64_t sz,
+                                              uint32_t og, const uint32_t (&ol)[NH], float relax, float (&rp)[5],
+                                              float (&rd)[5]) {
+    constexpr int N = (A - A0) < NP ? (A - A0) : NP;
+    f32x4w xv[N][NH], uv[N][NH], zp[N];
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+        const int a = A0 + i;
+        if (ZP) zp[i] = at4(z + a * sz, og);
+#pragma unroll
+        for (int j = 0; j < NH; j++) {
+            xv[i][j] = at4(x + a * sx, ol[j]);
+            uv[i][j] = at4(u + a * su, ol[j]);
+        }
+    }
+    constexpr float cnt = float(NH);
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+        const int a = A0 + i;
+        const int grp = plane_group(a);
+        f32x4w zn, un[NH], wn[NH];
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+            float xh[NH];
+            float acc = 0.f;
+#pragma unroll
+            for (int j = 0; j < NH; j++) {
+                xh[j] = RELAX ? relax * xv[i][j][c] + (1.0f - relax) * zp[i][c] : xv[i][j][c];
+                acc += xh[j];
+            }
+            const float zc = acc / cnt;
+            zn[c] = zc;
+#pragma unroll
+            for (int j = 0; j < NH; j++) {
+                un[j][c] = uv[i][j][c] + xh[j] - zc;
+                wn[j][c] = zc - un[j][c];
+                rp[grp] += (xv[i][j][c] - zc) * (xv[i][j][c] - zc);
+            }
+            if (ZP) rd[grp] += cnt * (zc - zp[i][c]) * (zc - zp[i][c]);
+        }
+        store_stream4w(z + a * sz, og, zn);
+#pragma unroll
+        for (int j = 0; j < NH; j++) {
+            if (NH > 1) store_stream4w(u + a * su, ol[j], un[j]);
+            store_stream4w(w + a * sw, ol[j], wn[j]);
+        }
+    }
 }
 
 // Planes [A0, A0 + NP) (clipped to A) of one global id (byte offset og in the
@@ -268,37 +345,122 @@ __device__ __forceinline__ void residual_flush(const float (&rp)[5], const float
     if (threadIdx.x < 10) {
         float t = 0.f;
         for (int i = 0; i < NW; i++) t += part[i][threadIdx.x];
-        atomicAdd(resid + threadIdx.x, t);
+        if (t != 0.f) atomicAdd(resid + threadIdx.x, t);   // a chunk of planes holds one to three of the groups
     }
 }
 
 __host__ __device__ constexpr int consensus_waves(int deg) { return (sh_planes(deg) + kChunk - 1) / kChunk; }
 
-template <int DEG, bool RELAX, bool RESID>
-__global__ __launch_bounds__(64 * consensus_waves(DEG)) void k_consensus(
+// How a lane's four ids from gid on are taken: 1 or 2 when all have that many
+// holders in consecutive columns, whose first byte offsets are then c0 (and
+// c1); 3 when some exist but not so; 0 past the last id.
+__device__ __forceinline__ int consensus_kind(const int64_t* __restrict__ hptr, const int64_t* __restrict__ hidx,
+                                              int64_t gid, int64_t n_global, uint32_t& c0, uint32_t& c1) {
+    c0 = c1 = 0u;
+    if (gid >= n_global) return 0;
+    if (gid + 4 > n_global) return 3;
+    const int64_t h0 = hptr[gid], nh = hptr[gid + 1] - h0;
+    bool ok = nh == 1 || nh == 2;
+#pragma unroll
+    for (int k = 2; k <= 4; k++) ok = ok && hptr[gid + k] == h0 + nh * k;
+    if (!ok) return 3;
+    const int64_t a = hidx[h0], b = hidx[h0 + nh - 1];
+#pragma unroll
+    for (int k = 1; k < 4; k++) ok = ok && hidx[h0 + nh * k] == a + k && hidx[h0 + nh * k + nh - 1] == b + k;
+    c0 = uint32_t(a) * 4u;
+    c1 = uint32_t(b) * 4u;
+    return ok ? int(nh) : 3;
+}
+
+constexpr int kConsBlock = 256;           // 4 wavefronts: consecutive runs of ids of one chunk of planes
+constexpr int kConsGrid = 512;            // two per CU: all resident
+
+// Up to this many ids a wavefront takes 64, one per lane (WIDE false): the
+// launch is then one trip through its dependent loads (holders, columns,
+// planes), and the wide form's further trips cost more than its accesses
+// save (20k ids, SH 3: 17 against 19 us; 60k, SH 0: 19 against 11).
+constexpr int64_t kConsNarrow = 32768;
+
+template <int DEG, bool RELAX, bool RESID, bool WIDE>
+__global__ __launch_bounds__(kConsBlock) void k_consensus(
     const float* __restrict__ x, float* __restrict__ u, float* __restrict__ w, float* __restrict__ z,
     const int64_t* __restrict__ hptr, const int64_t* __restrict__ hidx, int64_t n_global, int64_t sx, int64_t su,
     int64_t sw, int64_t sz, float relax, float* __restrict__ resid) {
     constexpr int A = sh_planes(DEG);
-    constexpr int NW = consensus_waves(DEG);
+    constexpr int NW = kConsBlock / kWave;
     constexpr bool ZP = RELAX || RESID;
-    const int chunk = threadIdx.x >> 6;     // uniform per wavefront
+    static_assert(2 * kVecChunk == kChunk, "a wavefront's chunk is two grouped chunks");
     float rp[5] = {0, 0, 0, 0, 0}, rd[5] = {0, 0, 0, 0, 0};
-    const int64_t groups = (n_global + 63) >> 6;
-    for (int64_t g = blockIdx.x; g < groups; g += gridDim.x) {
-        const int64_t gid = (g << 6) + lane_id();
-        if (gid >= n_global) continue;
-        const int64_t h0 = hptr[gid], nh = hptr[gid + 1] - h0;
-        if (nh <= 0) continue;
+    // items of four wavefronts' ids and one chunk of planes, chunk major: what
+    // is in flight lies in long runs of a few planes
+    const int64_t runs = WIDE ? (n_global + 1023) >> 10 : (n_global + 255) >> 8;
+    for (int64_t item = blockIdx.x; item < runs * consensus_waves(DEG); item += gridDim.x) {
+        const int chunk = int(item / runs);         // uniform
+        const int64_t g = (item - chunk * runs) * NW + (threadIdx.x >> 6);
 #define GS_CHUNK(C)                                                                                               \
     case C:                                                                                                       \
         consensus_planes<A, C * kChunk, RELAX, ZP>(x, u, w, z, hidx, sx, su, sw, sz, gid, h0, nh, relax, rp, rd); \
         break
+#define GS_CHUNKS(GID)                                       \
+    const int64_t gid = GID;                                 \
+    if (gid >= n_global) continue;                           \
+    const int64_t h0 = hptr[gid], nh = hptr[gid + 1] - h0;   \
+    if (nh <= 0) continue;                                   \
+    switch (chunk) {                                         \
+        GS_CHUNK(0); GS_CHUNK(1); GS_CHUNK(2); GS_CHUNK(3);  \
+        GS_CHUNK(4); GS_CHUNK(5); GS_CHUNK(6); GS_CHUNK(7);  \
+        default: break;                                      \
+    }
+        if constexpr (!WIDE) {
+            GS_CHUNKS((g << 6) + lane_id())
+            continue;
+        }
+        const int64_t gid0 = g << 8;
+        if (gid0 >= n_global) continue;
+        uint32_t c0, c1;
+        const int kind = consensus_kind(hptr, hidx, gid0 + 4 * lane_id(), n_global, c0, c1);
+        const uint32_t og = uint32_t(gid0 + 4 * lane_id()) * 4u;
+#define GS_VEC(C)                                                                                                   \
+    case C:                                                                                                         \
+        if constexpr (C * kChunk < A) {                                                                             \
+            if (kind == 1) {                                                                                        \
+                const uint32_t ol[1] = {c0};                                                                        \
+                consensus_vec<A, C * kChunk, kVecChunk, 1, RELAX, ZP>(x, u, w, z, sx, su, sw, sz, og, ol, relax,    \
+                                                                      rp, rd);                                      \
+                if constexpr (C * kChunk + kVecChunk < A)                                                           \
+                    consensus_vec<A, C * kChunk + kVecChunk, kVecChunk, 1, RELAX, ZP>(x, u, w, z, sx, su, sw, sz,   \
+                                                                                      og, ol, relax, rp, rd);       \
+            }                                                                                                       \
+            if (kind == 2) {                                                                                        \
+                const uint32_t ol[2] = {c0, c1};                                                                    \
+                consensus_vec<A, C * kChunk, kVecChunk, 2, RELAX, ZP>(x, u, w, z, sx, su, sw, sz, og, ol, relax,    \
+                                                                      rp, rd);                                      \
+                if constexpr (C * kChunk + kVecChunk < A)                                                           \
+                    consensus_vec<A, C * kChunk + kVecChunk, kVecChunk, 2, RELAX, ZP>(x, u, w, z, sx, su, sw, sz,   \
+                                                                                      og, ol, relax, rp, rd);       \
+            }                                                                                                       \
+        }                                                                                                           \
+        break
         switch (chunk) {
-            GS_CHUNK(0); GS_CHUNK(1); GS_CHUNK(2); GS_CHUNK(3);
-            GS_CHUNK(4); GS_CHUNK(5); GS_CHUNK(6); GS_CHUNK(7);
+            GS_VEC(0); GS_VEC(1); GS_VEC(2); GS_VEC(3);
+            GS_VEC(4); GS_VEC(5); GS_VEC(6); GS_VEC(7);
             default: break;
         }
+#undef GS_VEC
+        // the rest: sixteen lanes' ids at a time, one per lane
+        uint64_t rest = lane_mask(kind == 3);
+        while (rest) {
+            int from = -1;
+#pragma unroll
+            for (int q = 0; q < 16; q++) {
+                const int src = rest ? __ffsll((long long)rest) - 1 : -1;      // uniform
+                rest &= rest - 1;
+                from = (lane_id() >> 2) == q ? src : from;
+            }
+            if (from < 0) continue;
+            GS_CHUNKS(gid0 + 4 * from + (lane_id() & 3))
+        }
+#undef GS_CHUNKS
 #undef GS_CHUNK
     }
     if (RESID) residual_flush<NW>(rp, rd, resid);
@@ -310,11 +472,19 @@ static void consensus_launch(int64_t G, hipStream_t s, bool rel, float* resid, c
                              float* Z, const int64_t* hptr, const int64_t* hidx, int64_t sx, int64_t su, int64_t sw,
                              int64_t sz, float relax) {
     static_assert(consensus_waves(DEG) <= 8, "one wavefront per chunk of planes");
-    const int64_t groups = (G + 63) / 64;
-    const dim3 grid(unsigned(groups < 2048 ? groups : 2048)), block(64 * consensus_waves(DEG));
-#define GS_CONSENSUS(R, Q)                                                                                     \
-    GS_LAUNCH("k_consensus", (k_consensus<DEG, R, Q>), grid, block, 0, s, X, U, W, Z, hptr, hidx, G, sx, su, sw, \
-              sz, relax, resid)
+    const bool wide = G > kConsNarrow;
+    constexpr int chunks = consensus_waves(DEG);
+    const int64_t runs = wide ? (G + 1023) / 1024 : (G + 255) / 256;     // of a workgroup's four wavefronts
+    const dim3 grid(unsigned(std::min<int64_t>(runs * chunks, kConsGrid))), block(kConsBlock);
+#define GS_CONSENSUS(R, Q)                                                                                       \
+    do {                                                                                                         \
+        if (wide)                                                                                                \
+            GS_LAUNCH("k_consensus", (k_consensus<DEG, R, Q, true>), grid, block, 0, s, X, U, W, Z, hptr, hidx, G, \
+                      sx, su, sw, sz, relax, resid);                                                             \
+        else                                                                                                     \
+            GS_LAUNCH("k_consensus", (k_consensus<DEG, R, Q, false>), grid, block, 0, s, X, U, W, Z, hptr, hidx, \
+                      G, sx, su, sw, sz, relax, resid);                                                          \
+    } while (0)
     if (rel && resid) GS_CONSENSUS(true, true);
     else if (rel) GS_CONSENSUS(true, false);
     else if (resid) GS_CONSENSUS(false, true);
