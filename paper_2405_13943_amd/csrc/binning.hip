@@ -730,7 +730,7 @@ __device__ inline void plan_place(const Plan& p, int c, uint32_t* cnt) {
         p.order[4 + plan_slot(cnt, plan_bin(p, pairs, p.ranges[t]))] = uint32_t(t);
 }
 
-// the plan of a frame whose lists are all empty
+// the plan as launches of its own (frames without the sort's launches)
 __global__ __launch_bounds__(1024) void k_tile_plan(Plan p) {
     __shared__ uint32_t cnt[2 * kPlanBins];
     plan_count(p, int(blockIdx.x), cnt);
@@ -1019,6 +1019,149 @@ __global__ __launch_bounds__(kLongBlock) void k_tile_sort_long(const uint4* __re
 }
 
 // ---------------------------------------------------------------------------
+// small frames: one launch.  Every tile's workgroup reads the metadata of all
+// records, collects those that cover its tile in LDS, sorts them by (depth
+// bits, record) and writes the list; where the list starts needs no other
+// workgroup, because how many pairs lie in earlier tiles follows in closed
+// form from each record's rectangle.  Further workgroups of the launch write
+// the records' first pairs and the counters.  The pipeline above takes 8 to 11
+// launches of 3 to 8 us each for such frames, all of them waiting.
+
+constexpr int kSmallList = 2048, kSmallListWide = 8192;   // most records of a job (and entries of a list) per form
+constexpr int64_t kSmallWork = 32 << 20;                   // most tiles x records
+
+// pairs of a record (rectangle m.z, m.w of tiles) in tiles before (tx, ty)
+__device__ __forceinline__ uint32_t pairs_before(const uint4& m, uint32_t tx, uint32_t ty, bool& inside) {
+    const uint32_t x0 = m.z & 0xffffu, y0 = m.z >> 16, x1 = m.w & 0xffffu, y1 = m.w >> 16;
+    const uint32_t w = x1 - x0 + 1u;
+    inside = tx >= x0 && tx <= x1 && ty >= y0 && ty <= y1;
+    if (ty < y0) return 0u;
+    if (ty > y1) return w * (y1 - y0 + 1u);
+    return w * (ty - y0) + (tx > x0 ? min(tx - x0, w) : 0u);
+}
+
+template <int BLOCK>
+__device__ inline uint32_t block_sum_u32(uint32_t v, uint32_t* s_wave) {
+    v = wave_sum_u32(v);
+    __syncthreads();
+    if (lane_id() == 0) s_wave[threadIdx.x / kWave] = v;
+    __syncthreads();
+    uint32_t t = 0u;
+#pragma unroll
+    for (int w = 0; w < BLOCK / kWave; w++) t += s_wave[w];
+    return t;
+}
+
+template <int BLOCK, int CAP>
+__global__ __launch_bounds__(BLOCK) void k_bin_small(const uint4* __restrict__ meta, gs_frame frame, uint64_t capacity,
+                                                     uint32_t* __restrict__ vals, uint2* __restrict__ ranges,
+                                                     uint32_t* __restrict__ pair_off, uint32_t* __restrict__ counters) {
+    constexpr int ITEMS = CAP / BLOCK;
+    constexpr uint32_t kPrefix = 4 * BLOCK;      // records per prefix workgroup
+    __shared__ uint64_t sk[CAP];
+    __shared__ uint32_t s_wave[2 * BLOCK / kWave];
+    __shared__ uint32_t s_count;
+    const uint32_t nrec = uint32_t(frame.n_records), t = threadIdx.x;
+    if (int(blockIdx.x) >= frame.n_tiles) {
+        // first pairs of records [lo, hi), after the pairs of all records before
+        VisPairs* s_vp = reinterpret_cast<VisPairs*>(s_wave);
+        const uint32_t lo = (blockIdx.x - uint32_t(frame.n_tiles)) * kPrefix, hi = min(nrec, lo + kPrefix);
+        VisPairs acc{};
+        for (uint32_t i = t; i < lo; i += BLOCK) {
+            const uint32_t n = meta_tiles(meta[i].y);
+            acc = scan_add(acc, VisPairs{n > 0 ? 1u : 0u, n});
+        }
+        VisPairs carry;
+        block_excl_scan<BLOCK>(acc, s_vp, carry);
+        for (uint32_t base = lo; base < hi; base += BLOCK) {
+            const uint32_t i = base + t, n = i < hi ? meta_tiles(meta[i].y) : 0u;
+            VisPairs tot;
+            const VisPairs ex = block_excl_scan<BLOCK>(VisPairs{n > 0 ? 1u : 0u, n}, s_vp, tot);
+            if (n > 0) pair_off[i] = scan_add(carry, ex).p;
+            carry = scan_add(carry, tot);
+        }
+        if (hi == nrec && t == 0) RecordScan::finish(carry, counters, capacity);
+        return;
+    }
+    const int tile = int(blockIdx.x);
+    const gs_job& job = frame.jobs[job_of_tile(frame.jobs, frame.n_jobs, tile)];
+    const uint32_t lt = uint32_t(tile - job.tile0);
+    const uint32_t tx = lt % uint32_t(job.tiles_x), ty = lt / uint32_t(job.tiles_x);
+    const uint32_t r0 = uint32_t(job.rec0), r1 = r0 + uint32_t(job.g1 - job.g0);
+    if (t == 0) s_count = 0u;
+    __syncthreads();
+    auto collect = [&](const uint4& m, uint32_t i) {
+        const uint32_t at = atomicAdd(&s_count, 1u);
+        if (at < uint32_t(CAP)) sk[at] = uint64_t(m.x) << 32 | i;     // always: a job has at most CAP records
+    };
+    uint32_t before = 0u, total = 0u;
+    constexpr int kAhead = 4;                    // records loaded before any is used
+    for (uint32_t i0 = t; i0 < nrec; i0 += kAhead * BLOCK) {
+        uint4 m[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; k++) {
+            const uint32_t i = i0 + uint32_t(k) * BLOCK;
+            m[k] = meta[i < nrec ? i : i0];
+        }
+#pragma unroll
+        for (int k = 0; k < kAhead; k++) {
+            const uint32_t i = i0 + uint32_t(k) * BLOCK;
+            const uint32_t n = i < nrec ? meta_tiles(m[k].y) : 0u;
+            if (n == 0u) continue;
+            total += n;
+            if (i < r0) before += n;
+            else if (i < r1) {
+                bool inside;
+                before += pairs_before(m[k], tx, ty, inside);
+                if (inside) collect(m[k], i);
+            }
+        }
+    }
+    total = block_sum_u32<BLOCK>(total, s_wave);
+    before = block_sum_u32<BLOCK>(before, s_wave);      // its barriers: every key is collected
+    if (uint64_t(total) > capacity) {
+        // overflow: only the first `capacity` pairs, in record order, exist
+        __syncthreads();
+        if (t == 0) s_count = 0u;
+        __syncthreads();
+        const uint32_t cap = uint32_t(capacity);
+        uint32_t carry = 0u;
+        before = 0u;
+        for (uint32_t base = 0; base < nrec; base += BLOCK) {
+            const uint32_t i = base + t;
+            const uint4 m = meta[i < nrec ? i : 0u];
+            const uint32_t n = i < nrec ? meta_tiles(m.y) : 0u;
+            uint32_t tot;
+            const uint32_t off = carry + block_excl_scan<BLOCK>(n, s_wave, tot);
+            carry += tot;
+            const uint32_t left = off < cap ? cap - off : 0u;     // of this record's pairs, how many exist
+            if (n > 0u && i < r0) before += min(n, left);
+            else if (n > 0u && i < r1) {
+                bool inside;
+                const uint32_t k = pairs_before(m, tx, ty, inside);
+                before += min(k, left);
+                if (inside && k < left) collect(m, i);
+            }
+        }
+        before = block_sum_u32<BLOCK>(before, s_wave);
+    }
+    const uint32_t n = min(s_count, uint32_t(CAP));
+    if (t == 0) ranges[tile] = n ? make_uint2(before, before + n) : make_uint2(0u, 0u);
+    uint32_t* v = vals + before;
+    if (n <= uint32_t(BLOCK)) {
+        if (t < n) {
+            const uint64_t k = sk[t];
+            uint32_t rank = 0u;
+            for (uint32_t j = 0; j < n; j++) rank += sk[j] < k ? 1u : 0u;
+            v[rank] = uint32_t(k);
+        }
+        return;
+    }
+    block_merge_sort<BLOCK, ITEMS>(sk, n);
+    for (uint32_t i = t; i < n; i += BLOCK) v[i] = uint32_t(sk[i]);
+}
+
+// ---------------------------------------------------------------------------
 
 static int grid_for(uint64_t n_max, int per_block) {
     uint64_t g = (n_max + per_block - 1) / per_block;
@@ -1099,6 +1242,29 @@ hipError_t launch_bin_sort(const gs_frame& f, const gs_raster_cfg& cfg, const ui
         GS_LAUNCH("k_counters_empty", k_counters_empty, dim3(1), dim3(64), 0, s, bins.counters);
         GS_LAUNCH("k_fill_u32", k_fill_u32, dim3(unsigned(std::min<int64_t>((2 * nt + 255) / 256, 2048))), dim3(256), 0,
                   s, bins.ranges, 0u, 2 * nt);
+        if (plan.order) {
+            GS_LAUNCH("k_tile_plan", k_tile_plan, dim3(unsigned(plan.blocks)), dim3(1024), 0, s, plan);
+            GS_LAUNCH("k_tile_plan", k_tile_plan_place, dim3(unsigned(plan.blocks)), dim3(1024), 0, s, plan);
+        }
+        return hipGetLastError();
+    }
+
+    // Frames of few records and tiles: one launch (below it would be 8 to 11),
+    // while a tile's pass over all records costs less than the launches save
+    // (us a call, one launch / the pipeline: 200 records, 16 tiles 3.6 / 28;
+    // 8k, 256 tiles 9 / 36; 8k, 1,024 tiles 10 / 52; 2k, 6,700 tiles 18 / 56;
+    // 24k, 1,425 tiles 37 / 55; but 8k, 6,700 tiles 88 / 59), and a list fits
+    // one workgroup's LDS whatever the records are (a job's are below g_max).
+    if (f.g_max <= kSmallListWide && nt > 0 && nt <= kSmallWork / f.n_records) {
+        const bool wide = f.g_max > kSmallList;
+        const int per = 4 * (wide ? 512 : 256);
+        const dim3 grid(unsigned(nt + (f.n_records + per - 1) / per));
+        if (wide)
+            GS_LAUNCH("k_bin_small", (k_bin_small<512, kSmallListWide>), grid, dim3(512), 0, s, meta, f, bins.capacity,
+                      bins.vals, ranges, bins.pair_off, bins.counters);
+        else
+            GS_LAUNCH("k_bin_small", (k_bin_small<256, kSmallList>), grid, dim3(256), 0, s, meta, f, bins.capacity,
+                      bins.vals, ranges, bins.pair_off, bins.counters);
         if (plan.order) {
             GS_LAUNCH("k_tile_plan", k_tile_plan, dim3(unsigned(plan.blocks)), dim3(1024), 0, s, plan);
             GS_LAUNCH("k_tile_plan", k_tile_plan_place, dim3(unsigned(plan.blocks)), dim3(1024), 0, s, plan);

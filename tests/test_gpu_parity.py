@@ -851,3 +851,64 @@ def test_consensus_runs_of_ids_match_oracle(deg, G):
         rp, rd = oracle.residual_sums(x, rz, zp, ptr, idx, G)
         np.testing.assert_allclose(res[:5], rp, rtol=2e-5, atol=1e-6)
         np.testing.assert_allclose(res[5:], rd, rtol=2e-5, atol=1e-6)
+
+
+@pytest.mark.parametrize("jobs", [1, 3])
+@pytest.mark.parametrize("n", [1, 255, 256, 257, 512, 513, 2047, 2048, 2049, 8192, 8193])
+@pytest.mark.parametrize("room", ["all", "exact", "half", "one"])
+def test_bins_of_small_frames(n, jobs, room):
+    """Frames on both sides of the record counts where one launch makes the
+    bins (2048 and 8192 records a job; more: the pipeline): most records in
+    one tile, the others' rectangles up to the whole image, culled ones among
+    them, depths with ties.  Bins, first pairs and counters against pairs
+    listed here in record order; with fewer pairs of capacity than the frame
+    has, the lists of the first `capacity` pairs, and the overflow is
+    reported and counted."""
+    rng = np.random.default_rng(n + jobs)
+    cams = [scenes.look_at([0.0, 0.0, 3.0], [0, 0, 0], 100 + 30 * k, 70, 100.0, 100.0) for k in range(jobs)]
+    cfg = gs.raster_cfg((16, 16))
+    frame = gs.Frame(cams, [gs.JobSpec(k, 0, n, 1.0) for k in range(jobs)], cfg)
+    meta = np.zeros((frame.n_records, 4), np.uint32)
+    lists, first = [], []
+    for k in range(jobs):
+        j = frame.job(k)
+        x0, y0 = rng.integers(0, j.tiles_x, n), rng.integers(0, j.tiles_y, n)
+        x1 = np.minimum(x0 + rng.integers(0, 3, n), j.tiles_x - 1)
+        y1 = np.minimum(y0 + rng.integers(0, 3, n), j.tiles_y - 1)
+        one = rng.random(n) < 0.8
+        x0[one], x1[one], y0[one], y1[one] = 1, 1, 2, 2
+        x0[n // 2], x1[n // 2], y0[n // 2], y1[n // 2] = 0, j.tiles_x - 1, 0, j.tiles_y - 1
+        m = meta[j.rec0:j.rec0 + n]
+        m[:, 0] = (1.0 + rng.integers(0, 50, n) / 16.0).astype(np.float32).view(np.uint32)
+        m[:, 1] = (x1 - x0 + 1) * (y1 - y0 + 1)
+        m[:, 2], m[:, 3] = x0 | (y0 << 16), x1 | (y1 << 16)
+        culled = rng.random(n) < 0.1
+        culled[n // 2] = False
+        m[culled] = [0xffffffff, 0, 0, 0]
+        for i in range(n):
+            first.append(len(lists))
+            if not culled[i]:
+                lists += [(j.tile0 + y * j.tiles_x + x, int(m[i, 0]), j.rec0 + i)
+                          for y in range(y0[i], y1[i] + 1) for x in range(x0[i], x1[i] + 1)]
+    pairs = len(lists)
+    capacity = {"all": 2 * pairs + 7, "exact": pairs, "half": (pairs + 1) // 2, "one": 1}[room]
+    buf = gs.Buffers(frame, capacity)
+    buf.meta.copy_(torch.from_numpy(meta.view(np.int32).reshape(-1)))
+    buf.ranges.fill_(99)
+    for call in (1, 2):
+        gs.bin_sort(frame, cfg, buf)
+    c = gs.read_counters(buf)
+    over = pairs > buf.capacity
+    assert (c["visible"], c["pairs"]) == (int((meta[:, 1] > 0).sum()), pairs)
+    assert bool(c["status"] & gs.GS_STATUS_PAIR_OVERFLOW) == over and c["overflowed"] == (2 if over else 0)
+    kept = sorted(lists[:buf.capacity])
+    vals = buf.vals.cpu().numpy().view(np.uint32)
+    assert vals[:len(kept)].tolist() == [r for _, _, r in kept]
+    tiles = np.asarray([t for t, _, _ in kept])
+    ranges = np.zeros((frame.n_tiles, 2), np.int64)
+    for t in np.unique(tiles):
+        at = np.nonzero(tiles == t)[0]
+        ranges[t] = at[0], at[-1] + 1
+    np.testing.assert_array_equal(buf.ranges.view(-1, 2).cpu().numpy(), ranges)
+    vis = meta[:, 1] > 0
+    np.testing.assert_array_equal(buf.pair_off.cpu().numpy()[vis], np.asarray(first)[vis])
