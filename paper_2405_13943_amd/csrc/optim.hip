@@ -376,10 +376,11 @@ constexpr int kConsBlock = 256;           // 4 wavefronts: consecutive runs of i
 constexpr int kConsGrid = 512;            // two per CU: all resident
 
 // Up to this many ids a wavefront takes 64, one per lane (WIDE false): the
-// launch is then one trip through its dependent loads (holders, columns,
-// planes), and the wide form's further trips cost more than its accesses
-// save (20k ids, SH 3: 17 against 19 us; 60k, SH 0: 19 against 11).
-constexpr int64_t kConsNarrow = 32768;
+// launch is then one or two trips through its dependent loads (holders,
+// columns, planes), and the wide form's further trips cost more than its
+// accesses save: 45k ids of four blocks, SH 3, 21 us narrow and 24 wide; 130k
+// 42 and 45; 200k 58 and 57; 400k 116 and 114 (1.9M 578 and 541).
+constexpr int64_t kConsNarrow = 131072;
 
 template <int DEG, bool RELAX, bool RESID, bool WIDE>
 __global__ __launch_bounds__(kConsBlock) void k_consensus(

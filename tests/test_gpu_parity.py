@@ -800,57 +800,87 @@ def test_shared_gaussians_backward_adds_the_jobs(dtype, views, n):
     assert torch.equal(grad, total)
 
 
-@pytest.mark.parametrize("G,deg", [(1, 0), (3, 3), (257, 2), (1029, 3), (1029, 1), (32768, 0), (33797, 0)])
-def test_consensus_runs_of_ids_match_oracle(deg, G):
-    """Ids in runs of one holder set with consecutive columns, at every
-    alignment and length (whole lanes of four, runs that end inside a lane,
-    runs whose columns jump, unheld ids, three holders), on both sides of the
-    size where lanes take four ids: z, u, w against the
-    oracle, columns of no holder untouched, and the same bits as the same ids
-    in another order, whose columns are nowhere consecutive."""
-    rng = np.random.default_rng(G + deg)
-    A = 11 + 3 * (deg + 1) ** 2
+def _holder_runs(rng, G):
+    """Holder CSR of G ids in runs of one holder set with consecutive columns:
+    runs of 1 .. 300 ids (inside a lane's four, over several wavefronts), 0 to
+    3 holders, columns that jump between runs.  Returns (ptr, idx, columns)."""
     sets, nxt = [], 0
     while len(sets) < G:
         n = min(int(rng.choice([1, 2, 3, 4, 5, 7, 64, 130, 300])), G - len(sets))
-        nh = int(rng.choice([0, 1, 1, 1, 2, 2, 2, 3]))
         first = []
-        for _ in range(nh):
+        for _ in range(int(rng.choice([0, 1, 1, 1, 2, 2, 2, 3]))):
             nxt += int(rng.integers(0, 3))
             first.append(nxt)
             nxt += n
         sets += [[c + i for c in first] for i in range(n)]
-    L = nxt + 3
     ptr = np.concatenate([[0], np.cumsum([len(h) for h in sets])]).astype(np.int64)
-    idx = np.asarray([c for h in sets for c in h], np.int64)
+    return ptr, np.asarray([c for h in sets for c in h], np.int64), nxt + 3
+
+
+def _consensus(x, u, z, ptr, idx, relax):
+    """gs.consensus on copies; w starts at 7.  Returns u, w, z, residual sums."""
+    t = [torch.from_numpy(v.reshape(-1).copy().reshape(v.shape)).cuda() for v in (x, u, np.full_like(u, 7.0), z)]
+    res = torch.zeros(10, device="cuda")
+    dev = [torch.from_numpy(v.copy() if len(v) else np.zeros(1, np.int64)).cuda() for v in (ptr, idx)]
+    gs.consensus(*t, *dev, relax, res)
+    return [v.cpu().numpy() for v in t[1:]] + [res.cpu().numpy()]
+
+
+@pytest.mark.parametrize("relax", [1.0, 1.6])
+@pytest.mark.parametrize("G,deg", [(1, 0), (3, 3), (257, 2), (1029, 3), (1029, 1)])
+def test_consensus_runs_of_ids_match_oracle(G, deg, relax):
+    """z, u, w and the residual sums against the oracle, columns of no holder
+    and ids of no holder untouched, and the same bits as the same ids in
+    another order."""
+    rng = np.random.default_rng(G + deg)
+    A = 11 + 3 * (deg + 1) ** 2
+    ptr, idx, L = _holder_runs(rng, G)
     x = rng.standard_normal((A, L)).astype(np.float32)
     u = (0.1 * rng.standard_normal((A, L))).astype(np.float32)
     zp = rng.standard_normal((A, G)).astype(np.float32)
-    perm = rng.permutation(G)
-    pptr = np.concatenate([[0], np.cumsum([len(sets[g]) for g in perm])]).astype(np.int64)
-    pidx = np.asarray([c for g in perm for c in sets[g]], np.int64)
     held, hg = np.sort(idx), np.diff(ptr) > 0
-    for relax in (1.0, 1.6):
-        out = []
-        for zz, pp, ii in ((zp, ptr, idx), (zp[:, perm], pptr, pidx)):
-            t = [torch.from_numpy(v.reshape(-1).copy().reshape(v.shape)).cuda() for v in (x, u, np.full_like(u, 7.0), zz)]
-            res = torch.zeros(10, device="cuda")
-            dev = [torch.from_numpy(v if len(v) else np.zeros(1, np.int64)).cuda() for v in (pp, ii)]
-            gs.consensus(*t, *dev, relax, res)
-            out.append([v.cpu().numpy() for v in t[1:]] + [res.cpu().numpy()])
-        gu, gw, gz, res = out[0]
-        assert np.array_equal(gu, out[1][0]) and np.array_equal(gw, out[1][1])
-        assert np.array_equal(gz[:, perm][:, hg[perm]], out[1][2][:, hg[perm]])
-        rz, ru, rw = oracle.consensus(x, u, ptr, idx, G, relax=relax, z_prev=zp)
-        np.testing.assert_allclose(gz[:, hg], rz[:, hg], rtol=1e-6, atol=1e-6)
-        np.testing.assert_allclose(gu[:, held], ru[:, held], rtol=1e-6, atol=1e-6)
-        np.testing.assert_allclose(gw[:, held], rw[:, held], rtol=1e-6, atol=1e-6)
-        free = np.setdiff1d(np.arange(L), held)
-        assert np.array_equal(gu[:, free], u[:, free]) and (gw[:, free] == 7.0).all()
-        assert np.array_equal(gz[:, ~hg], zp[:, ~hg])
-        rp, rd = oracle.residual_sums(x, rz, zp, ptr, idx, G)
-        np.testing.assert_allclose(res[:5], rp, rtol=2e-5, atol=1e-6)
-        np.testing.assert_allclose(res[5:], rd, rtol=2e-5, atol=1e-6)
+    gu, gw, gz, res = _consensus(x, u, zp, ptr, idx, relax)
+    perm = rng.permutation(G)
+    pptr = np.concatenate([[0], np.cumsum(np.diff(ptr)[perm])])
+    pidx = np.concatenate([idx[ptr[g]:ptr[g + 1]] for g in perm])
+    pu, pw, pz, _ = _consensus(x, u, zp[:, perm], pptr, pidx, relax)
+    assert np.array_equal(gu, pu) and np.array_equal(gw, pw)
+    assert np.array_equal(gz[:, perm][:, hg[perm]], pz[:, hg[perm]])
+    rz, ru, rw = oracle.consensus(x, u, ptr, idx, G, relax=relax, z_prev=zp)
+    np.testing.assert_allclose(gz[:, hg], rz[:, hg], rtol=1e-6, atol=1e-6)
+    np.testing.assert_allclose(gu[:, held], ru[:, held], rtol=1e-6, atol=1e-6)
+    np.testing.assert_allclose(gw[:, held], rw[:, held], rtol=1e-6, atol=1e-6)
+    free = np.setdiff1d(np.arange(L), held)
+    assert np.array_equal(gu[:, free], u[:, free]) and (gw[:, free] == 7.0).all()
+    assert np.array_equal(gz[:, ~hg], zp[:, ~hg])
+    rp, rd = oracle.residual_sums(x, rz, zp, ptr, idx, G)
+    np.testing.assert_allclose(res[:5], rp, rtol=2e-5, atol=1e-6)
+    np.testing.assert_allclose(res[5:], rd, rtol=2e-5, atol=1e-6)
+
+
+@pytest.mark.parametrize("relax", [1.0, 1.6])
+@pytest.mark.parametrize("deg", [0, 1, 2, 3])
+def test_consensus_of_many_ids_equals_its_parts(deg, relax):
+    """Past 131,072 ids (lanes of four ids) the bits equal those of two calls
+    on parts of the ids below that (one id per lane), and the residual sums
+    agree to their rounding."""
+    rng = np.random.default_rng(deg)
+    G, A = 131_072 + 1029, 11 + 3 * (deg + 1) ** 2
+    ptr, idx, L = _holder_runs(rng, G)
+    x = rng.standard_normal((A, L), dtype=np.float32)
+    u = 0.1 * rng.standard_normal((A, L), dtype=np.float32)
+    zp = rng.standard_normal((A, G), dtype=np.float32)
+    gu, gw, gz, res = _consensus(x, u, zp, ptr, idx, relax)
+    half, total = 70_001, np.zeros(10)
+    wu, ww, wz = u.copy(), np.full_like(u, 7.0), zp.copy()
+    for a, b in ((0, half), (half, G)):
+        ha, hb = ptr[a], ptr[b]
+        pu, pw, pz, pr = _consensus(x, u, np.ascontiguousarray(zp[:, a:b]), ptr[a:b + 1] - ha, idx[ha:hb], relax)
+        cols = idx[ha:hb]
+        wu[:, cols], ww[:, cols], wz[:, a:b] = pu[:, cols], pw[:, cols], pz
+        total += pr
+    assert np.array_equal(gu, wu) and np.array_equal(gw, ww) and np.array_equal(gz, wz)
+    np.testing.assert_allclose(res, total, rtol=1e-4)
 
 
 @pytest.mark.parametrize("jobs", [1, 3])
