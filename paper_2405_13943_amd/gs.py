@@ -138,33 +138,41 @@ def _check(rc, what):
         raise GsError(f"{what} failed ({rc}): {lib.gs_last_error().decode()}")
 
 
+# The calls below take 10 to 30 us of device time on small inputs, so the
+# marshalling is kept short: handles and addresses go to ctypes as plain
+# integers, and the stream handle comes without a Stream object around it.
 def _stream():
-    return c_vp(torch.cuda.current_stream().cuda_stream)
+    """Handle of the current stream of the current device (0: the default)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t):
-    return c_vp(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def n_attr(sh_degree):
     return 11 + 3 * (sh_degree + 1) ** 2
 
 
+_SH_DEGREE = {n_attr(d): d for d in range(4)}
+
+
 def sh_degree_of(n_planes):
-    d = int(round(((n_planes - 11) / 3) ** 0.5)) - 1
-    if n_attr(d) != n_planes or not 0 <= d <= 3:
+    d = _SH_DEGREE.get(n_planes)
+    if d is None:
         raise ValueError(f"{n_planes} planes do not match an SH degree in 0..3")
     return d
 
 
 def params_struct(t: torch.Tensor, sh_degree=None) -> GsParams:
     """[A][N] plane tensor (rows may be strided) -> gs_params."""
-    if t.dim() != 2 or t.stride(1) != 1:
+    shape, stride = t.shape, t.stride()
+    if len(shape) != 2 or stride[1] != 1:
         raise ValueError("parameter planes must be a [A][N] tensor with unit inner stride")
     if not t.is_cuda:
         raise ValueError("parameter planes must live on the GPU")
-    d = sh_degree_of(t.shape[0]) if sh_degree is None else sh_degree
-    return GsParams(t.data_ptr(), t.shape[1], t.stride(0), d, 0)
+    d = sh_degree_of(shape[0]) if sh_degree is None else sh_degree
+    return GsParams(t.data_ptr(), shape[1], stride[0], d, 0)
 
 
 def raster_cfg(tile=(16, 16), near_z=0.2, alpha_min=1.0 / 255.0, alpha_max=0.99, T_min=1e-4, dilation=0.3,
@@ -291,7 +299,7 @@ class Buffers:
 
 def status_ptr(buf):
     """Device address of a buffer's status word (its counters[CTR_STATUS])."""
-    return c_vp(buf.counters.data_ptr() + 4 * CTR_STATUS)
+    return buf.counters.data_ptr() + 4 * CTR_STATUS
 
 
 def project(params: torch.Tensor, frame: Frame, cfg: GsRasterCfg, buf: Buffers):
