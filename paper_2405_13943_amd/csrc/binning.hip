@@ -482,8 +482,12 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ tke
 //               the launch takes 12 us (19 as a workgroup a list, ranked by
 //               comparison; 17 with 256 to a wavefront, as the workgroups
 //               with longer lists then go round twice).  At a mean of 220
-//               (three served views, capacity 287 a tile) 58 -> 36 us;
-//   kSortBlocks one list per workgroup of 256;
+//               (three served views, 13,660 tiles) 58 -> 36 us;
+//   kSortBlocks one list per workgroup of 256: frames whose longer lists would
+//               hold up a workgroup of waves, when there are too few tiles to
+//               hide it (us, waves / blocks: 1,536 tiles of mean 169 24 / 11,
+//               6,767 of 172 28 / 26, 9,126 of 147 21 / 32, 2,752 of 111
+//               12 / 12, 6,767 of 65 14 / 19); short lists by comparison;
 //   kSortDense  one list per workgroup of 512, up to 4096 on chip.
 // k_tile_sort_long takes the longer lists, one large workgroup each, by
 // merging: every thread sorts E consecutive keys in registers (a sorting
@@ -493,12 +497,15 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ tke
 // and then merging sequentially (ties go to the first run).
 
 constexpr int kSortWaves = 0, kSortBlocks = 1, kSortDense = 2;
-constexpr uint64_t kWaveList = 400;                     // mean list length up to which: kSortWaves
+constexpr uint64_t kWaveList = 150;                     // mean list length up to which: kSortWaves,
+constexpr uint64_t kWaveListMany = 400;                 // and up to which in frames of many tiles
+constexpr int64_t kManyTiles = 8192;
 constexpr uint64_t kDenseList = 1024;                   // and above which: kSortDense
 constexpr int kSortItems = 8;                           // keys per thread: lists up to 2048 (dense: 4096) on chip
 constexpr int kWaveItems = 8;                           // keys per lane of a wavefront's list
 constexpr int kWaveMost = kWaveItems * kWave;           // 512
 constexpr uint32_t kBucketMost = 32;
+constexpr uint32_t kRankMost = 128;                     // a workgroup's lists up to this are ranked by comparison
 constexpr int kLongBlock = 1024;
 constexpr int kLongItems = 8;
 constexpr int kLongChunk = kLongBlock * kLongItems;     // 8192
@@ -914,6 +921,21 @@ __device__ void block_sort(const uint4* __restrict__ meta, uint32_t* __restrict_
     __syncthreads();
 }
 
+// one list of 2 .. kRankMost entries by the workgroup, each key ranked against
+// all: fewer barriers than the buckets; ends with a barrier
+__device__ void block_rank(const uint4* __restrict__ meta, uint32_t* __restrict__ v, uint32_t n, uint64_t* sk) {
+    const uint32_t i = threadIdx.x;
+    const uint64_t k = i < n ? depth_key(meta, v[i]) : 0ull;
+    if (i < n) sk[i] = k;
+    __syncthreads();
+    if (i < n) {
+        uint32_t rank = 0u;
+        for (uint32_t j = 0; j < n; j++) rank += sk[j] < k ? 1u : 0u;
+        v[rank] = uint32_t(k);
+    }
+    __syncthreads();
+}
+
 template <int FORM>
 __global__ __launch_bounds__(sort_block(FORM)) void k_tile_sort(const uint4* __restrict__ meta,
                                                                 const uint2* __restrict__ ranges, int n_tiles,
@@ -937,7 +959,8 @@ __global__ __launch_bounds__(sort_block(FORM)) void k_tile_sort(const uint4* __r
             if (threadIdx.x == 0) longq[1 + atomicAdd(&longq[0], 1u)] = uint32_t(tile);
             return;
         }
-        block_sort<BLOCK, kSortItems, NB>(meta, vals + rg.x, n, sk, cnt, s_tmp);
+        if (n <= kRankMost) block_rank(meta, vals + rg.x, n, sk);
+        else block_sort<BLOCK, kSortItems, NB>(meta, vals + rg.x, n, sk, cnt, s_tmp);
     };
     if (FORM == kSortWaves) {
         const int wave = int(threadIdx.x / kWave);
@@ -1028,7 +1051,7 @@ __global__ __launch_bounds__(kLongBlock) void k_tile_sort_long(const uint4* __re
 // launches of 3 to 8 us each for such frames, all of them waiting.
 
 constexpr int kSmallList = 2048, kSmallListWide = 8192;   // most records of a job (and entries of a list) per form
-constexpr int64_t kSmallWork = 32 << 20;                   // most tiles x records
+constexpr int64_t kSmallWork = 24 << 20;                   // most tiles x records
 
 // pairs of a record (rectangle m.z, m.w of tiles) in tiles before (tx, ty)
 __device__ __forceinline__ uint32_t pairs_before(const uint4& m, uint32_t tx, uint32_t ty, bool& inside) {
@@ -1253,8 +1276,9 @@ hipError_t launch_bin_sort(const gs_frame& f, const gs_raster_cfg& cfg, const ui
     // while a tile's pass over all records costs less than the launches save
     // (us a call, one launch / the pipeline: 200 records, 16 tiles 3.6 / 28;
     // 8k, 256 tiles 9 / 36; 8k, 1,024 tiles 10 / 52; 2k, 6,700 tiles 18 / 56;
-    // 24k, 1,425 tiles 37 / 55; but 8k, 6,700 tiles 88 / 59), and a list fits
-    // one workgroup's LDS whatever the records are (a job's are below g_max).
+    // 8k, 2,400 tiles 36 / 57; 5k, 6,161 tiles 49 / 50; 8k, 6,700 tiles
+    // 88 / 59), and a list fits one workgroup's LDS whatever the records are
+    // (a job's are below g_max).
     if (f.g_max <= kSmallListWide && nt > 0 && nt <= kSmallWork / f.n_records) {
         const bool wide = f.g_max > kSmallList;
         const int per = 4 * (wide ? 512 : 256);
@@ -1318,7 +1342,7 @@ hipError_t launch_bin_sort(const gs_frame& f, const gs_raster_cfg& cfg, const ui
             GS_LAUNCH("k_tile_sort", kernel, dim3(plan_wgs + unsigned(std::min<int64_t>(lists, 4096))),
                       dim3(sort_block(form)), 0, s, meta, ranges, f.n_tiles, bins.vals, w.longq, plan);
         };
-        if (bins.capacity <= uint64_t(nt) * kWaveList) sort(k_tile_sort<kSortWaves>, kSortWaves, (nt + 3) / 4);
+        if (bins.capacity <= uint64_t(nt) * (nt >= kManyTiles ? kWaveListMany : kWaveList)) sort(k_tile_sort<kSortWaves>, kSortWaves, (nt + 3) / 4);
         else if (bins.capacity <= uint64_t(nt) * kDenseList) sort(k_tile_sort<kSortBlocks>, kSortBlocks, nt);
         else sort(k_tile_sort<kSortDense>, kSortDense, nt);
         GS_LAUNCH("k_tile_sort_long", k_tile_sort_long, dim3(plan_wgs + unsigned(std::min<int64_t>(nt, 256))),
