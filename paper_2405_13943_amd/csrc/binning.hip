@@ -13,6 +13,9 @@
 //   4. sort each tile's list by the unique key (depth bits, record) on chip
 //      (positive floats order like their bits).
 //
+// Frames of few records take one launch (k_bin_small), of somewhat more two
+// (k_bin_strips, k_bin_tiles) in place of steps 1 to 4.
+//
 // Every count that depends on the data (visible records V, pairs P) stays on
 // the device: kernels read it from the counters and size their loops from
 // it, so the whole chain runs without a host round trip.
@@ -1051,16 +1054,17 @@ __global__ __launch_bounds__(kLongBlock) void k_tile_sort_long(const uint4* __re
 // launches of 3 to 8 us each for such frames, all of them waiting.
 
 constexpr int kSmallList = 2048, kSmallListWide = 8192;   // most records of a job (and entries of a list) per form
-constexpr int64_t kSmallWork = 24 << 20;                   // most tiles x records
+constexpr int64_t kSmallWork = 12 << 20, kSmallWorkWide = 4 << 20;     // most tiles x records
 
-// pairs of a record (rectangle m.z, m.w of tiles) in tiles before (tx, ty)
-__device__ __forceinline__ uint32_t pairs_before(const uint4& m, uint32_t tx, uint32_t ty, bool& inside) {
+// pairs of a record (rectangle m.z, m.w of tiles) in tiles before (c0, ty);
+// inside: it has some in tiles c0 to c1 of row ty
+__device__ __forceinline__ uint32_t pairs_before(const uint4& m, uint32_t c0, uint32_t c1, uint32_t ty, bool& inside) {
     const uint32_t x0 = m.z & 0xffffu, y0 = m.z >> 16, x1 = m.w & 0xffffu, y1 = m.w >> 16;
     const uint32_t w = x1 - x0 + 1u;
-    inside = tx >= x0 && tx <= x1 && ty >= y0 && ty <= y1;
+    inside = c1 >= x0 && c0 <= x1 && ty >= y0 && ty <= y1;
     if (ty < y0) return 0u;
     if (ty > y1) return w * (y1 - y0 + 1u);
-    return w * (ty - y0) + (tx > x0 ? min(tx - x0, w) : 0u);
+    return w * (ty - y0) + (c0 > x0 ? min(c0 - x0, w) : 0u);
 }
 
 template <int BLOCK>
@@ -1075,35 +1079,101 @@ __device__ inline uint32_t block_sum_u32(uint32_t v, uint32_t* s_wave) {
     return t;
 }
 
+// one workgroup: first pairs of records [4 BLOCK b, 4 BLOCK (b + 1)), after the
+// pairs of all records before; the last one also the counters.  s_vp: BLOCK /
+// kWave values of LDS
+template <int BLOCK>
+__device__ inline void write_first_pairs(const uint4* __restrict__ meta, uint32_t nrec, uint32_t b, uint64_t capacity,
+                                         uint32_t* __restrict__ pair_off, uint32_t* __restrict__ counters,
+                                         VisPairs* s_vp) {
+    const uint32_t t = threadIdx.x, lo = b * 4u * BLOCK, hi = min(nrec, lo + 4u * BLOCK);
+    constexpr int kAhead = 8;                    // records loaded before any is used
+    VisPairs acc{};
+    for (uint32_t i0 = t; i0 < lo; i0 += kAhead * BLOCK) {
+        uint32_t y[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; k++) y[k] = meta[i0 + (i0 + uint32_t(k) * BLOCK < lo ? uint32_t(k) * BLOCK : 0u)].y;
+#pragma unroll
+        for (int k = 0; k < kAhead; k++) {
+            const uint32_t n = i0 + uint32_t(k) * BLOCK < lo ? meta_tiles(y[k]) : 0u;
+            acc = scan_add(acc, VisPairs{n > 0 ? 1u : 0u, n});
+        }
+    }
+    VisPairs carry, tot, four{};
+    block_excl_scan<BLOCK>(acc, s_vp, carry);
+    const uint32_t i0 = lo + 4u * t;             // a thread's four records
+    uint32_t n[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4; k++) {
+        n[k] = i0 + k < hi ? meta_tiles(meta[i0 + k].y) : 0u;
+        four = scan_add(four, VisPairs{n[k] > 0 ? 1u : 0u, n[k]});
+    }
+    uint32_t at = scan_add(carry, block_excl_scan<BLOCK>(four, s_vp, tot)).p;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; k++) {
+        if (n[k] > 0) pair_off[i0 + k] = at;
+        at += n[k];
+    }
+    carry = scan_add(carry, tot);
+    if (hi == nrec && t == 0) RecordScan::finish(carry, counters, capacity);
+}
+
+// A frame with more pairs than capacity: only the first `capacity`, in record
+// order, exist.  One workgroup: collect(m, i) for each of them in tile (tx, ty)
+// of the job of records [r0, r1); returns how many lie in tiles before.
+template <int BLOCK, typename Collect>
+__device__ inline uint32_t collect_truncated(const uint4* __restrict__ meta, uint32_t nrec, uint32_t r0, uint32_t r1,
+                                             uint32_t tx, uint32_t ty, uint64_t capacity, uint32_t* s_wave,
+                                             Collect collect) {
+    const uint32_t cap = uint32_t(capacity);
+    uint32_t carry = 0u, before = 0u;
+    for (uint32_t base = 0; base < nrec && carry < cap; base += BLOCK) {
+        const uint32_t i = base + threadIdx.x;
+        const uint4 m = meta[i < nrec ? i : 0u];
+        const uint32_t n = i < nrec ? meta_tiles(m.y) : 0u;
+        uint32_t tot;
+        const uint32_t off = carry + block_excl_scan<BLOCK>(n, s_wave, tot);
+        carry += tot;
+        const uint32_t left = off < cap ? cap - off : 0u;     // of this record's pairs, how many exist
+        if (n > 0u && i < r0) before += min(n, left);
+        else if (n > 0u && i < r1) {
+            bool inside;
+            const uint32_t k = pairs_before(m, tx, tx, ty, inside);
+            before += min(k, left);
+            if (inside && k < left) collect(m, i);
+        }
+    }
+    return block_sum_u32<BLOCK>(before, s_wave);
+}
+
+// one workgroup: the n <= CAP keys collected in sk, ordered, to v
+template <int BLOCK, int CAP>
+__device__ inline void write_sorted(uint64_t* sk, uint32_t n, uint32_t* __restrict__ v) {
+    const uint32_t t = threadIdx.x;
+    if (n <= uint32_t(BLOCK)) {
+        if (t < n) {
+            const uint64_t k = sk[t];
+            uint32_t rank = 0u;
+            for (uint32_t j = 0; j < n; j++) rank += sk[j] < k ? 1u : 0u;
+            v[rank] = uint32_t(k);
+        }
+        return;
+    }
+    block_merge_sort<BLOCK, CAP / BLOCK>(sk, n);
+    for (uint32_t i = t; i < n; i += BLOCK) v[i] = uint32_t(sk[i]);
+}
+
 template <int BLOCK, int CAP>
 __global__ __launch_bounds__(BLOCK) void k_bin_small(const uint4* __restrict__ meta, gs_frame frame, uint64_t capacity,
                                                      uint32_t* __restrict__ vals, uint2* __restrict__ ranges,
                                                      uint32_t* __restrict__ pair_off, uint32_t* __restrict__ counters) {
-    constexpr int ITEMS = CAP / BLOCK;
-    constexpr uint32_t kPrefix = 4 * BLOCK;      // records per prefix workgroup
     __shared__ uint64_t sk[CAP];
     __shared__ uint32_t s_wave[2 * BLOCK / kWave];
     __shared__ uint32_t s_count;
     const uint32_t nrec = uint32_t(frame.n_records), t = threadIdx.x;
     if (int(blockIdx.x) >= frame.n_tiles) {
-        // first pairs of records [lo, hi), after the pairs of all records before
-        VisPairs* s_vp = reinterpret_cast<VisPairs*>(s_wave);
-        const uint32_t lo = (blockIdx.x - uint32_t(frame.n_tiles)) * kPrefix, hi = min(nrec, lo + kPrefix);
-        VisPairs acc{};
-        for (uint32_t i = t; i < lo; i += BLOCK) {
-            const uint32_t n = meta_tiles(meta[i].y);
-            acc = scan_add(acc, VisPairs{n > 0 ? 1u : 0u, n});
-        }
-        VisPairs carry;
-        block_excl_scan<BLOCK>(acc, s_vp, carry);
-        for (uint32_t base = lo; base < hi; base += BLOCK) {
-            const uint32_t i = base + t, n = i < hi ? meta_tiles(meta[i].y) : 0u;
-            VisPairs tot;
-            const VisPairs ex = block_excl_scan<BLOCK>(VisPairs{n > 0 ? 1u : 0u, n}, s_vp, tot);
-            if (n > 0) pair_off[i] = scan_add(carry, ex).p;
-            carry = scan_add(carry, tot);
-        }
-        if (hi == nrec && t == 0) RecordScan::finish(carry, counters, capacity);
+        write_first_pairs<BLOCK>(meta, nrec, blockIdx.x - uint32_t(frame.n_tiles), capacity, pair_off, counters,
+                                 reinterpret_cast<VisPairs*>(s_wave));
         return;
     }
     const int tile = int(blockIdx.x);
@@ -1135,7 +1205,7 @@ __global__ __launch_bounds__(BLOCK) void k_bin_small(const uint4* __restrict__ m
             if (i < r0) before += n;
             else if (i < r1) {
                 bool inside;
-                before += pairs_before(m[k], tx, ty, inside);
+                before += pairs_before(m[k], tx, tx, ty, inside);
                 if (inside) collect(m[k], i);
             }
         }
@@ -1143,45 +1213,194 @@ __global__ __launch_bounds__(BLOCK) void k_bin_small(const uint4* __restrict__ m
     total = block_sum_u32<BLOCK>(total, s_wave);
     before = block_sum_u32<BLOCK>(before, s_wave);      // its barriers: every key is collected
     if (uint64_t(total) > capacity) {
-        // overflow: only the first `capacity` pairs, in record order, exist
         __syncthreads();
         if (t == 0) s_count = 0u;
         __syncthreads();
-        const uint32_t cap = uint32_t(capacity);
-        uint32_t carry = 0u;
-        before = 0u;
-        for (uint32_t base = 0; base < nrec; base += BLOCK) {
-            const uint32_t i = base + t;
-            const uint4 m = meta[i < nrec ? i : 0u];
-            const uint32_t n = i < nrec ? meta_tiles(m.y) : 0u;
-            uint32_t tot;
-            const uint32_t off = carry + block_excl_scan<BLOCK>(n, s_wave, tot);
-            carry += tot;
-            const uint32_t left = off < cap ? cap - off : 0u;     // of this record's pairs, how many exist
-            if (n > 0u && i < r0) before += min(n, left);
-            else if (n > 0u && i < r1) {
-                bool inside;
-                const uint32_t k = pairs_before(m, tx, ty, inside);
-                before += min(k, left);
-                if (inside && k < left) collect(m, i);
-            }
-        }
-        before = block_sum_u32<BLOCK>(before, s_wave);
+        before = collect_truncated<BLOCK>(meta, nrec, r0, r1, tx, ty, capacity, s_wave, collect);
     }
     const uint32_t n = min(s_count, uint32_t(CAP));
     if (t == 0) ranges[tile] = n ? make_uint2(before, before + n) : make_uint2(0u, 0u);
-    uint32_t* v = vals + before;
-    if (n <= uint32_t(BLOCK)) {
-        if (t < n) {
-            const uint64_t k = sk[t];
-            uint32_t rank = 0u;
-            for (uint32_t j = 0; j < n; j++) rank += sk[j] < k ? 1u : 0u;
-            v[rank] = uint32_t(k);
-        }
+    write_sorted<BLOCK, CAP>(sk, n, vals + before);
+}
+
+// Frames of somewhat more records: the same in two launches.  k_bin_strips: a
+// workgroup reads all records for a strip (`wide` tiles of one row) and leaves
+// those that meet it (key and columns) in a list that starts where the strip's
+// pairs will, in closed form again; the list is no longer than they are.
+// k_bin_tiles: each tile's workgroup reads its strip's list instead of all
+// records; a list too long for its LDS is left for k_tile_sort_long.  All of
+// it waits on loads and launches; strips are cut so that a little less than
+// one workgroup a CU reads the records (a frame of 20k records, 1,900 tiles:
+// 39 us with 512 strips, 33 with 192 or 128; 65k, 6,700 tiles: 112, 92, 96).
+// All bins of the first took 53 us in the pipeline's 11 launches, 33 here in 4.
+constexpr int kStripBlock = 1024, kStripHold = 4096;        // threads; longest list collected in LDS
+constexpr int64_t kStrips = 192;                            // about as many strips
+constexpr int64_t kStripRecords = 65536, kStripTiles = 32768;   // most records and tiles
+static_assert(kStripRecords * kStripTiles < (int64_t(1) << 32), "sums of pairs fit 32 bits");
+
+struct StripInfo {
+    uint32_t first, count;      // the list, and pairs in earlier tiles
+    uint32_t overflow;          // the frame has more pairs than capacity: no lists
+    uint32_t reserved;
+};
+
+// a record's columns in the strip [c0, c1]: first (below kStripTiles) and how many
+__device__ __forceinline__ uint32_t strip_columns(const uint4& m, uint32_t c0, uint32_t c1) {
+    const uint32_t x0 = max(m.z & 0xffffu, c0), x1 = min(m.w & 0xffffu, c1);
+    return x0 | (x1 - x0 + 1u) << 16;
+}
+
+__global__ __launch_bounds__(kStripBlock, 8) void k_bin_strips(const uint4* __restrict__ meta, gs_frame frame,
+                                                            uint64_t capacity, uint64_t* __restrict__ key,
+                                                            uint32_t* __restrict__ cols, StripInfo* __restrict__ info,
+                                                            int wide, int strip_wgs, uint32_t* __restrict__ longq,
+                                                            uint32_t* __restrict__ pair_off,
+                                                            uint32_t* __restrict__ counters) {
+    __shared__ uint64_t s_key[kStripHold];
+    __shared__ uint32_t s_cols[kStripHold];
+    __shared__ uint32_t s_wave[2 * kStripBlock / kWave];
+    __shared__ uint32_t s_count;
+    const uint32_t nrec = uint32_t(frame.n_records), t = threadIdx.x;
+    if (int(blockIdx.x) >= strip_wgs) {
+        if (int(blockIdx.x) == strip_wgs && t == 0) *longq = 0u;
+        write_first_pairs<kStripBlock>(meta, nrec, blockIdx.x - uint32_t(strip_wgs), capacity, pair_off, counters,
+                                       reinterpret_cast<VisPairs*>(s_wave));
         return;
     }
-    block_merge_sort<BLOCK, ITEMS>(sk, n);
-    for (uint32_t i = t; i < n; i += BLOCK) v[i] = uint32_t(sk[i]);
+    int strip = int(blockIdx.x);                // the jobs' strips one after the other
+    for (int j = 0; j < frame.n_jobs; j++) {
+        const gs_job& job = frame.jobs[j];
+        const int per_row = (job.tiles_x + wide - 1) / wide;
+        const uint32_t r0 = uint32_t(job.rec0), r1 = r0 + uint32_t(job.g1 - job.g0);
+        for (; strip < job.tiles_y * per_row; strip += strip_wgs) {
+            const uint32_t ty = uint32_t(strip / per_row), c0 = uint32_t(strip % per_row * wide);
+            const uint32_t c1 = min(c0 + uint32_t(wide), uint32_t(job.tiles_x)) - 1u;
+            uint32_t before = 0u, total = 0u;
+            __syncthreads();
+            if (t == 0) s_count = 0u;
+            __syncthreads();
+            constexpr int kAhead = 4;
+            for (uint32_t i0 = t; i0 < nrec; i0 += kAhead * kStripBlock) {
+                uint4 m[kAhead];
+#pragma unroll
+                for (int k = 0; k < kAhead; k++) {
+                    const uint32_t i = i0 + uint32_t(k) * kStripBlock;
+                    m[k] = meta[i < nrec ? i : i0];
+                }
+#pragma unroll
+                for (int k = 0; k < kAhead; k++) {
+                    const uint32_t i = i0 + uint32_t(k) * kStripBlock;
+                    const uint32_t n = i < nrec ? meta_tiles(m[k].y) : 0u;
+                    if (n == 0u) continue;
+                    total += n;
+                    if (i < r0) before += n;
+                    else if (i < r1) {
+                        bool inside;
+                        before += pairs_before(m[k], c0, c1, ty, inside);
+                        if (inside) {
+                            const uint32_t at = atomicAdd(&s_count, 1u);
+                            if (at < uint32_t(kStripHold)) {
+                                s_key[at] = uint64_t(m[k].x) << 32 | i;
+                                s_cols[at] = strip_columns(m[k], c0, c1);
+                            }
+                        }
+                    }
+                }
+            }
+            total = block_sum_u32<kStripBlock>(total, s_wave);
+            before = block_sum_u32<kStripBlock>(before, s_wave);    // its barriers: every record is collected
+            const uint32_t count = s_count;
+            const bool overflow = uint64_t(total) > capacity;       // uniform
+            if (!overflow && count <= uint32_t(kStripHold)) {
+                for (uint32_t i = t; i < count; i += kStripBlock) {
+                    key[before + i] = s_key[i];
+                    cols[before + i] = s_cols[i];
+                }
+            } else if (!overflow) {                                 // longer than the LDS holds: another pass
+                __syncthreads();
+                if (t == 0) s_count = 0u;
+                __syncthreads();
+                for (uint32_t i = r0 + t; i < r1; i += kStripBlock) {
+                    const uint4 m = meta[i];
+                    bool inside = false;
+                    if (meta_tiles(m.y) > 0u) pairs_before(m, c0, c1, ty, inside);
+                    if (inside) {
+                        const uint32_t at = before + atomicAdd(&s_count, 1u);
+                        key[at] = uint64_t(m.x) << 32 | i;
+                        cols[at] = strip_columns(m, c0, c1);
+                    }
+                }
+            }
+            if (t == 0) info[job.tile0 + int(ty) * job.tiles_x + int(c0)] = {before, count, overflow ? 1u : 0u, 0u};
+        }
+        strip -= job.tiles_y * per_row;
+    }
+}
+
+constexpr int kBinTileBlock = 256, kBinTileList = 2048;
+__global__ __launch_bounds__(kBinTileBlock) void k_bin_tiles(const uint4* __restrict__ meta, gs_frame frame,
+                                                             uint64_t capacity, const uint64_t* __restrict__ key,
+                                                             const uint32_t* __restrict__ cols,
+                                                             const StripInfo* __restrict__ info, int wide,
+                                                             uint32_t* __restrict__ vals, uint2* __restrict__ ranges,
+                                                             uint32_t* __restrict__ longq) {
+    constexpr int BLOCK = kBinTileBlock, CAP = kBinTileList;
+    __shared__ uint64_t sk[CAP];
+    __shared__ uint32_t s_wave[2 * BLOCK / kWave];
+    __shared__ uint32_t s_count;
+    const uint32_t t = threadIdx.x;
+    const int tile = int(blockIdx.x);
+    const gs_job& job = frame.jobs[job_of_tile(frame.jobs, frame.n_jobs, tile)];
+    const uint32_t lt = uint32_t(tile - job.tile0);
+    const uint32_t tx = lt % uint32_t(job.tiles_x), ty = lt / uint32_t(job.tiles_x);
+    const StripInfo strip = info[tile - int(tx) % wide];
+    uint32_t before = 0u, n = 0u;
+    for (int pass = 0; pass < 2; pass++) {
+        // keys to LDS; a list too long for it goes to vals unsorted in a second pass
+        if (t == 0) s_count = 0u;
+        __syncthreads();
+        auto put = [&](uint64_t k) {
+            const uint32_t at = atomicAdd(&s_count, 1u);
+            if (pass) vals[before + at] = uint32_t(k);
+            else if (at < uint32_t(CAP)) sk[at] = k;
+        };
+        if (strip.overflow) {                             // uniform
+            const uint32_t r0 = uint32_t(job.rec0);
+            const uint32_t b = collect_truncated<BLOCK>(
+                meta, uint32_t(frame.n_records), r0, r0 + uint32_t(job.g1 - job.g0), tx, ty, capacity, s_wave,
+                [&](const uint4& m, uint32_t i) { put(uint64_t(m.x) << 32 | i); });
+            if (pass == 0) before = b;
+        } else {
+            uint32_t left = 0u;
+            constexpr int kAhead = 4;
+            for (uint32_t i0 = t; i0 < strip.count; i0 += kAhead * BLOCK) {
+                uint32_t c[kAhead];
+#pragma unroll
+                for (int k = 0; k < kAhead; k++) {
+                    const uint32_t i = i0 + uint32_t(k) * BLOCK;
+                    c[k] = cols[strip.first + (i < strip.count ? i : i0)];
+                }
+#pragma unroll
+                for (int k = 0; k < kAhead; k++) {
+                    const uint32_t i = i0 + uint32_t(k) * BLOCK, x0 = c[k] & 0xffffu, w = c[k] >> 16;
+                    if (i >= strip.count) continue;
+                    if (tx > x0) left += min(tx - x0, w);
+                    if (tx - x0 < w) put(key[strip.first + i]);        // wraps below x0
+                }
+            }
+            if (pass == 0) before = strip.first + block_sum_u32<BLOCK>(left, s_wave);
+        }
+        __syncthreads();
+        if (pass) break;
+        n = s_count;
+        if (t == 0) ranges[tile] = n ? make_uint2(before, before + n) : make_uint2(0u, 0u);
+        if (n <= uint32_t(CAP)) {                       // uniform
+            write_sorted<BLOCK, CAP>(sk, n, vals + before);
+            return;
+        }
+        __syncthreads();
+    }
+    if (t == 0) longq[1 + atomicAdd(&longq[0], 1u)] = uint32_t(tile);
 }
 
 // ---------------------------------------------------------------------------
@@ -1272,15 +1491,15 @@ hipError_t launch_bin_sort(const gs_frame& f, const gs_raster_cfg& cfg, const ui
         return hipGetLastError();
     }
 
-    // Frames of few records and tiles: one launch (below it would be 8 to 11),
-    // while a tile's pass over all records costs less than the launches save
-    // (us a call, one launch / the pipeline: 200 records, 16 tiles 3.6 / 28;
-    // 8k, 256 tiles 9 / 36; 8k, 1,024 tiles 10 / 52; 2k, 6,700 tiles 18 / 56;
-    // 8k, 2,400 tiles 36 / 57; 5k, 6,161 tiles 49 / 50; 8k, 6,700 tiles
-    // 88 / 59), and a list fits one workgroup's LDS whatever the records are
-    // (a job's are below g_max).
-    if (f.g_max <= kSmallListWide && nt > 0 && nt <= kSmallWork / f.n_records) {
-        const bool wide = f.g_max > kSmallList;
+    // Frames of few records and tiles: one launch, while a tile's pass over all
+    // records costs less than the launches save, and a list fits one
+    // workgroup's LDS whatever the records are (a job's are below g_max).  Us
+    // a call with the plan, one launch / by strips: 200 records, 16 tiles
+    // 8.9 / 15.5; 2k, 1,200 tiles 12.5 / 18.2; 2k, 3,072 tiles 16.8 / 20.8;
+    // 2k, 6,700 tiles 24.5 / 24.9; the wide form 8k, 475 tiles 16.0 / 22.4;
+    // 5k, 1,200 tiles 22.2 / 20.4; 8k, 1,900 tiles 35.8 / 23.4.
+    const bool wide = f.g_max > kSmallList;
+    if (f.g_max <= kSmallListWide && nt > 0 && nt <= (wide ? kSmallWorkWide : kSmallWork) / f.n_records) {
         const int per = 4 * (wide ? 512 : 256);
         const dim3 grid(unsigned(nt + (f.n_records + per - 1) / per));
         if (wide)
@@ -1293,6 +1512,35 @@ hipError_t launch_bin_sort(const gs_frame& f, const gs_raster_cfg& cfg, const ui
             GS_LAUNCH("k_tile_plan", k_tile_plan, dim3(unsigned(plan.blocks)), dim3(1024), 0, s, plan);
             GS_LAUNCH("k_tile_plan", k_tile_plan_place, dim3(unsigned(plan.blocks)), dim3(1024), 0, s, plan);
         }
+        return hipGetLastError();
+    }
+
+    // workgroups for the lists k_tile_sort_long may be left: each is longer than `chunk`
+    auto long_wgs = [&](uint64_t chunk) {
+        return unsigned(std::min<uint64_t>({uint64_t(nt), 256u, bins.capacity / chunk + 1}));
+    };
+    // By strips while every strip's pass over all records costs less than the
+    // pipeline's launches (us a call with the plan, strips / pipeline, one
+    // view: 9k records, 64 tiles 28 / 34; 18k, 64 tiles 32 / 36; 40k, 64 tiles
+    // 46 / 40; 20k, 256 tiles 33 / 35; 40k, 256 tiles 43 / 38; 60k, 475 tiles
+    // 55 / 58; 20k, 1,900 tiles 33 / 53; 65k, 1,900 tiles 61 / 71; 65k, 6,700
+    // tiles 92 / 114; 90k, 1,200 tiles 75 / 72; 90k, 6,700 tiles 156 / 134).
+    if (f.n_records <= std::min(kStripRecords, 16384 + 48 * nt) && nt > 0 && nt <= kStripTiles) {
+        static_assert(sizeof(StripInfo) * kStripTiles <= sizeof(uint32_t) * 256 * kMaxGrid, "in the histograms' place");
+        StripInfo* info = reinterpret_cast<StripInfo*>(w.hist);
+        uint32_t* cols = reinterpret_cast<uint32_t*>(w.key[1]);
+        const int cols_per = int((nt + kStrips - 1) / kStrips), strip_wgs = int(std::min<int64_t>(nt, 2 * kStrips));
+        GS_LAUNCH("k_bin_strips", k_bin_strips,
+                  dim3(unsigned(strip_wgs + (f.n_records + 4 * kStripBlock - 1) / (4 * kStripBlock))),
+                  dim3(kStripBlock), 0, s, meta, f, bins.capacity, w.key[0], cols, info, cols_per, strip_wgs, w.longq,
+                  bins.pair_off, bins.counters);
+        GS_LAUNCH("k_bin_tiles", k_bin_tiles, dim3(unsigned(nt)), dim3(kBinTileBlock), 0, s, meta, f, bins.capacity,
+                  w.key[0], cols, info, cols_per, bins.vals, ranges, w.longq);
+        // the plan's counts take the strips' place
+        if (plan.order) GS_LAUNCH("k_tile_plan", k_tile_plan, dim3(unsigned(plan.blocks)), dim3(1024), 0, s, plan);
+        GS_LAUNCH("k_tile_sort_long", k_tile_sort_long,
+                  dim3((plan.order ? unsigned(plan.blocks) : 0u) + long_wgs(kBinTileList)), dim3(kLongBlock), 0, s,
+                  meta, ranges, w.longq, bins.vals, w.key[0], w.key[1], plan);
         return hipGetLastError();
     }
 
@@ -1342,11 +1590,16 @@ hipError_t launch_bin_sort(const gs_frame& f, const gs_raster_cfg& cfg, const ui
             GS_LAUNCH("k_tile_sort", kernel, dim3(plan_wgs + unsigned(std::min<int64_t>(lists, 4096))),
                       dim3(sort_block(form)), 0, s, meta, ranges, f.n_tiles, bins.vals, w.longq, plan);
         };
-        if (bins.capacity <= uint64_t(nt) * (nt >= kManyTiles ? kWaveListMany : kWaveList)) sort(k_tile_sort<kSortWaves>, kSortWaves, (nt + 3) / 4);
+        uint64_t chunk = sort_chunk(kSortBlocks);
+        if (bins.capacity <= uint64_t(nt) * (nt >= kManyTiles ? kWaveListMany : kWaveList))
+            sort(k_tile_sort<kSortWaves>, kSortWaves, (nt + 3) / 4);
         else if (bins.capacity <= uint64_t(nt) * kDenseList) sort(k_tile_sort<kSortBlocks>, kSortBlocks, nt);
-        else sort(k_tile_sort<kSortDense>, kSortDense, nt);
-        GS_LAUNCH("k_tile_sort_long", k_tile_sort_long, dim3(plan_wgs + unsigned(std::min<int64_t>(nt, 256))),
-                  dim3(kLongBlock), 0, s, meta, ranges, w.longq, bins.vals, w.key[0], w.key[1], plan);
+        else {
+            sort(k_tile_sort<kSortDense>, kSortDense, nt);
+            chunk = sort_chunk(kSortDense);
+        }
+        GS_LAUNCH("k_tile_sort_long", k_tile_sort_long, dim3(plan_wgs + long_wgs(chunk)), dim3(kLongBlock), 0, s, meta,
+                  ranges, w.longq, bins.vals, w.key[0], w.key[1], plan);
     }
     return hipGetLastError();
 }

@@ -888,7 +888,7 @@ def test_consensus_of_many_ids_equals_its_parts(deg, relax):
 @pytest.mark.parametrize("room", ["all", "exact", "half", "one"])
 def test_bins_of_small_frames(n, jobs, room):
     """Frames on both sides of the record counts where one launch makes the
-    bins (2048 and 8192 records a job; more: the pipeline): most records in
+    bins (2048 and 8192 records a job; more: by strips): most records in
     one tile, the others' rectangles up to the whole image, culled ones among
     them, depths with ties.  Bins, first pairs and counters against pairs
     listed here in record order; with fewer pairs of capacity than the frame
@@ -942,3 +942,102 @@ def test_bins_of_small_frames(n, jobs, room):
     np.testing.assert_array_equal(buf.ranges.view(-1, 2).cpu().numpy(), ranges)
     vis = meta[:, 1] > 0
     np.testing.assert_array_equal(buf.pair_off.cpu().numpy()[vis], np.asarray(first)[vis])
+
+
+def _bins_of(frame, cfg, meta, capacity):
+    buf = gs.Buffers(frame, capacity)
+    buf.meta.copy_(torch.from_numpy(meta.view(np.int32).reshape(-1)))
+    buf.ranges.fill_(99)
+    gs.bin_sort(frame, cfg, buf)
+    return buf
+
+
+def _expect_bins(frame, buf, meta):
+    """vals, ranges, first pairs and counters against the first `capacity` of
+    all pairs, listed here in record order."""
+    n = meta[:, 1].astype(np.int64)
+    rec = np.repeat(np.arange(len(meta)), n)
+    first = np.cumsum(n) - n
+    k = np.arange(len(rec)) - first[rec]                          # pair of its record
+    x0, y0 = (meta[rec, 2] & 0xFFFF).astype(np.int64), (meta[rec, 2] >> 16).astype(np.int64)
+    w = (meta[rec, 3] & 0xFFFF) - x0 + 1
+    tile = np.empty(len(rec), np.int64)
+    for j in range(frame.n_jobs):
+        b = frame.job(j)
+        own = (rec >= b.rec0) & (rec < b.rec0 + b.g1 - b.g0)
+        tile[own] = b.tile0 + (y0[own] + k[own] // w[own]) * b.tiles_x + x0[own] + k[own] % w[own]
+    c = gs.read_counters(buf)
+    over = len(rec) > buf.capacity
+    assert (c["visible"], c["pairs"], c["overflowed"]) == (int((n > 0).sum()), len(rec), int(over))
+    rec, tile = rec[:buf.capacity], tile[:buf.capacity]
+    order = np.lexsort((rec, meta[rec, 0], tile))
+    got = buf.vals[:len(rec)].cpu().numpy().view(np.uint32)
+    np.testing.assert_array_equal(got, rec[order])
+    ranges = np.zeros((frame.n_tiles, 2), np.int64)
+    count = np.bincount(tile, minlength=frame.n_tiles)
+    ranges[:, 1] = np.cumsum(count)
+    ranges[:, 0] = ranges[:, 1] - count
+    ranges[count == 0] = 0
+    np.testing.assert_array_equal(buf.ranges.view(-1, 2).cpu().numpy(), ranges)
+    np.testing.assert_array_equal(buf.pair_off.cpu().numpy()[n > 0], first[n > 0])
+    plan = np.sort(buf.tile_order[4:4 + frame.n_tiles].cpu().numpy())
+    assert np.array_equal(plan, np.arange(frame.n_tiles))
+
+
+@pytest.mark.parametrize("room", ["all", "exact", "half"])
+@pytest.mark.parametrize("n,w,h,jobs", [(8193, 16, 16, 1), (8193, 17, 16, 2), (9000, 16 * 191, 16, 1),
+                                        (9000, 16 * 193, 16, 2), (5000, 700, 420, 2), (20000, 330, 500, 1),
+                                        (20227, 160, 128, 1), (65535, 800, 410, 1), (65537, 800, 410, 1),
+                                        (32768, 790, 400, 2)])
+def test_bins_by_strips(n, w, h, jobs, room):
+    """Frames of some thousand records (up to 65,536, or 20,224 in 80 tiles):
+    strips of one tile to a whole row, ragged at the row's end, strips' lists
+    on both sides of 4096 entries and tiles' of 2048 and 8192, rectangles from
+    one tile to the image, equal depths, culled records."""
+    rng = np.random.default_rng(n + w)
+    cams = [scenes.look_at([0.0, 0.0, 3.0], [0, 0, 0], w + 16 * k, h, 100.0, 100.0) for k in range(jobs)]
+    cfg = gs.raster_cfg((16, 16, -1))
+    frame = gs.Frame(cams, [gs.JobSpec(k, 0, n, 1.0) for k in range(jobs)], cfg)
+    meta = np.zeros((frame.n_records, 4), np.uint32)
+    for k in range(jobs):
+        j = frame.job(k)
+        x0, y0 = rng.integers(0, j.tiles_x, n), rng.integers(0, j.tiles_y, n)
+        one = rng.random(n) < 0.2 + 0.3 * k                       # these crowd into one tile
+        x0[one], y0[one] = j.tiles_x // 2, j.tiles_y // 2
+        x1 = np.minimum(x0 + np.where(one, 0, rng.integers(0, 4, n)), j.tiles_x - 1)
+        y1 = np.minimum(y0 + np.where(one, 0, rng.integers(0, 3, n)), j.tiles_y - 1)
+        full = rng.random(n) < 4.0 / n
+        x0[full], y0[full], x1[full], y1[full] = 0, 0, j.tiles_x - 1, j.tiles_y - 1
+        m = meta[j.rec0:j.rec0 + n]
+        m[:, 0] = (1.0 + rng.integers(0, 500, n) / 16.0).astype(np.float32).view(np.uint32)
+        m[:, 1], m[:, 2], m[:, 3] = (x1 - x0 + 1) * (y1 - y0 + 1), x0 | (y0 << 16), x1 | (y1 << 16)
+        m[rng.random(n) < 0.1] = [0xffffffff, 0, 0, 0]
+    pairs = int(meta[:, 1].sum())
+    buf = _bins_of(frame, cfg, meta, {"all": 2 * pairs + 7, "exact": pairs, "half": pairs // 2}[room])
+    _expect_bins(frame, buf, meta)
+
+
+@pytest.mark.parametrize("size", [(16, 16), (32, 16), (48, 16), (13 * 16, 16), (16 * 16, 16 * 17), (16 * 96, 16 * 87)])
+@pytest.mark.parametrize("mean", [40, 300, 1000, 1100])
+def test_bins_of_many_records(size, mean):
+    """More records than go by strips (most of them culled): no radix pass to
+    two, tile lists at the edges of every form of the tile sort, which follows
+    from the pair capacity per tile and the number of tiles."""
+    rng = np.random.default_rng(size[0] + mean)
+    cam = scenes.look_at([0.0, 0.0, 3.0], [0, 0, 0], *size, 100.0, 100.0)
+    cfg = gs.raster_cfg((16, 16, -1))
+    tx, nt = size[0] // 16, size[0] // 16 * (size[1] // 16)
+    lengths = [0, 1, 2, 3, 63, 64, 65, 128, 129, 256, 257, 511, 512, 513, 1025, 2047, 2048, 2049, 4096, 4097, 9000]
+    tiles = np.repeat(rng.permutation(max(nt, len(lengths)))[:len(lengths)], lengths) % nt
+    n = 70_000
+    rec = np.sort(rng.permutation(n)[:len(tiles)])
+    tiles = rng.permutation(tiles)
+    meta = np.zeros((n, 4), np.uint32)
+    meta[:, 0] = 0xffffffff
+    meta[rec, 0] = (1.0 + rng.integers(0, 3000, len(rec)) / 16.0).astype(np.float32).view(np.uint32)
+    meta[rec, 1] = 1
+    meta[rec, 2] = meta[rec, 3] = (tiles % tx) | (tiles // tx << 16)
+    frame = gs.Frame([cam], [gs.JobSpec(0, 0, n, 1.0)], cfg)
+    assert frame.n_tiles == nt
+    buf = _bins_of(frame, cfg, meta, max(mean * nt, len(rec)))
+    _expect_bins(frame, buf, meta)
