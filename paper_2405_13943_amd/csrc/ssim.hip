@@ -9,18 +9,24 @@
 // channel) items, staging the tile plus a 5-pixel halo in LDS and blurring
 // separably (rows, then columns, four outputs per thread), while the next
 // item's loads are in flight.
-//   k_ssim_fwd  blurs x, y, x^2, y^2, xy; forms SSIM and its derivatives with
+//   k_ssim_fwd  blurs x, y, x^2 + y^2 (the variances enter SSIM as their sum)
+//               and xy; forms SSIM and its derivatives with
 //               respect to the window sums (mu_x, E[x^2], E[xy]); writes the
 //               three derivative maps (pre-scaled by -w lambda / N) and adds
 //               the tile's share of the job's loss;
 //   k_ssim_bwd  blurs the three maps and combines them with x and y into
 //               dL/dC (plus the L1 term), the external gradient of the
 //               compositing backward.
+// Both are bound by VALU issue, most of it the blurs' multiply-adds, written
+// as fused ones (the rest of the library compiles with contraction off): the
+// passes took 63 and 50 us at 1600 x 1066 with five window sums and separate
+// multiplies and adds, and 50 and 46 as they are.
 // (A grid over every binning tile, with three of four workgroups exiting at
 // once, spent 40% of its time dispatching workgroups that did nothing.)
 #include "gs_device.hpp"
 #include "gs_internal.hpp"
 
+#include <algorithm>
 #include <cmath>
 
 namespace gs {
@@ -45,7 +51,7 @@ struct Taps {
 
 struct SsimTile {
     int job, x0, y0, W, H;
-    int64_t px;       // first element of the job's channel-0 plane
+    int64_t px;       // first element of the item's first channel plane
     int64_t plane;    // elements per channel plane
 };
 
@@ -85,6 +91,16 @@ __device__ inline SsimTile tile_at(const gs_frame& f, int tw, int th, uint32_t i
     t.H = cam.height;
     t.plane = int64_t(t.W) * t.H;
     t.px = 3 * job.px0;
+    return t;
+}
+
+// Item i of the walk: a tile with all three channels (split 1) or one channel
+// of a tile (split 3); ch: its first channel
+__device__ inline SsimTile item_at(const gs_frame& f, int tw, int th, int split, uint32_t i, int& ch) {
+    const uint32_t tile = i / uint32_t(split);
+    ch = int(i - tile * uint32_t(split));
+    SsimTile t = tile_at(f, tw, th, tile);
+    t.px += ch * t.plane;
     return t;
 }
 
@@ -148,7 +164,7 @@ __device__ inline void blur_rows(const float (*src)[kIn][kPitch], float (*dst)[k
                 if (tap < 0 || tap >= kTaps) continue;
                 const float g = taps.g[tap];
 #pragma unroll
-                for (int m = 0; m < M; m++) acc[m][q] += g * h[m];
+                for (int m = 0; m < M; m++) acc[m][q] = fmaf(g, h[m], acc[m][q]);
             }
         }
 #pragma unroll
@@ -158,32 +174,32 @@ __device__ inline void blur_rows(const float (*src)[kIn][kPitch], float (*dst)[k
     }
 }
 
-// horizontal pass of the forward: from staged x and y, the five window sums
-// of x, y, x^2, y^2, xy (products formed once per staged value and item)
+// horizontal pass of the forward: from staged x and y, the four window sums
+// of x, y, x^2 + y^2, xy (products formed once per staged value and item)
 __device__ inline void blur_rows_moments(const float (*src)[kIn][kPitch], float (*dst)[kIn][kHPitch],
                                          const Taps& taps) {
     for (int i = threadIdx.x; i < kIn * (kTile / kBlk); i += kThreads) {
         const int r = i / (kTile / kBlk), c0 = (i % (kTile / kBlk)) * kBlk;
-        float acc[5][kBlk];
+        float acc[4][kBlk];
 #pragma unroll
         for (int q = 0; q < kBlk; q++)
 #pragma unroll
-            for (int m = 0; m < 5; m++) acc[m][q] = 0.f;
+            for (int m = 0; m < 4; m++) acc[m][q] = 0.f;
 #pragma unroll
         for (int k = 0; k < kBlk + kTaps - 1; k++) {
             const float a = src[0][r][c0 + k], b = src[1][r][c0 + k];
-            const float h[5] = {a, b, a * a, b * b, a * b};
+            const float h[4] = {a, b, a * a + b * b, a * b};
 #pragma unroll
             for (int q = 0; q < kBlk; q++) {
                 const int tap = k - q;
                 if (tap < 0 || tap >= kTaps) continue;
                 const float g = taps.g[tap];
 #pragma unroll
-                for (int m = 0; m < 5; m++) acc[m][q] += g * h[m];
+                for (int m = 0; m < 4; m++) acc[m][q] = fmaf(g, h[m], acc[m][q]);
             }
         }
 #pragma unroll
-        for (int m = 0; m < 5; m++)
+        for (int m = 0; m < 4; m++)
 #pragma unroll
             for (int q = 0; q < kBlk; q++) dst[m][r][c0 + q] = acc[m][q];
     }
@@ -208,22 +224,24 @@ __device__ inline void blur_cols(const float (*src)[kIn][kHPitch], int c, int r0
             if (tap < 0 || tap >= kTaps) continue;
             const float g = taps.g[tap];
 #pragma unroll
-            for (int m = 0; m < M; m++) acc[m][q] += g * h[m];
+            for (int m = 0; m < M; m++) acc[m][q] = fmaf(g, h[m], acc[m][q]);
         }
     }
 }
 
-__global__ __launch_bounds__(kThreads, 3) void k_ssim_fwd(gs_frame f, int tw, int th, const float* __restrict__ rgb,
+__global__ __launch_bounds__(kThreads, 3) void k_ssim_fwd(gs_frame f, int tw, int th, int split, const float* __restrict__ rgb,
                                                        const float* __restrict__ tgt,
                                                        float lambda, Taps taps, float* __restrict__ dmaps,
                                                        int64_t map_stride, float* __restrict__ loss_out) {
     __shared__ float st[2][kIn][kPitch];       // staged x, y
-    __shared__ float hs[5][kIn][kHPitch];
+    __shared__ float hs[4][kIn][kHPitch];
     __shared__ float red[kThreads / 64];
-    const uint32_t cnt = frame_tiles(f, tw, th);
+    const uint32_t cnt = frame_tiles(f, tw, th) * uint32_t(split);
+    const int chs = 3 / split;                 // channels of an item
+    int ch0;
     uint32_t i = blockIdx.x;
     if (i >= cnt) return;
-    SsimTile t = tile_at(f, tw, th, i);
+    SsimTile t = item_at(f, tw, th, split, i, ch0);
     StageIdx si = stage_index(t);
     float va[kStage], vb[kStage];
 #pragma unroll
@@ -235,16 +253,16 @@ __global__ __launch_bounds__(kThreads, 3) void k_ssim_fwd(gs_frame f, int tw, in
     // loss sums of the workgroup's tiles of one job, added to loss_out when
     // the job changes or the workgroup is done (one atomic per job and
     // workgroup: per-tile atomics on one word would serialise)
-    float s_sum = 0.f, l1_sum = 0.f;
-    int firsts = 0;
+    float ds_sum = 0.f, l1_sum = 0.f;
     while (true) {
         const gs_job job = f.jobs[t.job];
         const float n = 3.f * float(t.W) * float(t.H);
         const float coef = -job.loss_weight * lambda / n;
         const uint32_t inext = i + gridDim.x;
         SsimTile tn = t;
+        int chn = ch0;
         StageIdx sn = si;
-        for (int ch = 0; ch < 3; ch++) {
+        for (int ch = 0; ch < chs; ch++) {
             const int64_t base = t.px + ch * t.plane;
 #pragma unroll
             for (int it = 0; it < kStage; it++) {
@@ -257,14 +275,14 @@ __global__ __launch_bounds__(kThreads, 3) void k_ssim_fwd(gs_frame f, int tw, in
             }
             __syncthreads();
             // the next item's tile, in flight during this one
-            if (ch < 2) {
+            if (ch + 1 < chs) {
 #pragma unroll
                 for (int it = 0; it < kStage; it++) {
                     va[it] = rgb[base + t.plane + si.off[it]];
                     vb[it] = tgt[base + t.plane + si.off[it]];
                 }
             } else if (inext < cnt) {
-                tn = tile_at(f, tw, th, inext);
+                tn = item_at(f, tw, th, split, inext, chn);
                 sn = stage_index(tn);
 #pragma unroll
                 for (int it = 0; it < kStage; it++) {
@@ -274,17 +292,17 @@ __global__ __launch_bounds__(kThreads, 3) void k_ssim_fwd(gs_frame f, int tw, in
             }
             blur_rows_moments(st, hs, taps);
             __syncthreads();
-            float acc[5][kBlk];
-            blur_cols<5>(hs, c, r0, taps, acc);
+            float acc[4][kBlk];
+            blur_cols<4>(hs, c, r0, taps, acc);
 #pragma unroll
             for (int q = 0; q < kBlk; q++) {
                 const int r = r0 + q;
                 const int gy = t.y0 + r, gx = t.x0 + c;
                 if (gy >= t.H || gx >= t.W) continue;
                 const float mx = acc[0][q], my = acc[1][q];
-                const float vx = acc[2][q] - mx * mx, vy = acc[3][q] - my * my, cxy = acc[4][q] - mx * my;
+                const float sq = mx * mx + my * my, var = acc[2][q] - sq, cxy = acc[3][q] - mx * my;
                 const float a1 = 2.f * mx * my + kC1, a2 = 2.f * cxy + kC2;
-                const float b1 = mx * mx + my * my + kC1, b2 = vx + vy + kC2;
+                const float b1 = sq + kC1, b2 = var + kC2;
                 const float inv = 1.f / (b1 * b2);
                 const float s = a1 * a2 * inv;
                 const float d_xx = -s * (b1 * inv);          // -S / B2
@@ -294,28 +312,25 @@ __global__ __launch_bounds__(kThreads, 3) void k_ssim_fwd(gs_frame f, int tw, in
                 dmaps[o] = coef * d_mu;
                 dmaps[map_stride + o] = coef * d_xx;
                 dmaps[2 * map_stride + o] = coef * d_xy;
-                s_sum += s;
+                ds_sum += 1.f - s;
                 const float d = st[0][r + kRad][c + kRad] - st[1][r + kRad][c + kRad];
                 l1_sum += d < 0.f ? -d : d;
             }
             __syncthreads();                   // st and hs are rewritten by the next item
         }
-        if (t.x0 == 0 && t.y0 == 0) firsts++;
         // uniform: the loss is optional, and the next tile is the same for the workgroup
         if (loss_out != nullptr && (inext >= cnt || tn.job != t.job)) {
-            const float ss = block_sum(s_sum, red);
+            const float ds = block_sum(ds_sum, red);
             const float ls = block_sum(l1_sum, red);
             if (threadIdx.x == 0) {
-                // w (mean |d| - lambda mean S), plus w lambda once per job for the 1 of 1 - mean S
-                const float add = job.loss_weight * (ls - lambda * ss) / n + float(firsts) * job.loss_weight * lambda;
-                atomicAdd(loss_out + t.job, add);
+                atomicAdd(loss_out + t.job, job.loss_weight * (ls + lambda * ds) / n);
             }
-            s_sum = l1_sum = 0.f;
-            firsts = 0;
+            ds_sum = l1_sum = 0.f;
         }
         if (inext >= cnt) break;
         i = inext;
         t = tn;
+        ch0 = chn;
         si = sn;
     }
 }
@@ -330,17 +345,19 @@ __device__ inline void out_index(const SsimTile& t, int c, int r0, int32_t (&oo)
     }
 }
 
-__global__ __launch_bounds__(kThreads) void k_ssim_bwd(gs_frame f, int tw, int th, const float* __restrict__ rgb,
+__global__ __launch_bounds__(kThreads) void k_ssim_bwd(gs_frame f, int tw, int th, int split, const float* __restrict__ rgb,
                                                        const float* __restrict__ tgt,
                                                        Taps taps, const float* __restrict__ dmaps, int64_t map_stride,
                                                        float* __restrict__ grad) {
     __shared__ float sd[3][kIn][kPitch];
     __shared__ float hd[3][kIn][kHPitch];
-    const uint32_t cnt = frame_tiles(f, tw, th);
+    const uint32_t cnt = frame_tiles(f, tw, th) * uint32_t(split);
+    const int chs = 3 / split;                 // channels of an item
+    int ch0;
     uint32_t i = blockIdx.x;
     if (i >= cnt) return;
     const int c = int(threadIdx.x) % kTile, r0 = (int(threadIdx.x) / kTile) * kBlk;
-    SsimTile t = tile_at(f, tw, th, i);
+    SsimTile t = item_at(f, tw, th, split, i, ch0);
     StageIdx si = stage_index(t);
     int32_t oo[kBlk];
     uint32_t oin;
@@ -362,12 +379,13 @@ __global__ __launch_bounds__(kThreads) void k_ssim_bwd(gs_frame f, int tw, int t
         const float l1 = job.loss_weight / (3.f * float(t.W) * float(t.H));
         const uint32_t inext = i + gridDim.x;
         SsimTile tn = t;
+        int chn = ch0;
         StageIdx sn = si;
         int32_t on[kBlk];
         uint32_t onin = oin;
 #pragma unroll
         for (int q = 0; q < kBlk; q++) on[q] = oo[q];
-        for (int ch = 0; ch < 3; ch++) {
+        for (int ch = 0; ch < chs; ch++) {
             const int64_t base = t.px + ch * t.plane;
 #pragma unroll
             for (int it = 0; it < kStage; it++) {
@@ -384,7 +402,7 @@ __global__ __launch_bounds__(kThreads) void k_ssim_bwd(gs_frame f, int tw, int t
             for (int q = 0; q < kBlk; q++) { xc[q] = xo[q]; yc[q] = yo[q]; }
             __syncthreads();
             // the next item's tile, in flight during this one
-            if (ch < 2) {
+            if (ch + 1 < chs) {
                 const int64_t nb = base + t.plane;
 #pragma unroll
                 for (int it = 0; it < kStage; it++) {
@@ -398,7 +416,7 @@ __global__ __launch_bounds__(kThreads) void k_ssim_bwd(gs_frame f, int tw, int t
                     yo[q] = tgt[nb + oo[q]];
                 }
             } else if (inext < cnt) {
-                tn = tile_at(f, tw, th, inext);
+                tn = item_at(f, tw, th, split, inext, chn);
                 sn = stage_index(tn);
                 out_index(tn, c, r0, on, onin);
 #pragma unroll
@@ -429,6 +447,7 @@ __global__ __launch_bounds__(kThreads) void k_ssim_bwd(gs_frame f, int tw, int t
         if (inext >= cnt) break;
         i = inext;
         t = tn;
+        ch0 = chn;
         si = sn;
         oin = onin;
 #pragma unroll
@@ -474,12 +493,19 @@ hipError_t launch_ssim_loss_grad(const gs_frame& f, const gs_raster_cfg& cfg, co
         resident[1] = cus * (nb > 0 ? nb : 1);
         resident_dev = dev;
     }
-    const int gf = f.n_tiles < resident[0] ? f.n_tiles : resident[0];
-    const int gb = f.n_tiles < resident[1] ? f.n_tiles : resident[1];
-    GS_LAUNCH("k_ssim_fwd", k_ssim_fwd, dim3(unsigned(gf)), dim3(kThreads), 0, s, f, cfg.tile_w, cfg.tile_h, rgb, tgt,
-              lambda, taps, maps, stride, loss);
-    GS_LAUNCH("k_ssim_bwd", k_ssim_bwd, dim3(unsigned(gb)), dim3(kThreads), 0, s, f, cfg.tile_w, cfg.tile_h, rgb, tgt,
-              taps, maps, stride, grad);
+    // One channel an item while the frame's tiles (at least that many) leave
+    // half of the grid empty: three channels one after the other are then the
+    // launch's time (forward / backward, us with the events: 11 tiles 20.3 /
+    // 14.7 by tile, 10.1 / 8.2 by channel; 130 tiles 20.0 / 13.2, 15.8 / 9.5;
+    // 651 tiles 29.4 / 24.9, 30.0 / 24.0; 1,700 tiles 53.8 / 50.0, 58.3 /
+    // 52.0: a tile's indices are kept for its three channels)
+    const int64_t tiles = int64_t(f.n_tiles) * (cfg.tile_w * cfg.tile_h) / (kTile * kTile);
+    auto split = [&](int k) { return 2 * tiles <= resident[k] ? 3 : 1; };
+    auto grid = [&](int k) { return unsigned(std::min<int64_t>(int64_t(f.n_tiles) * split(k), resident[k])); };
+    GS_LAUNCH("k_ssim_fwd", k_ssim_fwd, dim3(grid(0)), dim3(kThreads), 0, s, f, cfg.tile_w, cfg.tile_h, split(0), rgb,
+              tgt, lambda, taps, maps, stride, loss);
+    GS_LAUNCH("k_ssim_bwd", k_ssim_bwd, dim3(grid(1)), dim3(kThreads), 0, s, f, cfg.tile_w, cfg.tile_h, split(1), rgb,
+              tgt, taps, maps, stride, grad);
     return hipGetLastError();
 }
 

@@ -53,6 +53,17 @@ def _check(frame, cfg, rgb, tgt, lam, weights):
     return grad
 
 
+@pytest.mark.parametrize("sizes", [[(673, 641)], [(1010, 915)], [(700, 500), (33, 65), (640, 417), (5, 400)]])
+def test_large_images_match_oracle(sizes):
+    """More 32 x 32 tiles than half a grid (a workgroup takes a tile's three
+    channels) and than a whole one (several tiles, of several jobs)."""
+    cfg = gs.raster_cfg((16, 16))
+    weights = [1.0, 0.5, 2.0, 0.25][:len(sizes)]
+    frame = _frame(cfg, sizes, weights)
+    rgb, tgt = _images(frame, 21)
+    _check(frame, cfg, rgb, tgt, 0.2, weights)
+
+
 @pytest.mark.parametrize("tile", [(16, 16), (8, 8), (16, 8), (32, 8)])
 def test_loss_and_gradient_match_oracle(tile):
     cfg = gs.raster_cfg(tile)
