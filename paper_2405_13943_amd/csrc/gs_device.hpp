@@ -12,8 +12,17 @@ constexpr int kWave = 64;
 
 // 16-byte accesses with the non-temporal hint, for state that one step
 // touches once (the optimiser's moments and the consensus target): they
-// keep it from evicting the lines that the same kernel reads again
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+// keep it from evicting the lines that the same kernel reads again.  Any
+// element may be the first (4-byte alignment: planes of an odd stride)
+typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ inline float4 load4(const float* p) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ inline void store4(float* p, float4 v) {
+    const f32x4 w = {v.x, v.y, v.z, v.w};
+    *reinterpret_cast<f32x4*>(p) = w;
+}
 __device__ inline float4 load_stream4(const float* p) {
     const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
     return make_float4(v.x, v.y, v.z, v.w);

@@ -742,8 +742,8 @@ __host__ __device__ inline unsigned uncovered_blocks(int64_t n_unc) {
 // colour gradient dc[ch] (the SH-plane gradient is the product Y[k] dc[ch],
 // formed exactly as the chain rule emits it); a culled record leaves zeros.
 // (2) The block streams the optimiser over all planes of its Gaussians: when
-// they are contiguous and 16-byte aligned, as items of (plane, 4 Gaussians)
-// with 16-byte accesses, else one Gaussian per thread.  The gradient never
+// they are contiguous, as items of (plane, 4 Gaussians) with 16-byte accesses
+// (aligned or not), else one Gaussian per thread.  The gradient never
 // reaches HBM and the parameters read by the chain are still in cache for the
 // update.  Same arithmetic as k_project_bwd_rec followed by k_adam_admm.
 //
@@ -761,7 +761,7 @@ __device__ inline float staged_grad(const float* geo, const float* Y, const floa
                   : Y[((a - 11) / 3) * kFusedBlock + i] * dc[((a - 11) % 3) * kFusedBlock + i];
 }
 
-// phase 2 over contiguous, 16-byte aligned Gaussians g0 .. g0 + kFusedBlock - 1:
+// phase 2 over contiguous Gaussians g0 .. g0 + kFusedBlock - 1:
 // each wavefront takes every fourth plane, its lanes 4 Gaussians each with
 // 16-byte accesses; the loads of kUnroll planes are issued before any of
 // them is used, so several lines per lane are in flight.  m, v and w stream
@@ -781,14 +781,14 @@ __device__ inline void adam_block_vec(float* __restrict__ X, int64_t sx, float* 
     const int64_t gv = g0 + i;
     const int a_first = __builtin_amdgcn_readfirstlane(t / kCols);   // the wavefront's first plane
     float4 kv = make_float4(1.f, 1.f, 1.f, 1.f);
-    if (MASK) kv = *reinterpret_cast<const float4*>(mask + gv);
+    if (MASK) kv = load4(mask + gv);
     for (int a0 = a_first; a0 < A; a0 += kUnroll * kStep) {
         float4 xv[kUnroll], mv[kUnroll], vv[kUnroll], wv[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; u++) {
             const int a = a0 + u * kStep;   // uniform
             if (a >= A) break;
-            xv[u] = *reinterpret_cast<const float4*>(X + a * sx + gv);
+            xv[u] = load4(X + a * sx + gv);
             mv[u] = load_stream4(M + a * sm + gv);
             vv[u] = load_stream4(V + a * sv + gv);
             wv[u] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -813,7 +813,7 @@ __device__ inline void adam_block_vec(float* __restrict__ X, int64_t sx, float* 
             adam_one(xv[u].y, gq.y, mv[u].y, vv[u].y, wv[u].y, PEN ? rho * kv.y : 0.f, lr, c);
             adam_one(xv[u].z, gq.z, mv[u].z, vv[u].z, wv[u].z, PEN ? rho * kv.z : 0.f, lr, c);
             adam_one(xv[u].w, gq.w, mv[u].w, vv[u].w, wv[u].w, PEN ? rho * kv.w : 0.f, lr, c);
-            *reinterpret_cast<float4*>(X + a * sx + gv) = xv[u];
+            store4(X + a * sx + gv, xv[u]);
             store_stream4(M + a * sm + gv, mv[u]);
             store_stream4(V + a * sv + gv, vv[u]);
             adam_finite(fin, xv[u].x, vv[u].x);
@@ -843,7 +843,7 @@ __device__ inline void adam_block_one(float* __restrict__ X, int64_t sx, float* 
     }
 }
 
-template <int D, bool PEN, bool MASK, bool VEC>
+template <int D, bool PEN, bool MASK>
 __global__ __launch_bounds__(kFusedBlock) void k_project_bwd_adam(
     float* X, int64_t sx, gs_frame frame, gs_raster_cfg cfg, const float* __restrict__ rec,
     const uint4* __restrict__ meta, const uint32_t* __restrict__ pair_off, uint64_t capacity,
@@ -921,7 +921,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_project_bwd_adam(
 
     // phase 2: optimiser over the planes
     float fin = 0.f;
-    if (VEC && contiguous && (g0 & 3) == 0)
+    if (contiguous)
         adam_block_vec<A, PEN, MASK>(X, sx, M, sm, V, sv, Wp, sw, mask, g0, &s_geo[0][0], &s_Y[0][0], &s_dc[0][0], c,
                                      fin);
     else if (active)
@@ -1015,8 +1015,6 @@ hipError_t launch_project_bwd(const gs_params& p, const gs_frame& f, const gs_ra
     return hipGetLastError();
 }
 
-static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-
 template <int D, bool PEN, bool MASK>
 static void project_bwd_adam_launch(gs_params& x, const gs_frame& f, const gs_raster_cfg& cfg, const float* rec,
                                     const uint4* M,
@@ -1028,22 +1026,14 @@ static void project_bwd_adam_launch(gs_params& x, const gs_frame& f, const gs_ra
     float* Vo = static_cast<float*>(v.data);
     const float* Wd = w ? static_cast<const float*>(w->data) : nullptr;
     const int64_t sw = w ? w->stride : 0;
-    const bool vec = aligned16(X) && aligned16(Mo) && aligned16(Vo) && (!Wd || aligned16(Wd)) &&
-                     (!mask || aligned16(mask)) && x.stride % 4 == 0 && m.stride % 4 == 0 && v.stride % 4 == 0 &&
-                     sw % 4 == 0;
     constexpr unsigned A = 11 + 3 * (D + 1) * (D + 1);
     const unsigned rec_blocks = unsigned((f.n_records + kFusedBlock - 1) / kFusedBlock);
     const int64_t n_unc = x.n > f.n_records ? x.n - f.n_records : 0;   // disjoint jobs: every record is another column
     const unsigned lb = loss_blocks(f, loss);
     const dim3 grid(lb + rec_blocks + A * uncovered_blocks(n_unc)), block(kFusedBlock);
-    if (vec)
-        GS_LAUNCH("k_project_bwd_adam", (k_project_bwd_adam<D, PEN, MASK, true>), grid, block, 0, s, X, x.stride, f,
-                  cfg, rec, M, pair_off, capacity, pg, Mo, m.stride, Vo, v.stride, Wd, sw, mask, c, status,
-                  rec_blocks, x.n, n_unc, loss, lb);
-    else
-        GS_LAUNCH("k_project_bwd_adam", (k_project_bwd_adam<D, PEN, MASK, false>), grid, block, 0, s, X, x.stride,
-                  f, cfg, rec, M, pair_off, capacity, pg, Mo, m.stride, Vo, v.stride, Wd, sw, mask, c, status,
-                  rec_blocks, x.n, n_unc, loss, lb);
+    GS_LAUNCH("k_project_bwd_adam", (k_project_bwd_adam<D, PEN, MASK>), grid, block, 0, s, X, x.stride, f, cfg, rec, M,
+              pair_off, capacity, pg, Mo, m.stride, Vo, v.stride, Wd, sw, mask, c, status, rec_blocks, x.n, n_unc,
+              loss, lb);
 }
 
 template <int D>

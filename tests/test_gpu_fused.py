@@ -141,3 +141,49 @@ def test_columns_no_job_covers(ranges):
     assert (grad[:, ~covered] == 0).all()
     a, b = both_paths(x, frame, cfg, target, True, True, step=4, seed=9)
     assert_same(a, b)
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 255, 256, 257, 1027])
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+def test_planes_of_any_alignment(n, shift):
+    """Planes that start at any element and have any stride, ranges that start
+    at any column: the same bits as from contiguous planes, by both paths, and
+    nothing written beside them."""
+    p = scenes.gaussians(n + 3, 1, 77 + n, [-0.3, -0.3, -0.3], [0.3, 0.3, 0.3], -2.0, 0.3)
+    x = torch.from_numpy(p).cuda()
+    cam = scenes.look_at([0.0, 0.0, 3.0], [0, 0, 0], 64, 48, 60.0, 60.0)
+    cfg = gs.raster_cfg((16, 16))
+    frame = gs.Frame([cam], [gs.JobSpec(0, shift, shift + n, 1.0)], cfg)
+    target = torch.rand(3 * frame.n_pixels, generator=torch.Generator().manual_seed(n)).cuda()
+    m, v, w, mask = state(x, n)
+    A, N = x.shape
+
+    def inside(t, k):                       # a view at element shift + k of a buffer of sevens, odd strides
+        big = torch.full((A, N + 5 + k), 7.0, device="cuda")
+        view = big[:, (shift + k) % 4:(shift + k) % 4 + N]
+        view.copy_(t)
+        return big, view
+
+    acfg = gs.adam_cfg(LR, RHO, 3)
+    ref = both_paths(x, frame, cfg, target, True, True, step=3, seed=n)
+    assert_same(*ref)
+    out = []
+    for fused in (False, True):
+        (bx, xs), (bm, ms), (bv, vs), (_, ws) = (inside(t, k) for k, t in enumerate((x, m, v, w)))
+        ks = torch.cat([mask.new_zeros(shift), mask])[shift:]
+        buf = gs.rasterize(xs, frame, cfg)
+        loss = torch.zeros(1, device="cuda")
+        if fused:
+            gs.render_bwd_adam(xs, frame, cfg, buf, ms, vs, ws, ks, acfg, gs.LOSS_L1, target, loss)
+        else:
+            _, g = inside(torch.zeros_like(x), 3)
+            gs.render_bwd(xs, frame, cfg, buf, g, gs.LOSS_L1, target, loss)
+            gs.adam_admm(xs, g, ms, vs, ws, ks, acfg)
+        out.append((xs, ms, vs, loss))
+        for big, view in ((bx, xs), (bm, ms), (bv, vs)):
+            kept = view.clone()
+            view.fill_(7.0)
+            assert (big == 7.0).all()
+            view.copy_(kept)
+    assert_same(out[0], ref[0])
+    assert_same(out[1], ref[0])
