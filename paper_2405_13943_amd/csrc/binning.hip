@@ -1232,7 +1232,11 @@ __global__ __launch_bounds__(BLOCK) void k_bin_small(const uint4* __restrict__ m
 // it waits on loads and launches; strips are cut so that a little less than
 // one workgroup a CU reads the records (a frame of 20k records, 1,900 tiles:
 // 39 us with 512 strips, 33 with 192 or 128; 65k, 6,700 tiles: 112, 92, 96).
-// All bins of the first took 53 us in the pipeline's 11 launches, 33 here in 4.
+// The records' first pairs are written by workgroups ahead of k_bin_tiles',
+// beside which they finish: ahead of the strips they were that launch's last
+// (33 -> 31 us; 13k records in each of two views of 1,900 tiles 36 -> 31; but
+// 20k in each of two of 8,160, where the tiles are the time, 75 -> 78).
+// All bins of the first took 53 us in the pipeline's 11 launches, 31 here in 4.
 constexpr int kStripBlock = 1024, kStripHold = 4096;        // threads; longest list collected in LDS
 constexpr int64_t kStrips = 192;                            // about as many strips
 constexpr int64_t kStripRecords = 65536, kStripTiles = 32768;   // most records and tiles
@@ -1253,20 +1257,13 @@ __device__ __forceinline__ uint32_t strip_columns(const uint4& m, uint32_t c0, u
 __global__ __launch_bounds__(kStripBlock, 8) void k_bin_strips(const uint4* __restrict__ meta, gs_frame frame,
                                                             uint64_t capacity, uint64_t* __restrict__ key,
                                                             uint32_t* __restrict__ cols, StripInfo* __restrict__ info,
-                                                            int wide, int strip_wgs, uint32_t* __restrict__ longq,
-                                                            uint32_t* __restrict__ pair_off,
-                                                            uint32_t* __restrict__ counters) {
+                                                            int wide, int strip_wgs, uint32_t* __restrict__ longq) {
     __shared__ uint64_t s_key[kStripHold];
     __shared__ uint32_t s_cols[kStripHold];
     __shared__ uint32_t s_wave[2 * kStripBlock / kWave];
     __shared__ uint32_t s_count;
     const uint32_t nrec = uint32_t(frame.n_records), t = threadIdx.x;
-    if (int(blockIdx.x) >= strip_wgs) {
-        if (int(blockIdx.x) == strip_wgs && t == 0) *longq = 0u;
-        write_first_pairs<kStripBlock>(meta, nrec, blockIdx.x - uint32_t(strip_wgs), capacity, pair_off, counters,
-                                       reinterpret_cast<VisPairs*>(s_wave));
-        return;
-    }
+    if (blockIdx.x == 0 && t == 0) *longq = 0u;
     int strip = int(blockIdx.x);                // the jobs' strips one after the other
     for (int j = 0; j < frame.n_jobs; j++) {
         const gs_job& job = frame.jobs[j];
@@ -1343,13 +1340,20 @@ __global__ __launch_bounds__(kBinTileBlock) void k_bin_tiles(const uint4* __rest
                                                              const uint32_t* __restrict__ cols,
                                                              const StripInfo* __restrict__ info, int wide,
                                                              uint32_t* __restrict__ vals, uint2* __restrict__ ranges,
-                                                             uint32_t* __restrict__ longq) {
+                                                             uint32_t* __restrict__ longq, int first_wgs,
+                                                             uint32_t* __restrict__ pair_off,
+                                                             uint32_t* __restrict__ counters) {
     constexpr int BLOCK = kBinTileBlock, CAP = kBinTileList;
     __shared__ uint64_t sk[CAP];
     __shared__ uint32_t s_wave[2 * BLOCK / kWave];
     __shared__ uint32_t s_count;
     const uint32_t t = threadIdx.x;
-    const int tile = int(blockIdx.x);
+    if (int(blockIdx.x) < first_wgs) {
+        write_first_pairs<BLOCK>(meta, uint32_t(frame.n_records), blockIdx.x, capacity, pair_off, counters,
+                                 reinterpret_cast<VisPairs*>(s_wave));
+        return;
+    }
+    const int tile = int(blockIdx.x) - first_wgs;
     const gs_job& job = frame.jobs[job_of_tile(frame.jobs, frame.n_jobs, tile)];
     const uint32_t lt = uint32_t(tile - job.tile0);
     const uint32_t tx = lt % uint32_t(job.tiles_x), ty = lt / uint32_t(job.tiles_x);
@@ -1530,12 +1534,12 @@ hipError_t launch_bin_sort(const gs_frame& f, const gs_raster_cfg& cfg, const ui
         StripInfo* info = reinterpret_cast<StripInfo*>(w.hist);
         uint32_t* cols = reinterpret_cast<uint32_t*>(w.key[1]);
         const int cols_per = int((nt + kStrips - 1) / kStrips), strip_wgs = int(std::min<int64_t>(nt, 2 * kStrips));
-        GS_LAUNCH("k_bin_strips", k_bin_strips,
-                  dim3(unsigned(strip_wgs + (f.n_records + 4 * kStripBlock - 1) / (4 * kStripBlock))),
-                  dim3(kStripBlock), 0, s, meta, f, bins.capacity, w.key[0], cols, info, cols_per, strip_wgs, w.longq,
-                  bins.pair_off, bins.counters);
-        GS_LAUNCH("k_bin_tiles", k_bin_tiles, dim3(unsigned(nt)), dim3(kBinTileBlock), 0, s, meta, f, bins.capacity,
-                  w.key[0], cols, info, cols_per, bins.vals, ranges, w.longq);
+        GS_LAUNCH("k_bin_strips", k_bin_strips, dim3(unsigned(strip_wgs)), dim3(kStripBlock), 0, s, meta, f,
+                  bins.capacity, w.key[0], cols, info, cols_per, strip_wgs, w.longq);
+        const int first_wgs = int((f.n_records + 4 * kBinTileBlock - 1) / (4 * kBinTileBlock));
+        GS_LAUNCH("k_bin_tiles", k_bin_tiles, dim3(unsigned(first_wgs + nt)), dim3(kBinTileBlock), 0, s, meta, f,
+                  bins.capacity, w.key[0], cols, info, cols_per, bins.vals, ranges, w.longq, first_wgs, bins.pair_off,
+                  bins.counters);
         // the plan's counts take the strips' place
         if (plan.order) GS_LAUNCH("k_tile_plan", k_tile_plan, dim3(unsigned(plan.blocks)), dim3(1024), 0, s, plan);
         GS_LAUNCH("k_tile_sort_long", k_tile_sort_long,
