@@ -110,7 +110,7 @@ class Slot:
 
 class RenderServer:
     MAX_TRIES = 4      # overflowing launches of one request before the server gives up
-    GATHER = 100e-6    # run_open_loop: an arrival due this soon is waited for (a launch takes longer)
+    GATHER = 100e-6    # run_open_loop: longest wait of an arrival for others of its batch (a launch takes longer)
 
     def __init__(self, params: torch.Tensor, cfg: gs.GsRasterCfg, hbm_budget: float = 32e9, n_slots: int = 3,
                  max_batch: int = 16, resolutions=None, pair_headroom: float = 1.5, spatial_order: bool = True):
@@ -234,6 +234,14 @@ class RenderServer:
 
     def poll(self, now):
         """Retire finished batches, then fill free slots from the queue."""
+        self._retire()
+        for s in self.slots:
+            if s.batch is None and self.queue:
+                batch = self._admit(s)
+                if batch:
+                    self._launch(s, batch, now)
+
+    def _retire(self):
         for s in self.slots:
             if s.batch is not None and s.event.query():
                 st = int(s.arena.counters_host[gs.CTR_STATUS].item())
@@ -259,11 +267,6 @@ class RenderServer:
                         r.done = t
                     self.finished.extend(s.batch)
                 s.batch, s.event = None, None
-        for s in self.slots:
-            if s.batch is None and self.queue:
-                batch = self._admit(s)
-                if batch:
-                    self._launch(s, batch, now)
 
     def idle(self):
         return not self.queue and all(s.batch is None for s in self.slots)
@@ -272,8 +275,10 @@ class RenderServer:
         """Serve requests arriving at the given times (seconds from start).
         Submitting and launching share this thread, and a launch keeps it for
         some 200 us: what falls due meanwhile would wait for it and then for
-        a launch of its own, so an arrival due within ``GATHER`` seconds of
-        a submission is waited for and joins its batch.
+        a launch of its own.  So while a slot is free and the queue does not
+        fill a batch, a launch is held for arrivals due within ``GATHER``
+        seconds of the first one submitted since the last launch; finished
+        batches are retired meanwhile.
         Returns latency / throughput statistics over requests arriving after
         ``warmup``; the images of request ids in ``keep`` are kept (copied out
         of the pinned pool), all others are released when done."""
@@ -283,17 +288,20 @@ class RenderServer:
         nxt = 0
         reqs = []
         n_done = 0
+        hold = None                         # until when the launch is held; None: nothing submitted since the last
         while nxt < len(arrivals) or not self.idle():
             now = time.perf_counter() - t0
-            due = now                       # moved on by GATHER past each request submitted
-            while nxt < len(arrivals) and arrivals[nxt] <= due:
-                while now < arrivals[nxt]:
-                    now = time.perf_counter() - t0
-                r = self.submit(nxt, cams[nxt], t0 + arrivals[nxt])
-                reqs.append(r)
+            while nxt < len(arrivals) and arrivals[nxt] <= now:
+                if hold is None:
+                    hold = arrivals[nxt] + self.GATHER
+                reqs.append(self.submit(nxt, cams[nxt], t0 + arrivals[nxt]))
                 nxt += 1
-                due = max(now, arrivals[nxt - 1] + self.GATHER)
-            self.poll(now)
+            if hold is not None and now < hold and nxt < len(arrivals) and arrivals[nxt] <= hold \
+                    and len(self.queue) < self.max_batch and any(s.batch is None for s in self.slots):
+                self._retire()
+            else:
+                self.poll(now)
+                hold = None
             for r in self.finished[n_done:]:
                 if r.rid in keep:
                     self.kept[r.rid] = r.image.clone()
