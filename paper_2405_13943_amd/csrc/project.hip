@@ -711,28 +711,79 @@ __global__ __launch_bounds__(kAccBlock, sizeof(T) == 4 ? 4 : 1) void k_project_b
         }
 }
 
-// Column of the i-th Gaussian (from 0) that no job covers, for jobs over
-// disjoint ranges in any order: the smallest c with
-// c = i + (columns of the jobs that start at or before c), reached by
-// iterating that map from c = i (it never passes the answer, and between two
-// steps at least one more job is counted, so n_jobs + 1 steps end it).
-__device__ inline int64_t uncovered_column(const gs_frame& frame, int64_t i) {
-    int64_t c = i;
-    for (int it = 0; it <= frame.n_jobs; it++) {
-        int64_t next = i;
-        for (int j = 0; j < frame.n_jobs; j++)
-            if (frame.jobs[j].g0 <= c) next += frame.jobs[j].g1 - frame.jobs[j].g0;
-        if (next == c) break;
-        c = next;
+// The columns that no job covers, for jobs over disjoint ranges in any order;
+// made and used by a whole workgroup.  Up to kMost jobs are put in order in
+// LDS, each with the uncovered columns before its start and the columns
+// covered up to its end: the i-th uncovered column (from 0) is i plus what is
+// covered up to the last job that has at most i before it.  (Without the
+// table, a search that counts every job again for each one passed: 64 blocks
+// of 500 padded by 32, SH 2, took 196 us a backward and 188 an update, 61 and
+// 91 with a thread per column of the whole store, 52 and 56 as it is; 128 of
+// 5,000 1,615 and 1,745, 496 and 575, 468 and 515.)
+struct UncoveredColumns {
+    static constexpr int kMost = 512;
+    const gs_frame& frame;
+    const int64_t (*table)[2];
+    int jobs = 0;               // in the table; -1: more than it holds
+    // table_: LDS; ends with a barrier
+    __device__ UncoveredColumns(const gs_frame& f, int64_t (*table_)[2]) : frame(f), table(table_) {
+        if (f.n_jobs > kMost) {         // uniform
+            jobs = -1;
+            return;
+        }
+        for (int base = 0; base < f.n_jobs; base += int(blockDim.x)) {
+            const int t = base + int(threadIdx.x);
+            const bool own = t < f.n_jobs;
+            const int64_t g0 = own ? f.jobs[t].g0 : 0, len = own ? f.jobs[t].g1 - g0 : 0;
+            int rank = 0;
+            int64_t before = 0;
+            jobs = 0;
+            for (int j = 0; j < f.n_jobs; j++) {
+                const int64_t a = f.jobs[j].g0, n = f.jobs[j].g1 - a;
+                if (n <= 0) continue;
+                jobs++;
+                if (a < g0 || (a == g0 && j < t)) {
+                    rank++;
+                    before += n;
+                }
+            }
+            if (len > 0) {
+                table_[rank][0] = g0 - before;
+                table_[rank][1] = before + len;
+            }
+        }
+        __syncthreads();
     }
-    return c;
-}
+    __device__ int64_t operator()(int64_t i) const {
+        if (jobs < 0) {
+            // the smallest c with c = i + (columns of the jobs that start at or
+            // before c): each pass counts on from where it has got, never past it
+            int64_t c = i;
+            for (int it = 0; it <= frame.n_jobs; it++) {
+                int64_t next = i;
+                for (int j = 0; j < frame.n_jobs; j++)
+                    if (frame.jobs[j].g0 <= (next > c ? next : c)) next += frame.jobs[j].g1 - frame.jobs[j].g0;
+                if (next == c) break;
+                c = next;
+            }
+            return c;
+        }
+        int lo = 0, hi = jobs;          // jobs with at most i uncovered columns before them
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (table[mid][0] <= i) lo = mid + 1; else hi = mid;
+        }
+        return i + (lo > 0 ? table[lo - 1][1] : 0);
+    }
+};
 
-// workgroups of 256 per plane of n_unc uncovered columns (they stride over
-// the rest: the whole grid stays far below 2^32 threads)
+// workgroups of 256 per plane of n_unc uncovered columns: up to 64, some
+// 3,800 over the planes of SH 3, which stride over the rest (each makes the
+// table again: 64 blocks of 2,000 padded by 2,000, SH 2, 271 us a backward
+// with a workgroup for every 256 columns, 150 so)
 __host__ __device__ inline unsigned uncovered_blocks(int64_t n_unc) {
     const int64_t b = (n_unc + 255) / 256;
-    return unsigned(b < 32768 ? b : 32768);
+    return unsigned(b < 64 ? b : 64);
 }
 
 // Fused projection backward + Adam/ADMM for jobs over disjoint Gaussian
@@ -859,8 +910,13 @@ __global__ __launch_bounds__(kFusedBlock) void k_project_bwd_adam(
         return;
     }
     if (adam_skipped(status)) return;   // uniform over the grid: no wavefront reaches the barrier
+    __shared__ __align__(16) float s_geo[11][kFusedBlock];
+    __shared__ __align__(16) float s_Y[NK][kFusedBlock];
+    __shared__ __align__(16) float s_dc[3][kFusedBlock];
     const unsigned block = blockIdx.x - loss_blocks;
     if (block >= rec_blocks) {          // uniform: a plane of 256 uncovered columns
+        static_assert(sizeof(s_geo) >= sizeof(int64_t[UncoveredColumns::kMost][2]), "the table takes their place");
+        const UncoveredColumns column(frame, reinterpret_cast<int64_t (*)[2]>(&s_geo[0][0]));
         const unsigned per_plane = uncovered_blocks(n_unc);
         const unsigned b = block - rec_blocks;
         const int a = int(b / per_plane);
@@ -868,7 +924,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_project_bwd_adam(
         float fin = 0.f;
         for (int64_t i = int64_t(b % per_plane) * kFusedBlock + threadIdx.x; i < n_unc;
              i += int64_t(per_plane) * kFusedBlock) {
-            const int64_t gu = uncovered_column(frame, i);
+            const int64_t gu = column(i);
             if (gu >= n) continue;
             float xv = X[a * sx + gu], mv = M[a * sm + gu], vv = V[a * sv + gu];
             const float wv = PEN ? Wp[a * sw + gu] : 0.f;
@@ -881,9 +937,6 @@ __global__ __launch_bounds__(kFusedBlock) void k_project_bwd_adam(
         adam_flag(status, fin);
         return;
     }
-    __shared__ __align__(16) float s_geo[11][kFusedBlock];
-    __shared__ __align__(16) float s_Y[NK][kFusedBlock];
-    __shared__ __align__(16) float s_dc[3][kFusedBlock];
     const int t = threadIdx.x;
     const int64_t r0 = int64_t(block) * kFusedBlock;
     const int64_t r = r0 + t;
@@ -937,8 +990,10 @@ __global__ __launch_bounds__(kFusedBlock) void k_project_bwd_adam(
 template <typename T>
 __global__ __launch_bounds__(256) void k_zero_uncovered(int64_t n, int64_t n_unc, gs_frame frame,
                                                         T* __restrict__ grad, int64_t gstride) {
+    __shared__ int64_t s_table[UncoveredColumns::kMost][2];
+    const UncoveredColumns column(frame, s_table);
     for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n_unc; i += int64_t(gridDim.x) * blockDim.x) {
-        const int64_t g = uncovered_column(frame, i);
+        const int64_t g = column(i);
         if (g < n) grad[int64_t(blockIdx.y) * gstride + g] = T(0);
     }
 }

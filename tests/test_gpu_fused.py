@@ -187,3 +187,31 @@ def test_planes_of_any_alignment(n, shift):
             view.copy_(kept)
     assert_same(out[0], ref[0])
     assert_same(out[1], ref[0])
+
+
+@pytest.mark.parametrize("jobs", [64, 257, 512, 513])
+@pytest.mark.parametrize("order", ["ascending", "descending", "shuffled"])
+def test_columns_outside_many_jobs(jobs, order):
+    """As above with the job counts around a workgroup's width and the 512 that
+    its table holds: ranges of 0 to 6 columns with gaps of 0 to 3."""
+    rng = np.random.default_rng(jobs)
+    lens, gaps = rng.integers(0, 7, jobs), rng.integers(0, 4, jobs + 1)
+    starts = np.cumsum(gaps[:-1] + np.concatenate([[0], lens[:-1]]))
+    n = int(starts[-1] + lens[-1] + gaps[-1])
+    at = {"ascending": np.arange(jobs), "descending": np.arange(jobs)[::-1], "shuffled": rng.permutation(jobs)}[order]
+    x = torch.from_numpy(scenes.gaussians(n, 1, 7, [-0.3, -0.3, -0.3], [0.3, 0.3, 0.3], -2.0, 0.3)).cuda()
+    cam = scenes.look_at([0.0, 0.0, 3.0], [0, 0, 0], 16, 8, 15.0, 15.0)
+    cfg = gs.raster_cfg((16, 16))
+    frame = gs.Frame([cam], [gs.JobSpec(0, int(starts[k]), int(starts[k] + lens[k]), 1.0) for k in at], cfg)
+    assert frame.jobs_disjoint and frame.n_records < n
+    dl = torch.randn(3 * frame.n_pixels, generator=torch.Generator().manual_seed(4)).cuda()
+    buf = gs.rasterize(x, frame, cfg)
+    grad = torch.full_like(x, float("nan"))
+    gs.render_bwd(x, frame, cfg, buf, grad, gs.LOSS_EXTERNAL, dl)
+    covered = torch.zeros(n, dtype=torch.bool, device="cuda")
+    for a, k in zip(starts, lens):
+        covered[a:a + k] = True
+    assert torch.isfinite(grad).all() and (grad[:, ~covered] == 0).all() and (grad[:, covered] != 0).any()
+    a, b = both_paths(x, frame, cfg, dl, True, True, step=4, mode=gs.LOSS_EXTERNAL, seed=9)
+    assert_same(a, b)
+    assert not torch.equal(a[0][:, ~covered], x[:, ~covered])
