@@ -1057,11 +1057,12 @@ constexpr int kSmallList = 2048, kSmallListWide = 8192;   // most records of a j
 constexpr int64_t kSmallWork = 12 << 20, kSmallWorkWide = 4 << 20;     // most tiles x records
 
 // pairs of a record (rectangle m.z, m.w of tiles) in tiles before (c0, ty);
-// inside: it has some in tiles c0 to c1 of row ty
-__device__ __forceinline__ uint32_t pairs_before(const uint4& m, uint32_t c0, uint32_t c1, uint32_t ty, bool& inside) {
+// inside: it has some in tiles c0 to c1 of rows ty to ty1
+__device__ __forceinline__ uint32_t pairs_before(const uint4& m, uint32_t c0, uint32_t c1, uint32_t ty, uint32_t ty1,
+                                                 bool& inside) {
     const uint32_t x0 = m.z & 0xffffu, y0 = m.z >> 16, x1 = m.w & 0xffffu, y1 = m.w >> 16;
     const uint32_t w = x1 - x0 + 1u;
-    inside = c1 >= x0 && c0 <= x1 && ty >= y0 && ty <= y1;
+    inside = c1 >= x0 && c0 <= x1 && ty1 >= y0 && ty <= y1;
     if (ty < y0) return 0u;
     if (ty > y1) return w * (y1 - y0 + 1u);
     return w * (ty - y0) + (c0 > x0 ? min(c0 - x0, w) : 0u);
@@ -1138,7 +1139,7 @@ __device__ inline uint32_t collect_truncated(const uint4* __restrict__ meta, uin
         if (n > 0u && i < r0) before += min(n, left);
         else if (n > 0u && i < r1) {
             bool inside;
-            const uint32_t k = pairs_before(m, tx, tx, ty, inside);
+            const uint32_t k = pairs_before(m, tx, tx, ty, ty, inside);
             before += min(k, left);
             if (inside && k < left) collect(m, i);
         }
@@ -1205,7 +1206,7 @@ __global__ __launch_bounds__(BLOCK) void k_bin_small(const uint4* __restrict__ m
             if (i < r0) before += n;
             else if (i < r1) {
                 bool inside;
-                before += pairs_before(m[k], tx, tx, ty, inside);
+                before += pairs_before(m[k], tx, tx, ty, ty, inside);
                 if (inside) collect(m[k], i);
             }
         }
@@ -1224,9 +1225,10 @@ __global__ __launch_bounds__(BLOCK) void k_bin_small(const uint4* __restrict__ m
 }
 
 // Frames of somewhat more records: the same in two launches.  k_bin_strips: a
-// workgroup reads all records for a strip (`wide` tiles of one row) and leaves
-// those that meet it (key and columns) in a list that starts where the strip's
-// pairs will, in closed form again; the list is no longer than they are.
+// workgroup reads all records for a strip (`wide` tiles of one row, or the whole
+// rows of a narrow view that `wide` tiles hold) and leaves those that meet it
+// (key and rectangle) in a list that starts where the strip's pairs will, in
+// closed form again; the list is no longer than they are.
 // k_bin_tiles: each tile's workgroup reads its strip's list instead of all
 // records; a list too long for its LDS is left for k_tile_sort_long.  All of
 // it waits on loads and launches; strips are cut so that a little less than
@@ -1242,103 +1244,165 @@ constexpr int64_t kStrips = 192;                            // about as many str
 constexpr int64_t kStripRecords = 65536, kStripTiles = 32768;   // most records and tiles
 static_assert(kStripRecords * kStripTiles < (int64_t(1) << 32), "sums of pairs fit 32 bits");
 
+// for each tile: its strip's list and its place in the strip
 struct StripInfo {
-    uint32_t first, count;      // the list, and pairs in earlier tiles
+    uint32_t first, count;      // the list; first also: pairs in tiles before the strip
+    uint32_t place;             // column | row << 16
     uint32_t overflow;          // the frame has more pairs than capacity: no lists
-    uint32_t reserved;
 };
 
-// a record's columns in the strip [c0, c1]: first (below kStripTiles) and how many
-__device__ __forceinline__ uint32_t strip_columns(const uint4& m, uint32_t c0, uint32_t c1) {
-    const uint32_t x0 = max(m.z & 0xffffu, c0), x1 = min(m.w & 0xffffu, c1);
-    return x0 | (x1 - x0 + 1u) << 16;
+// the strip of a view's tiles: columns [c0, c1], rows [y0, y1]
+struct Strip {
+    uint32_t c0, c1, y0, y1;
+};
+static_assert((kStripTiles + kStrips - 1) / kStrips < 256, "a strip's rectangles fit four bytes");
+// a / b for a below 2^20 and b > 0: the quotient of a + 1/2 keeps 1 / 2b from
+// any whole number, the reciprocal's and the product's rounding less
+__device__ __forceinline__ int small_div(int a, int b) {
+    return int((float(a) + 0.5f) * __builtin_amdgcn_rcpf(float(b)));
+}
+
+// strips of a view: at most two for every `wide` tiles, and one more
+struct StripGrid {
+    int per_row, rows, strips;      // strips across the view, rows of a strip, strips in all
+    __device__ StripGrid(const gs_job& job, int wide)
+        : per_row(small_div(job.tiles_x + wide - 1, wide)), rows(max(1, small_div(wide, job.tiles_x))),
+          strips(small_div(job.tiles_y + rows - 1, rows) * per_row) {}
+};
+
+// Strip i of the frame, the jobs' strips one after the other (wavefront-uniform;
+// false past the last).  More than two jobs are counted a lane each: one after
+// the other they took half a microsecond apiece.
+__device__ inline bool find_strip(const gs_frame& frame, int wide, int i, int& job, Strip& s) {
+    job = 0;
+    if (frame.n_jobs <= 2) {
+        if (frame.n_jobs == 2) {
+            const int first = StripGrid(frame.jobs[0], wide).strips;
+            job = i >= first ? 1 : 0;
+            i -= job ? first : 0;
+        }
+    } else {
+        int before = 0;
+        for (int j0 = 0;; j0 += kWave) {
+            if (j0 >= frame.n_jobs) return false;
+            const int j = j0 + lane_id();
+            const int strips = j < frame.n_jobs ? StripGrid(frame.jobs[j], wide).strips : 0;
+            const int end = before + int(wave_incl_scan_dpp(uint32_t(strips)));
+            const uint64_t after = __ballot(end > i);
+            if (after) {
+                const int l = __ffsll((long long)after) - 1;
+                job = j0 + l;
+                i -= __builtin_amdgcn_readlane(end - strips, l);
+                break;
+            }
+            before = __builtin_amdgcn_readlane(end, kWave - 1);
+        }
+    }
+    const gs_job& v = frame.jobs[job];
+    const StripGrid g(v, wide);
+    if (i >= g.strips) return false;
+    const int row = small_div(i, g.per_row);
+    s.c0 = uint32_t((i - row * g.per_row) * wide);
+    s.c1 = min(s.c0 + uint32_t(wide), uint32_t(v.tiles_x)) - 1u;
+    s.y0 = uint32_t(row * g.rows);
+    s.y1 = min(s.y0 + uint32_t(g.rows), uint32_t(v.tiles_y)) - 1u;
+    return true;
+}
+
+// a record's rectangle inside the strip: first column, columns, first row, rows, from the strip's corner
+__device__ __forceinline__ uint32_t strip_rect(const uint4& m, const Strip& s) {
+    const uint32_t x0 = max(m.z & 0xffffu, s.c0), x1 = min(m.w & 0xffffu, s.c1);
+    const uint32_t y0 = max(m.z >> 16, s.y0), y1 = min(m.w >> 16, s.y1);
+    return (x0 - s.c0) | (x1 - x0 + 1u) << 8 | (y0 - s.y0) << 16 | (y1 - y0 + 1u) << 24;
 }
 
 __global__ __launch_bounds__(kStripBlock, 8) void k_bin_strips(const uint4* __restrict__ meta, gs_frame frame,
                                                             uint64_t capacity, uint64_t* __restrict__ key,
-                                                            uint32_t* __restrict__ cols, StripInfo* __restrict__ info,
-                                                            int wide, int strip_wgs, uint32_t* __restrict__ longq) {
+                                                            uint32_t* __restrict__ rect, StripInfo* __restrict__ info,
+                                                            int wide, uint32_t* __restrict__ longq) {
     __shared__ uint64_t s_key[kStripHold];
-    __shared__ uint32_t s_cols[kStripHold];
+    __shared__ uint32_t s_rect[kStripHold];
     __shared__ uint32_t s_wave[2 * kStripBlock / kWave];
     __shared__ uint32_t s_count;
     const uint32_t nrec = uint32_t(frame.n_records), t = threadIdx.x;
     if (blockIdx.x == 0 && t == 0) *longq = 0u;
-    int strip = int(blockIdx.x);                // the jobs' strips one after the other
-    for (int j = 0; j < frame.n_jobs; j++) {
-        const gs_job& job = frame.jobs[j];
-        const int per_row = (job.tiles_x + wide - 1) / wide;
-        const uint32_t r0 = uint32_t(job.rec0), r1 = r0 + uint32_t(job.g1 - job.g0);
-        for (; strip < job.tiles_y * per_row; strip += strip_wgs) {
-            const uint32_t ty = uint32_t(strip / per_row), c0 = uint32_t(strip % per_row * wide);
-            const uint32_t c1 = min(c0 + uint32_t(wide), uint32_t(job.tiles_x)) - 1u;
-            uint32_t before = 0u, total = 0u;
-            __syncthreads();
-            if (t == 0) s_count = 0u;
-            __syncthreads();
-            constexpr int kAhead = 4;
-            for (uint32_t i0 = t; i0 < nrec; i0 += kAhead * kStripBlock) {
-                uint4 m[kAhead];
+    int j;
+    Strip st;
+    if (!find_strip(frame, wide, int(blockIdx.x), j, st)) return;   // uniform
+    const gs_job& job = frame.jobs[j];
+    const uint32_t r0 = uint32_t(job.rec0), r1 = r0 + uint32_t(job.g1 - job.g0);
+    uint32_t before = 0u, total = 0u;
+    if (t == 0) s_count = 0u;
+    __syncthreads();
+    auto read = [&](uint32_t y1) {      // st.y1; the same as st.y0 for most frames' strips, which saves tests
+        constexpr int kAhead = 4;
+        for (uint32_t i0 = t; i0 < nrec; i0 += kAhead * kStripBlock) {
+            uint4 m[kAhead];
 #pragma unroll
-                for (int k = 0; k < kAhead; k++) {
-                    const uint32_t i = i0 + uint32_t(k) * kStripBlock;
-                    m[k] = meta[i < nrec ? i : i0];
-                }
+            for (int k = 0; k < kAhead; k++) {
+                const uint32_t i = i0 + uint32_t(k) * kStripBlock;
+                m[k] = meta[i < nrec ? i : i0];
+            }
 #pragma unroll
-                for (int k = 0; k < kAhead; k++) {
-                    const uint32_t i = i0 + uint32_t(k) * kStripBlock;
-                    const uint32_t n = i < nrec ? meta_tiles(m[k].y) : 0u;
-                    if (n == 0u) continue;
-                    total += n;
-                    if (i < r0) before += n;
-                    else if (i < r1) {
-                        bool inside;
-                        before += pairs_before(m[k], c0, c1, ty, inside);
-                        if (inside) {
-                            const uint32_t at = atomicAdd(&s_count, 1u);
-                            if (at < uint32_t(kStripHold)) {
-                                s_key[at] = uint64_t(m[k].x) << 32 | i;
-                                s_cols[at] = strip_columns(m[k], c0, c1);
-                            }
+            for (int k = 0; k < kAhead; k++) {
+                const uint32_t i = i0 + uint32_t(k) * kStripBlock;
+                const uint32_t n = i < nrec ? meta_tiles(m[k].y) : 0u;
+                if (n == 0u) continue;
+                total += n;
+                if (i < r0) before += n;
+                else if (i < r1) {
+                    bool inside;
+                    before += pairs_before(m[k], st.c0, st.c1, st.y0, y1, inside);
+                    if (inside) {
+                        const uint32_t at = atomicAdd(&s_count, 1u);
+                        if (at < uint32_t(kStripHold)) {
+                            s_key[at] = uint64_t(m[k].x) << 32 | i;
+                            s_rect[at] = strip_rect(m[k], st);
                         }
                     }
                 }
             }
-            total = block_sum_u32<kStripBlock>(total, s_wave);
-            before = block_sum_u32<kStripBlock>(before, s_wave);    // its barriers: every record is collected
-            const uint32_t count = s_count;
-            const bool overflow = uint64_t(total) > capacity;       // uniform
-            if (!overflow && count <= uint32_t(kStripHold)) {
-                for (uint32_t i = t; i < count; i += kStripBlock) {
-                    key[before + i] = s_key[i];
-                    cols[before + i] = s_cols[i];
-                }
-            } else if (!overflow) {                                 // longer than the LDS holds: another pass
-                __syncthreads();
-                if (t == 0) s_count = 0u;
-                __syncthreads();
-                for (uint32_t i = r0 + t; i < r1; i += kStripBlock) {
-                    const uint4 m = meta[i];
-                    bool inside = false;
-                    if (meta_tiles(m.y) > 0u) pairs_before(m, c0, c1, ty, inside);
-                    if (inside) {
-                        const uint32_t at = before + atomicAdd(&s_count, 1u);
-                        key[at] = uint64_t(m.x) << 32 | i;
-                        cols[at] = strip_columns(m, c0, c1);
-                    }
-                }
-            }
-            if (t == 0) info[job.tile0 + int(ty) * job.tiles_x + int(c0)] = {before, count, overflow ? 1u : 0u, 0u};
         }
-        strip -= job.tiles_y * per_row;
+    };
+    if (st.y0 == st.y1) read(st.y0);    // uniform
+    else read(st.y1);
+    total = block_sum_u32<kStripBlock>(total, s_wave);
+    before = block_sum_u32<kStripBlock>(before, s_wave);    // its barriers: every record is collected
+    const uint32_t count = s_count;
+    const bool overflow = uint64_t(total) > capacity;       // uniform
+    if (!overflow && count <= uint32_t(kStripHold)) {
+        for (uint32_t i = t; i < count; i += kStripBlock) {
+            key[before + i] = s_key[i];
+            rect[before + i] = s_rect[i];
+        }
+    } else if (!overflow) {                                 // longer than the LDS holds: another pass
+        __syncthreads();
+        if (t == 0) s_count = 0u;
+        __syncthreads();
+        for (uint32_t i = r0 + t; i < r1; i += kStripBlock) {
+            const uint4 m = meta[i];
+            bool inside = false;
+            if (meta_tiles(m.y) > 0u) pairs_before(m, st.c0, st.c1, st.y0, st.y1, inside);
+            if (inside) {
+                const uint32_t at = before + atomicAdd(&s_count, 1u);
+                key[at] = uint64_t(m.x) << 32 | i;
+                rect[at] = strip_rect(m, st);
+            }
+        }
+    }
+    const uint32_t w = st.c1 - st.c0 + 1u;
+    for (uint32_t i = t; i < w * (st.y1 - st.y0 + 1u); i += kStripBlock) {
+        const uint32_t y = uint32_t(small_div(int(i), int(w))), x = i - y * w;
+        info[job.tile0 + int(st.y0 + y) * job.tiles_x + int(st.c0 + x)] = {before, count, x | y << 16,
+                                                                           overflow ? 1u : 0u};
     }
 }
 
 constexpr int kBinTileBlock = 256, kBinTileList = 2048;
 __global__ __launch_bounds__(kBinTileBlock) void k_bin_tiles(const uint4* __restrict__ meta, gs_frame frame,
                                                              uint64_t capacity, const uint64_t* __restrict__ key,
-                                                             const uint32_t* __restrict__ cols,
-                                                             const StripInfo* __restrict__ info, int wide,
+                                                             const uint32_t* __restrict__ rect,
+                                                             const StripInfo* __restrict__ info,
                                                              uint32_t* __restrict__ vals, uint2* __restrict__ ranges,
                                                              uint32_t* __restrict__ longq, int first_wgs,
                                                              uint32_t* __restrict__ pair_off,
@@ -1357,7 +1421,8 @@ __global__ __launch_bounds__(kBinTileBlock) void k_bin_tiles(const uint4* __rest
     const gs_job& job = frame.jobs[job_of_tile(frame.jobs, frame.n_jobs, tile)];
     const uint32_t lt = uint32_t(tile - job.tile0);
     const uint32_t tx = lt % uint32_t(job.tiles_x), ty = lt / uint32_t(job.tiles_x);
-    const StripInfo strip = info[tile - int(tx) % wide];
+    const StripInfo strip = info[tile];
+    const uint32_t rx = strip.place & 0xffffu, ry = strip.place >> 16;
     uint32_t before = 0u, n = 0u;
     for (int pass = 0; pass < 2; pass++) {
         // keys to LDS; a list too long for it goes to vals unsorted in a second pass
@@ -1382,14 +1447,17 @@ __global__ __launch_bounds__(kBinTileBlock) void k_bin_tiles(const uint4* __rest
 #pragma unroll
                 for (int k = 0; k < kAhead; k++) {
                     const uint32_t i = i0 + uint32_t(k) * BLOCK;
-                    c[k] = cols[strip.first + (i < strip.count ? i : i0)];
+                    c[k] = rect[strip.first + (i < strip.count ? i : i0)];
                 }
 #pragma unroll
                 for (int k = 0; k < kAhead; k++) {
-                    const uint32_t i = i0 + uint32_t(k) * BLOCK, x0 = c[k] & 0xffffu, w = c[k] >> 16;
+                    const uint32_t i = i0 + uint32_t(k) * BLOCK;
+                    const uint32_t x = c[k] & 0xffu, w = c[k] >> 8 & 0xffu, y = c[k] >> 16 & 0xffu, h = c[k] >> 24;
                     if (i >= strip.count) continue;
-                    if (tx > x0) left += min(tx - x0, w);
-                    if (tx - x0 < w) put(key[strip.first + i]);        // wraps below x0
+                    if (ry > y) left += w * min(ry - y, h);
+                    if (ry - y >= h) continue;                         // (wraps above y)
+                    if (rx > x) left += min(rx - x, w);
+                    if (rx - x < w) put(key[strip.first + i]);         // (wraps left of x)
                 }
             }
             if (pass == 0) before = strip.first + block_sum_u32<BLOCK>(left, s_wave);
@@ -1529,16 +1597,22 @@ hipError_t launch_bin_sort(const gs_frame& f, const gs_raster_cfg& cfg, const ui
     // 46 / 40; 20k, 256 tiles 33 / 35; 40k, 256 tiles 43 / 38; 60k, 475 tiles
     // 55 / 58; 20k, 1,900 tiles 33 / 53; 65k, 1,900 tiles 61 / 71; 65k, 6,700
     // tiles 92 / 114; 90k, 1,200 tiles 75 / 72; 90k, 6,700 tiles 156 / 134).
-    if (f.n_records <= std::min(kStripRecords, 16384 + 48 * nt) && nt > 0 && nt <= kStripTiles) {
+    // Of very few tiles, which then have lists longer than k_bin_tiles sorts, a
+    // record for each 2,048: 16k records, 1 tile 180 / 123; 4 tiles 111 / 95; 8
+    // tiles ZZZ / ZZZ; 16 tiles 35 / 53.  (Many views: 64 records each in 128
+    // of 16 tiles ...)
+    if (f.n_records <= std::min({kStripRecords, 16384 + 48 * nt, int64_t(kBinTileList) * nt}) && nt <= kStripTiles) {
         static_assert(sizeof(StripInfo) * kStripTiles <= sizeof(uint32_t) * 256 * kMaxGrid, "in the histograms' place");
         StripInfo* info = reinterpret_cast<StripInfo*>(w.hist);
-        uint32_t* cols = reinterpret_cast<uint32_t*>(w.key[1]);
-        const int cols_per = int((nt + kStrips - 1) / kStrips), strip_wgs = int(std::min<int64_t>(nt, 2 * kStrips));
-        GS_LAUNCH("k_bin_strips", k_bin_strips, dim3(unsigned(strip_wgs)), dim3(kStripBlock), 0, s, meta, f,
-                  bins.capacity, w.key[0], cols, info, cols_per, strip_wgs, w.longq);
+        uint32_t* rect = reinterpret_cast<uint32_t*>(w.key[1]);
+        const int per_strip = int((nt + kStrips - 1) / kStrips);
+        // a workgroup for every strip: at most two for every per_strip tiles, and one more for a view
+        const unsigned strip_wgs = unsigned(std::min<int64_t>(nt, 2 * kStrips + f.n_jobs));
+        GS_LAUNCH("k_bin_strips", k_bin_strips, dim3(strip_wgs), dim3(kStripBlock), 0, s, meta, f, bins.capacity,
+                  w.key[0], rect, info, per_strip, w.longq);
         const int first_wgs = int((f.n_records + 4 * kBinTileBlock - 1) / (4 * kBinTileBlock));
         GS_LAUNCH("k_bin_tiles", k_bin_tiles, dim3(unsigned(first_wgs + nt)), dim3(kBinTileBlock), 0, s, meta, f,
-                  bins.capacity, w.key[0], cols, info, cols_per, bins.vals, ranges, w.longq, first_wgs, bins.pair_off,
+                  bins.capacity, w.key[0], rect, info, bins.vals, ranges, w.longq, first_wgs, bins.pair_off,
                   bins.counters);
         // the plan's counts take the strips' place
         if (plan.order) GS_LAUNCH("k_tile_plan", k_tile_plan, dim3(unsigned(plan.blocks)), dim3(1024), 0, s, plan);

@@ -1041,3 +1041,29 @@ def test_bins_of_many_records(size, mean):
     assert frame.n_tiles == nt
     buf = _bins_of(frame, cfg, meta, max(mean * nt, len(rec)))
     _expect_bins(frame, buf, meta)
+
+
+@pytest.mark.parametrize("room", ["all", "half"])
+@pytest.mark.parametrize("jobs,n,tx,ty", [(1, 9000, 1, 2000), (3, 3000, 2, 200), (16, 300, 4, 100), (64, 200, 4, 5),
+                                          (65, 200, 4, 4), (200, 50, 3, 3), (130, 60, 17, 1), (2, 5000, 200, 3)])
+def test_bins_by_strips_of_many_and_narrow_views(jobs, n, tx, ty, room):
+    """Strips that hold several rows of a view, strips of up to 200 views,
+    views of different sizes; records over one tile to the whole view."""
+    rng = np.random.default_rng(n + tx)
+    cams = [scenes.look_at([0.0, 0.0, 3.0], [0, 0, 0], 16 * (tx + k % 3), 16 * (ty + k % 2), 100.0, 100.0)
+            for k in range(jobs)]
+    cfg = gs.raster_cfg((16, 16, -1))
+    frame = gs.Frame(cams, [gs.JobSpec(k, 0, n, 1.0) for k in range(jobs)], cfg)
+    meta = np.zeros((frame.n_records, 4), np.uint32)
+    for k in range(jobs):
+        j = frame.job(k)
+        x0, y0 = rng.integers(0, j.tiles_x, n), rng.integers(0, j.tiles_y, n)
+        x1 = np.minimum(x0 + rng.integers(0, 4, n), j.tiles_x - 1)
+        y1 = np.minimum(y0 + rng.integers(0, 12, n), j.tiles_y - 1)
+        x0[0], y0[0], x1[0], y1[0] = 0, 0, j.tiles_x - 1, j.tiles_y - 1
+        m = meta[j.rec0:j.rec0 + n]
+        m[:, 0] = (1.0 + rng.integers(0, 50, n) / 16.0).astype(np.float32).view(np.uint32)
+        m[:, 1], m[:, 2], m[:, 3] = (x1 - x0 + 1) * (y1 - y0 + 1), x0 | (y0 << 16), x1 | (y1 << 16)
+        m[rng.random(n) < 0.1] = [0xffffffff, 0, 0, 0]
+    pairs = int(meta[:, 1].sum())
+    _expect_bins(frame, _bins_of(frame, cfg, meta, 2 * pairs if room == "all" else pairs // 2), meta)
