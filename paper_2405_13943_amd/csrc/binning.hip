@@ -1228,7 +1228,10 @@ __global__ __launch_bounds__(BLOCK) void k_bin_small(const uint4* __restrict__ m
 // workgroup reads all records for a strip (`wide` tiles of one row, or the whole
 // rows of a narrow view that `wide` tiles hold) and leaves those that meet it
 // (key and rectangle) in a list that starts where the strip's pairs will, in
-// closed form again; the list is no longer than they are.
+// closed form again; the list is no longer than they are.  (Cut by rows alone,
+// narrow or many views had too many strips, us a call by rows / so: 4 views of
+// 16k records, 8 x 400 tiles, 1,600 / 392 strips, 114 / 46; 128 views of 500
+// records, 16 x 16 tiles, 2,048 / 256 strips, 195 / 74.)
 // k_bin_tiles: each tile's workgroup reads its strip's list instead of all
 // records; a list too long for its LDS is left for k_tile_sort_long.  All of
 // it waits on loads and launches; strips are cut so that a little less than
@@ -1597,10 +1600,10 @@ hipError_t launch_bin_sort(const gs_frame& f, const gs_raster_cfg& cfg, const ui
     // 46 / 40; 20k, 256 tiles 33 / 35; 40k, 256 tiles 43 / 38; 60k, 475 tiles
     // 55 / 58; 20k, 1,900 tiles 33 / 53; 65k, 1,900 tiles 61 / 71; 65k, 6,700
     // tiles 92 / 114; 90k, 1,200 tiles 75 / 72; 90k, 6,700 tiles 156 / 134).
-    // Of very few tiles, which then have lists longer than k_bin_tiles sorts, a
-    // record for each 2,048: 16k records, 1 tile 180 / 123; 4 tiles 111 / 95; 8
-    // tiles ZZZ / ZZZ; 16 tiles 35 / 53.  (Many views: 64 records each in 128
-    // of 16 tiles ...)
+    // The number of views makes no difference: 128 of 500 records and 16 tiles
+    // each 37 / 50, of 256 tiles 74 / 134.  Of very few tiles, whose lists are
+    // then longer than k_bin_tiles sorts, 2,048 records a tile: 16k records, 1
+    // tile 180 / 123; 4 tiles 113 / 94; 8 tiles 44 / 80; 16 tiles 35 / 53.
     if (f.n_records <= std::min({kStripRecords, 16384 + 48 * nt, int64_t(kBinTileList) * nt}) && nt <= kStripTiles) {
         static_assert(sizeof(StripInfo) * kStripTiles <= sizeof(uint32_t) * 256 * kMaxGrid, "in the histograms' place");
         StripInfo* info = reinterpret_cast<StripInfo*>(w.hist);
