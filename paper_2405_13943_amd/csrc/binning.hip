@@ -1055,6 +1055,7 @@ __global__ __launch_bounds__(kLongBlock) void k_tile_sort_long(const uint4* __re
 
 constexpr int kSmallList = 2048, kSmallListWide = 8192;   // most records of a job (and entries of a list) per form
 constexpr int64_t kSmallWork = 12 << 20, kSmallWorkWide = 4 << 20;     // most tiles x records
+constexpr int64_t kSmallRecords = 49152;                               // most records of all jobs
 
 // pairs of a record (rectangle m.z, m.w of tiles) in tiles before (c0, ty);
 // inside: it has some in tiles c0 to c1 of rows ty to ty1
@@ -1572,9 +1573,13 @@ hipError_t launch_bin_sort(const gs_frame& f, const gs_raster_cfg& cfg, const ui
     // a call with the plan, one launch / by strips: 200 records, 16 tiles
     // 8.9 / 15.5; 2k, 1,200 tiles 12.5 / 18.2; 2k, 3,072 tiles 16.8 / 20.8;
     // 2k, 6,700 tiles 24.5 / 24.9; the wide form 8k, 475 tiles 16.0 / 22.4;
-    // 5k, 1,200 tiles 22.2 / 20.4; 8k, 1,900 tiles 35.8 / 23.4.
+    // 5k, 1,200 tiles 22.2 / 20.4; 8k, 1,900 tiles 35.8 / 23.4.  And while one
+    // workgroup's walk over the records of all jobs is shorter than the
+    // pipeline, one launch / pipeline: 64k in 32 views of 1 tile 48 / 39, in 128
+    // 42 / 38, in 8 of 8 tiles 46 / 38; 128k in 64 views of 1 tile 75 / 40.
     const bool wide = f.g_max > kSmallList;
-    if (f.g_max <= kSmallListWide && nt > 0 && nt <= (wide ? kSmallWorkWide : kSmallWork) / f.n_records) {
+    if (f.g_max <= kSmallListWide && f.n_records <= kSmallRecords && nt > 0 &&
+        nt <= (wide ? kSmallWorkWide : kSmallWork) / f.n_records) {
         const int per = 4 * (wide ? 512 : 256);
         const dim3 grid(unsigned(nt + (f.n_records + per - 1) / per));
         if (wide)

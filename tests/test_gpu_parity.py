@@ -1045,10 +1045,13 @@ def test_bins_of_many_records(size, mean):
 
 @pytest.mark.parametrize("room", ["all", "half"])
 @pytest.mark.parametrize("jobs,n,tx,ty", [(1, 9000, 1, 2000), (3, 3000, 2, 200), (16, 300, 4, 100), (64, 200, 4, 5),
-                                          (65, 200, 4, 4), (200, 50, 3, 3), (130, 60, 17, 1), (2, 5000, 200, 3)])
+                                          (65, 200, 4, 4), (200, 50, 3, 3), (130, 60, 17, 1), (2, 5000, 200, 3),
+                                          (24, 2048, 1, 1), (25, 2000, 1, 1)])
 def test_bins_by_strips_of_many_and_narrow_views(jobs, n, tx, ty, room):
     """Strips that hold several rows of a view, strips of up to 200 views,
-    views of different sizes; records over one tile to the whole view."""
+    views of different sizes; records over one tile to the whole view; and
+    views of a few tiles on both sides of the 49,152 records up to which one
+    launch makes the bins."""
     rng = np.random.default_rng(n + tx)
     cams = [scenes.look_at([0.0, 0.0, 3.0], [0, 0, 0], 16 * (tx + k % 3), 16 * (ty + k % 2), 100.0, 100.0)
             for k in range(jobs)]
