@@ -490,7 +490,9 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ tke
 //               hold up a workgroup of waves, when there are too few tiles to
 //               hide it (us, waves / blocks: 1,536 tiles of mean 169 24 / 11,
 //               6,767 of 172 28 / 26, 9,126 of 147 21 / 32, 2,752 of 111
-//               12 / 12, 6,767 of 65 14 / 19); short lists by comparison;
+//               12 / 12, 6,767 of 65 14 / 19; all bins, 1,080 of 110 54 / 49,
+//               of 58 49 / 48, 2,542 of 58 51 / 52); short lists by
+//               comparison;
 //   kSortDense  one list per workgroup of 512, up to 4096 on chip.
 // k_tile_sort_long takes the longer lists, one large workgroup each, by
 // merging: every thread sorts E consecutive keys in registers (a sorting
@@ -502,7 +504,7 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ tke
 constexpr int kSortWaves = 0, kSortBlocks = 1, kSortDense = 2;
 constexpr uint64_t kWaveList = 150;                     // mean list length up to which: kSortWaves,
 constexpr uint64_t kWaveListMany = 400;                 // and up to which in frames of many tiles
-constexpr int64_t kManyTiles = 8192;
+constexpr int64_t kManyTiles = 8192, kFewTiles = 2048;  // below: never kSortWaves
 constexpr uint64_t kDenseList = 1024;                   // and above which: kSortDense
 constexpr int kSortItems = 8;                           // keys per thread: lists up to 2048 (dense: 4096) on chip
 constexpr int kWaveItems = 8;                           // keys per lane of a wavefront's list
@@ -1677,7 +1679,7 @@ hipError_t launch_bin_sort(const gs_frame& f, const gs_raster_cfg& cfg, const ui
                       dim3(sort_block(form)), 0, s, meta, ranges, f.n_tiles, bins.vals, w.longq, plan);
         };
         uint64_t chunk = sort_chunk(kSortBlocks);
-        if (bins.capacity <= uint64_t(nt) * (nt >= kManyTiles ? kWaveListMany : kWaveList))
+        if (nt >= kFewTiles && bins.capacity <= uint64_t(nt) * (nt >= kManyTiles ? kWaveListMany : kWaveList))
             sort(k_tile_sort<kSortWaves>, kSortWaves, (nt + 3) / 4);
         else if (bins.capacity <= uint64_t(nt) * kDenseList) sort(k_tile_sort<kSortBlocks>, kSortBlocks, nt);
         else {
