@@ -1070,3 +1070,46 @@ def test_bins_by_strips_of_many_and_narrow_views(jobs, n, tx, ty, room):
         m[rng.random(n) < 0.1] = [0xffffffff, 0, 0, 0]
     pairs = int(meta[:, 1].sum())
     _expect_bins(frame, _bins_of(frame, cfg, meta, 2 * pairs if room == "all" else pairs // 2), meta)
+
+
+@pytest.mark.parametrize("form", ["waves", "blocks", "dense"])
+@pytest.mark.parametrize("depths", ["uniform", "equal", "clusters", "octaves", "ulps"])
+def test_tile_sort_forms_by_list_length_and_depths(form, depths):
+    """As test_bins_bit_exact_list_lengths_and_depths on frames that take the
+    tile sort: 70,000 records, most of them culled, so that neither one launch
+    nor strips make the bins, and for the wavefronts' form 2,080 tiles with
+    pair capacity for 150 entries each (workgroups of 256: 1024, of 512:
+    1200, in 80 tiles).  Wavefronts' lists of 2 to 512 entries have crowded
+    buckets (equal depths, clusters, octaves) and depths within fewer values
+    than buckets (ulps)."""
+    rng = np.random.default_rng(7)
+    lengths = [0, 1, 2, 3, 63, 64, 65, 128, 129, 200, 256, 257, 400, 511, 512, 513, 1025, 2047, 2048, 2049]
+    tx, ty, per_tile = {"waves": (40, 52, 150), "blocks": (8, 10, 1024), "dense": (8, 10, 1200)}[form]
+    if form != "waves":
+        lengths += [4095, 4096, 4097, 9000]
+    cam = scenes.look_at([0.0, 0.0, 3.0], [0, 0, 0], 16 * tx, 16 * ty, 100.0, 100.0)
+    cfg = gs.raster_cfg((16, 16, -1))
+    at = rng.permutation(tx * ty)[:len(lengths)]
+    tiles = rng.permutation(np.repeat(at, lengths))               # of the visible records, in order
+    n, m = 70_000, len(tiles)
+    d = {"uniform": 1.0 + 3.0 * rng.random(m), "equal": np.full(m, 2.5),
+         "clusters": np.where(rng.random(m) < 0.5, 1.0, 4.0) + 1e-6 * rng.random(m),
+         "octaves": 2.0 ** rng.uniform(-2, 120, m), "ulps": np.full(m, 2.0)}[depths].astype(np.float32)
+    bits = d.view(np.uint32).copy()
+    if depths == "ulps":
+        bits += rng.integers(0, 40, m).astype(np.uint32)
+    meta = np.zeros((n, 4), np.uint32)
+    meta[:, 0] = 0xffffffff
+    rec = np.sort(rng.permutation(n)[:m])
+    meta[rec, 0], meta[rec, 1] = bits, 1
+    meta[rec, 2] = meta[rec, 3] = (tiles % tx) | (tiles // tx << 16)
+    frame = gs.Frame([cam], [gs.JobSpec(0, 0, n, 1.0)], cfg)
+    assert frame.n_tiles == tx * ty and m <= per_tile * tx * ty
+    gs.profile_set(["k_tile_sort", "k_bin_small", "k_bin_strips"])
+    try:
+        buf = _bins_of(frame, cfg, meta, per_tile * tx * ty)
+        ran = [gs.profile_get(k)[1] for k in ("k_tile_sort", "k_bin_small", "k_bin_strips")]
+    finally:
+        gs.profile_set(None)
+    assert ran == [1, 0, 0]
+    _expect_bins(frame, buf, meta)
