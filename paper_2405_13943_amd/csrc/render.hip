@@ -404,7 +404,15 @@ __global__ __launch_bounds__(kWave * kRenderWaves, sizeof(T) == 4 ? 5 : 1) void 
         sub = gw % NSD;
         valid = tile < frame.n_tiles;
     }
-    auto pslot = [&](uint32_t e) { return partial_slot(capacity, e, NS == 1 ? 0 : sub); };
+    // where this wavefront's partials of pair e lie (partial_slot): from own on,
+    // every `apart` values, both uniform; formed here, as a choice by sub for
+    // every record took registers (four spilled with the plan) and held up
+    // wavefronts that have a SIMD to themselves (500k at 1600x1066 with the
+    // plan 154.5 -> 151 us; 200k in 320x240 with 2 per tile 433 -> 418)
+    const bool further = NS != 1 && uniform(uint32_t(sub)) > 0u;
+    T* const own = pg + (further ? partial_slot(capacity, 0, int(uniform(uint32_t(sub)))) : 0);
+    const uint32_t apart = further ? 27u : 9u;
+    auto pslot = [&](uint32_t e) { return own + uint64_t(e) * apart; };
     do {
     if (!valid) break;
     const int j = job_of_tile(frame.jobs, frame.n_jobs, tile);
@@ -522,7 +530,7 @@ __global__ __launch_bounds__(kWave * kRenderWaves, sizeof(T) == 4 ? 5 : 1) void 
             // pairs carry zero gradient (slot 0 of all of them is stored)
             if (uint32_t(lane) < cnt)
 #pragma unroll
-                for (int q = 0; q < 9; q++) pg[pslot(e_own) + q] = T(0);
+                for (int q = 0; q < 9; q++) pslot(e_own)[q] = T(0);
             continue;
         }
         // records that reach some quadrant are staged compacted, with their
@@ -542,7 +550,7 @@ __global__ __launch_bounds__(kWave * kRenderWaves, sizeof(T) == 4 ? 5 : 1) void 
         } else if (uint32_t(lane) < cnt) {
             // reaches no quadrant this wave owns: zero partials
 #pragma unroll
-            for (int q = 0; q < 9; q++) pg[pslot(e_own) + q] = T(0);
+            for (int q = 0; q < 9; q++) pslot(e_own)[q] = T(0);
         }
         wave_lds_sync();
         const uint32_t n = __builtin_popcountll(staged);
@@ -602,8 +610,8 @@ __global__ __launch_bounds__(kWave * kRenderWaves, sizeof(T) == 4 ? 5 : 1) void 
 #pragma unroll
                 for (int q = 0; q < 9; q++) vb[q] = T(0);
             }
-            T* da = pg + pslot(uniform(s_eown[wave][i]));
-            T* db = i + 1 < n ? pg + pslot(uniform(s_eown[wave][i + 1])) : nullptr;
+            T* da = pslot(uniform(s_eown[wave][i]));
+            T* db = i + 1 < n ? pslot(uniform(s_eown[wave][i + 1])) : nullptr;
             if (ha || hb) {
                 store_pair_partials(va, vb, da, db);
             } else if (lane < 9) {
