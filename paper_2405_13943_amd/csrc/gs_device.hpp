@@ -137,14 +137,18 @@ __device__ inline int adaptive_waves(uint32_t count, uint32_t pairs, int n_tiles
 // alone would outlast the launch: when it is longer than the entries per
 // resident wavefront by some factor, so the line moves with n_tiles / resident
 // wavefronts, in units of the mean list length; below some 5,000 tiles the
-// plan's 1.25 (forward) and 2 (backward) times the mean take over.  Splitting
-// below the line repeats staging and, in the backward, each record's
-// reduction and store for nothing.  Measured, us with every tile above 1.25x
-// the mean split / with the line here / with no split (1600x1066 unless
-// noted; Gaussians of the scale scene):
-//   backward: 500k 201-217 / 164 / 184; 3M 775 / 467 / 443; three 1280x720
-//             views of 800k 692 / 542 / 542; four views of 1.5M 2073 / 1551 /
-//             1551; 500k at 979x651 227 / 218 / 334;
+// plan's 1.25 (forward) and 2 (backward; below 2,400 tiles 1.5) times the mean
+// take over.  Splitting below the line repeats staging and, in the backward,
+// each record's reduction and store for nothing.  Measured, us with every tile
+// above 1.25x the mean split / with the line here / with no split (1600x1066
+// unless noted; Gaussians of the scale scene; three views: 1280x720, 800x600
+// and 1920x1080):
+//   backward: 500k 201-217 / 164 / 184; 3M 775 / 467 / 443; three views of
+//             800k 692 / 542 / 542; four views of 1.5M 2073 / 1551 / 1551;
+//             500k at 979x651 227 / 218 / 334;
+//             the whole backward above 1.5x / 2x the mean: 500k 304 / 304 at
+//             1,520 tiles, 278 / 277 at 1,900, 236 / 232 at 2,542, and the
+//             parity scene's 200k 264 / 315, 229 / 275, 226 / 238;
 //   forward:  500k 68-74 / 68 / 99; 3M 201 / 200 / 204; three views of 800k
 //             213 / 183 / 202; four of 1.5M 602 / 530 / 530.
 // Line in half means, rounded: the bucket from which tiles are split.
@@ -154,7 +158,8 @@ __host__ __device__ inline int fwd_split_bucket(int n_tiles) {
 }
 __host__ __device__ inline int bwd_split_bucket(int n_tiles) {
     const int b = (n_tiles + 560) / 1120;      // 1.83 x entries per wavefront at 4 per SIMD
-    return b < 4 ? 4 : b;
+    const int least = n_tiles < 2400 ? 3 : 4;
+    return b < least ? least : b;
 }
 
 // The plan a pass runs (word 3 of the plan array holds the share of the list
