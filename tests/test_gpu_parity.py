@@ -1113,3 +1113,53 @@ def test_tile_sort_forms_by_list_length_and_depths(form, depths):
         gs.profile_set(None)
     assert ran == [1, 0, 0]
     _expect_bins(frame, buf, meta)
+
+
+@pytest.fixture(scope="module")
+def many_tiles(cfg1):
+    """2,000 Gaussians of the parity scene, one of them spanning the image, in
+    3,776 tiles: above every tile count up to which a launch takes more
+    wavefronts than the configuration's one or the plan's."""
+    w, h = 1024, 944
+    p = cfg1.params.copy()
+    p[scenes.LOGSCALE:scenes.LOGSCALE + 3, 7] = -0.5
+    cam = scenes.look_at([3 * math.sin(0.3), 0.0, 3 * math.cos(0.3)], [0, 0, 0], w, h, 1.2 * w, 1.2 * w)
+    target = torch.rand(3 * w * h, generator=torch.Generator().manual_seed(5))
+
+    def run(tile, dtype, share):
+        params = torch.from_numpy(p).to("cuda", dtype)
+        cfg = gs.raster_cfg(tile)
+        frame = gs.Frame([cam], [gs.JobSpec(0, 0, p.shape[1], 1.0)], cfg)
+        assert frame.n_tiles > 3600
+        buf = gs.Buffers(frame, 1 << 18, dtype)
+        buf.share_qmask = share
+        gs.rasterize(params, frame, cfg, buf)
+        assert 2 * gs.read_counters(buf)["pairs"] < buf.capacity          # room for the loss's sum
+        grad = torch.full_like(params, float("nan"))
+        loss = torch.zeros(1, dtype=dtype, device="cuda")
+        gs.render_bwd(params, frame, cfg, buf, grad, gs.LOSS_L1, target.to("cuda", dtype), loss)
+        return buf.rgb, buf.T, buf.ncontrib, grad, loss
+
+    return run
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("tile", [(16, 16, 1), (16, 16, -1), (16, 16, 1, -1), (16, 16, -1, 1), (16, 16, 4, 1),
+                                  (16, 16, 1, 4), (16, 16, 4, -1), (32, 8, 1), (32, 8, -1), (32, 8, -1, 2)])
+def test_one_wavefront_and_the_plan_in_frames_of_many_tiles(many_tiles, tile, dtype):
+    """The kernels of one wavefront per tile and of the plan, which smaller
+    frames do not reach, in both precisions and mixed with splits: the images
+    of two wavefronts per tile set outright bit for bit, its gradients up to
+    the order of their sums, its loss; and the same bits, the loss's among
+    them, whether the backward takes the forward's quadrant masks or makes
+    its own."""
+    rgb, T, nc, grad, loss = many_tiles(tile, dtype, True)
+    ref = many_tiles((*tile[:2], 2), dtype, True)
+    assert torch.equal(rgb, ref[0]) and torch.equal(T, ref[1]) and torch.equal(nc, ref[2])
+    # the same terms in another order: per plane, against the plane's norm
+    bound = 1e-4 if dtype == torch.float32 else 1e-12
+    a, b = grad.double(), ref[3].double()
+    assert ((a - b).norm(dim=1) <= bound * b.norm(dim=1) + 1e-12).all()
+    torch.testing.assert_close(loss, ref[4], rtol=1e-5 if dtype == torch.float32 else 1e-12, atol=0)
+    own = many_tiles(tile, dtype, False)
+    assert all(torch.equal(x, y) for x, y in zip((rgb, T, nc, grad, loss), own))
