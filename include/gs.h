@@ -138,13 +138,17 @@ typedef struct {
     float bg[3];             /* 0, 0, 0 */
     int16_t fwd_waves;       /* wavefronts per tile in the forward and in the backward */
     int16_t bwd_waves;       /* compositing, each owning an equal part of the tile and walking
-                                the whole list: 1 (0 = 1), 2 (16x8, 16x16, 32x8) or 4 (16x16,
-                                32x8); GS_WAVES_ADAPTIVE picks 1, 2 or 4 per tile from its
-                                list length against the frame mean and the tiles of the frame
-                                (at most 4 above 4x the mean, 2 above 1.25x; needs
-                                gs_bins.tile_order).  Frames of few tiles take more than
-                                1 or the plan's count where that fills the chip.  Images do not depend
-                                on them; gradients only through the order of their sums. */
+                                the whole list.  2 (16x8, 16x16, 32x8) and 4 (16x16, 32x8):
+                                so many in every frame.  1 (0 = 1): at least one; in frames of
+                                so few tiles that one each leaves most of the chip idle, 4
+                                (forward up to 1,800 tiles, backward 1,000) or 2 (3,600,
+                                1,400), at most the tile's 8x8 quadrants.  GS_WAVES_ADAPTIVE
+                                (needs gs_bins.tile_order): 1, 2 or 4 per tile from its list
+                                length against the frame mean and the tiles of the frame (at
+                                most 4 above 4x the mean, 2 above 1.25x); 4 for every tile in
+                                frames up to 1,800 (backward 1,400) tiles.  Images do not
+                                depend on them; gradients only through the order of their
+                                sums. */
 } gs_raster_cfg;
 
 #define GS_WAVES_ADAPTIVE (-1)

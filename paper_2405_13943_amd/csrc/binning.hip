@@ -471,9 +471,9 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ tke
 // That is a constant number of LDS round trips per key, where merging sorted
 // runs takes one dependent pair per key and round of log2(n / 8) rounds, with
 // a binary search each: at lists of 1,300 (the 6M-Gaussian view) 165 -> 84 us
-// a launch, at 760 (three 640x417 views of 100k) 41 -> 24.  Depths so clustered that a bucket holds more than kBucketMost
-// keys are merge-sorted instead (workgroups) or ranked by comparison
-// (wavefronts).
+// a launch, at 760 (three 640x417 views of 100k) 41 -> 24.  Depths so clustered
+// that a bucket holds more than kBucketMost keys are merge-sorted instead
+// (workgroups) or ranked by comparison (wavefronts).
 //
 // Three forms, by the frame's mean list length (pair capacity / tiles, which
 // includes the caller's headroom):
@@ -803,7 +803,7 @@ __device__ void wave_sort(const uint4* __restrict__ meta, uint32_t* __restrict__
     for (int k = 0; k < kWaveItems; k++)
         if (lane + uint32_t(k) * kWave < n) rank[k] = atomicAdd(&cnt[bucket(d[k])], 1u);
     wave_lds_order();
-    // lane: buckets 4 lane .. 4 lane + 3
+    // lane: buckets kWaveItems lane .. kWaveItems lane + kWaveItems - 1
     uint32_t c[kWaveItems], sum = 0u, most = 0u;
 #pragma unroll
     for (int k = 0; k < kWaveItems; k++) {

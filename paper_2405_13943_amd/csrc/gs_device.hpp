@@ -338,20 +338,6 @@ __device__ inline double row_sum_last(double v) {
     return v;
 }
 
-// Sum over each row of 16 lanes, returned to every lane of the row.
-__device__ inline float row_sum(float v) {
-    v += dpp_move<0xb1, 0xf>(v);   // quad_perm [1,0,3,2]
-    v += dpp_move<0x4e, 0xf>(v);   // quad_perm [2,3,0,1]
-    v += dpp_move<0x124, 0xf>(v);  // row_ror:4
-    v += dpp_move<0x128, 0xf>(v);  // row_ror:8
-    return v;
-}
-
-__device__ inline double row_sum(double v) {
-    for (int off = 8; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
-    return v;
-}
-
 __device__ inline double wave_sum(double v) {
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
     return v;
@@ -396,16 +382,6 @@ __device__ inline uint32_t wave_max_u32(uint32_t v) {
     for (int off = 32; off >= 1; off >>= 1) {
         const uint32_t o = __shfl_xor(v, off, kWave);
         v = o > v ? o : v;
-    }
-    return v;
-}
-
-// inclusive prefix sum over the lanes of a wave
-__device__ inline uint32_t wave_incl_scan(uint32_t v) {
-    const int lane = lane_id();
-    for (int off = 1; off < kWave; off <<= 1) {
-        uint32_t t = __shfl_up(v, off, kWave);
-        if (lane >= off) v += t;
     }
     return v;
 }

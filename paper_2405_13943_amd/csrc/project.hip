@@ -704,7 +704,7 @@ __global__ __launch_bounds__(kAccBlock, sizeof(T) == 4 ? 4 : 1) void k_project_b
         }
         __syncthreads();
     }
-    if (frame.n_jobs == 0)
+    if (frame.n_jobs == 0)      // a frame filled by hand: a planned one without jobs counts as disjoint
         for (int i = wave; i < SETS * A; i += NW) {
             const int64_t gs_ = first + (i / A) * kWave + lane;
             if (gs_ < n) grad[int64_t(i % A) * gstride + gs_] = T(0);
