@@ -491,8 +491,12 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ tke
 //               hide it (us, waves / blocks: 1,536 tiles of mean 169 24 / 11,
 //               6,767 of 172 28 / 26, 9,126 of 147 21 / 32, 2,752 of 111
 //               12 / 12, 6,767 of 65 14 / 19; all bins, 1,080 of 110 54 / 49,
-//               of 58 49 / 48, 2,542 of 58 51 / 52); short lists by
-//               comparison;
+//               of 58 49 / 48, 2,542 of 58 51 / 52, 9,000 of 189 108 / 113, of
+//               247 130 / 135, of 329 151 / 147, 14,400 of 193 133 / 155, of
+//               295 206 / 228, of 304 212 / 223); short lists by comparison.
+//               (Even lists of 115 to 200 in 4,000 to 7,000 tiles would do
+//               better as waves, 68 / 73, uneven ones of that mean worse, 92 /
+//               79: the capacity does not tell them apart);
 //   kSortDense  one list per workgroup of 512, up to 4096 on chip.
 // k_tile_sort_long takes the longer lists, one large workgroup each, by
 // merging: every thread sorts E consecutive keys in registers (a sorting

@@ -361,7 +361,12 @@ constexpr int kConsGrid = 512;            // two per CU: all resident
 // launch is then one or two trips through its dependent loads (holders,
 // columns, planes), and the wide form's further trips cost more than its
 // accesses save: 45k ids of four blocks, SH 3, 21 us narrow and 24 wide; 130k
-// 42 and 45; 200k 58 and 57; 400k 116 and 114 (1.9M 578 and 541).
+// 42 and 45; 200k 58 and 57; 400k 116 and 114 (1.9M 578 and 541).  Against the
+// kernel of 64 ids by all planes a workgroup, by that / narrow / wide (a tenth
+// of the ids held twice): 20k 15 / 14 / -, 90k 33 / 28 / -, 140k 44 / 40 / 40,
+// 200k 53 / 52 / 51, 260k 65 / 66 / 73, 300k 70 / 73 / 71, 700k 197 / 195 / 190;
+// and with a fifth held three times, which the wide form takes one by one:
+// 140k 51 / 48 / 53, 260k 84 / 85 / 97, 400k 141 / 138 / 148, 700k 263 / 254 / 268.
 constexpr int64_t kConsNarrow = 131072;
 
 template <int DEG, bool RELAX, bool RESID, bool WIDE>

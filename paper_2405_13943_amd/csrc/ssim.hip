@@ -17,10 +17,11 @@
 //   k_ssim_bwd  blurs the three maps and combines them with x and y into
 //               dL/dC (plus the L1 term), the external gradient of the
 //               compositing backward.
-// Both are bound by VALU issue, most of it the blurs' multiply-adds, written
-// as fused ones (the rest of the library compiles with contraction off): the
-// passes took 63 and 50 us at 1600 x 1066 with five window sums and separate
-// multiplies and adds, and 50 and 46 as they are.
+// The blurs' multiply-adds are fused ones (the rest of the library compiles
+// with contraction off): with five window sums and separate multiplies and
+// adds the forward issued VALU instructions in 76% of the slots, 63 us at 1600
+// x 1066, the backward in 56%, 50 us; as they are 58% and 38%, 47 and 46 us,
+// between LDS accesses and the stages' barriers.
 // (A grid over every binning tile, with three of four workgroups exiting at
 // once, spent 40% of its time dispatching workgroups that did nothing.)
 #include "gs_device.hpp"
